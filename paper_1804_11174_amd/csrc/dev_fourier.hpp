@@ -1,0 +1,616 @@
+#pragma once
+// Device pieces of the Fourier-moment evaluation of the von Mises CV
+// objective (Sec. II.B, Eq. cv_def), shared by the CV scan (cv.hip), the
+// Fourier entry points (fourier.hip) and the batched engine (batch.hip):
+// the moments of the particle angles and the series over them.
+//
+// Moments S_m = sum_j exp(i m theta_j), m = 1..M, theta = 2 pi x / L. With a
+// step s and m = s a + b or s a - b, 0 <= b <= (s - 1) / 2, the real and
+// imaginary parts of both modes are sums and differences of four real
+// products,
+//   sum cos(s a theta) cos(b theta),  sum sin(s a theta) sin(b theta),
+//   sum sin(s a theta) cos(b theta),  sum cos(s a theta) sin(b theta),
+// so all of them are one real matrix product over the particles, [cos, sin](s
+// a theta) by [cos, sin](b theta): 2 multiply-adds per particle and mode on
+// the FP64 matrix cores, and only about sqrt(M) phases per particle, against
+// 6 operations of a rotation and two additions per particle and mode (and a
+// fresh phase every 16 modes) on the vector pipe. A workgroup stages the
+// phases of 64 particles at a time in LDS and four waves multiply them out
+// (v_mfma_f64_16x16x4: 8 values of a by the cosines or sines of 16 values
+// of b, four particles per instruction). Every phase table entry is at
+// most 7 rotations from a phase reduced mod 1 exactly, evaluated from a
+// table of 256 unit vectors and a short polynomial.
+//   wide   (M > 112): s = 31, b <= 15; a workgroup holds 32 values of a (8
+//          per wave), 976 modes and more by further mode blocks; a wave
+//          whose tile of a is not needed takes a share of the particles.
+//          Two teams of four waves work in opposite phases: while one
+//          generates a group's phases (vector pipe), the other multiplies
+//          its own (matrix pipe).
+//   narrow (M <= 112): s = 15, b <= 7, 8 values of a: one tile holds every
+//          mode, and each wave takes its own groups of 64 particles, with
+//          no barrier between the waves.
+// The matrix instruction and the vector FMAs share a SIMD's FP64 units, so
+// what bounds it is their sum: the products (2 operations per particle and
+// mode) and the phases. Measured on MI355X against the kernel of rotations
+// (6 operations per particle and mode and two phases every 16 modes): 65,536
+// particles to order 911 in 10.2 us (47.6), 1,048,576 to order 46 in 18.8 us
+// (49.0), to order 911 in 111 us (39 TFLOP/s; the products alone 76 us).
+//
+// Layout of the double instruction (one value per lane for A and B, four for
+// C): lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and, in element r,
+// C[4 r + l / 16][l % 16].
+#include <cmath>
+
+#include "dev_layout.hpp"
+#include "kde_internal.hpp"
+
+namespace kde {
+
+using f64x4 = double __attribute__((ext_vector_type(4)));
+
+constexpr double kFourierTail = 1e-18;  // rho_M below this ends the series
+constexpr int kMomGroup = 64;           // particles whose phases are in LDS at a time (per wave when narrow)
+constexpr int kMomPad = kMomGroup + 2;  // padded so that the 8 or 16 rows read together lie in different banks
+constexpr int kWideStep = 31, kWideB = 16, kWideA = 32;  // mode block: a < 32
+constexpr int kNarrowStep = 15, kNarrowB = 8, kNarrowA = 8;
+constexpr int kNarrowMax = kNarrowStep * (kNarrowA - 1) + kNarrowB - 1;  // 112
+constexpr int kWideModes = kWideStep * kWideA;                          // modes a further mode block adds
+constexpr int kMomBlock = 512;          // threads of a moment workgroup: two teams, or eight waves
+constexpr int kMomTeam = 256;
+constexpr int kMomWaves = kMomBlock / 64;
+constexpr int64_t kMomChunks = 256;     // particle chunks a launch aims for (one workgroup per CU: its LDS)
+
+// How the moments of n particles to order M are cut: a function of (n, M)
+// alone, so the one-set calls and the batched engine sum the same partials
+// in the same order.
+struct MomentPlan {
+  int M;
+  int narrow;
+  int mblocks;  // mode blocks
+  int tiles;    // wide: tiles of 8 a in a mode block (the last block may need fewer)
+  int ks;       // wide: waves sharing a tile (each a share of the particles, with rows of their own)
+  int na;       // values of a (narrow)
+  int64_t per;  // particles per chunk
+  int64_t chunks, rows;
+};
+
+__host__ __device__ inline MomentPlan moment_plan(int64_t n, int M) {
+  MomentPlan p{};
+  p.M = M;
+  p.narrow = M <= kNarrowMax ? 1 : 0;
+  if (p.narrow) {
+    p.mblocks = p.tiles = p.ks = 1;
+    p.na = M <= kNarrowB - 1 ? 1 : (M - (kNarrowB - 1) + kNarrowStep - 1) / kNarrowStep + 1;
+    p.per = kMomBlock * ceil_div(ceil_div(n, kMomBlock), kMomChunks);
+    p.chunks = ceil_div(n, p.per);
+    p.rows = p.chunks;
+    return p;
+  }
+  const int na = (M - (kWideB - 1) + kWideStep - 1) / kWideStep + 1;
+  p.mblocks = (na + kWideA - 1) / kWideA;
+  p.tiles = p.mblocks > 1 ? 4 : (na + 7) / 8;
+  p.ks = p.tiles == 1 ? 4 : (p.tiles == 2 ? 2 : 1);
+  const int64_t aim = kMomChunks / p.mblocks > 1 ? kMomChunks / p.mblocks : 1;
+  p.per = 2 * kMomGroup * ceil_div(ceil_div(n, 2 * kMomGroup), aim);  // the teams take groups in turn
+  p.chunks = ceil_div(n, p.per);
+  p.rows = p.chunks * p.ks;
+  return p;
+}
+
+// Phase exp(i 2 pi m f) for f in [0, 1]: m f reduced mod 1 with its
+// rounding error recovered, so the angle is exact to a few units of f's
+// last place times m.
+__device__ __forceinline__ void phase(int m, double f, double& c, double& s) {
+  const double t = double(m) * f;
+  const double e = fma(double(m), f, -t);
+  const double fr = (t - floor(t)) + e;
+  sincospi(2.0 * fr, &s, &c);
+}
+
+// Position as a fraction of the period: wrap_d(x, L) / L. For x inside [0, L)
+// the quotient comes from the reciprocal and one correction (within a
+// rounding unit of the division), elsewhere from the wrap.
+__device__ __forceinline__ double period_fraction(double x, double L, double inv_L) {
+  const double q0 = x * inv_L;
+  const double q = fma(fma(-q0, L, x), inv_L, q0);
+  return (q0 >= 0.0 && q0 < 1.0) ? q : wrap_d(x, L) / L;
+}
+
+// exp(i 2 pi j / 256), one entry per thread of the first kMomTeam.
+__device__ __forceinline__ void unit_table_fill(double2* unit) {
+  if (threadIdx.x < 256) {
+    double s, c;
+    sincospi(double(threadIdx.x) / 128.0, &s, &c);
+    unit[threadIdx.x] = double2{c, s};
+  }
+}
+
+// phase() from the table: m f = k / 256 + r mod 1, |r| <= 1/512 (and the
+// product's rounding error), then exp(i 2 pi r) by its Taylor series (|2 pi
+// r| <= 0.0123: the first terms left out are below 2e-20) times the table
+// entry. Its error is about a rounding unit, absolute, like that of the
+// rotations that follow; sincospi's relative accuracy near the axes is not
+// needed in a sum.
+__device__ __forceinline__ double2 table_phase(double m, double f, const double2* unit) {
+  const double t = m * f;
+  const double e = fma(m, f, -t);
+  const double k = rint(t * 256.0);
+  const double r = fma(k, -1.0 / 256.0, t) + e;
+  const double2 u = unit[int(k) & 255];
+  const double x = r * 6.283185307179586;
+  const double x2 = x * x;
+  const double cm = x2 * fma(x2, fma(x2, -1.0 / 720.0, 1.0 / 24.0), -0.5);  // cos - 1
+  const double sn = x * fma(x2, fma(x2, fma(x2, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0), 1.0);
+  return double2{fma(u.x, cm, fma(-u.y, sn, u.x)), fma(u.y, cm, fma(u.x, sn, u.y))};
+}
+__device__ __forceinline__ double2 rotate(double2 z, double2 w) {
+  return double2{fma(z.x, w.x, -(z.y * w.y)), fma(z.y, w.x, z.x * w.y)};
+}
+
+struct MomSmem {
+  // narrow: 16 rows per wave; wide: 48 rows per team
+  double2 z[kMomWaves * (kNarrowA + kNarrowB) * kMomPad];
+  double2 unit[256];
+};
+
+// One (chunk, mode block) of the wide form; `rows` points at the chunk's ks
+// partial rows of 2 M doubles. Every thread of the workgroup must call this.
+template <typename T>
+__device__ __forceinline__ void moments_wide(const T* __restrict__ x, int64_t lo, int64_t hi, double L,
+                                             const MomentPlan& p, int mb, double* __restrict__ rows, MomSmem& sm,
+                                             uint32_t* status) {
+  const int tid = threadIdx.x, lane = tid & 63, team = tid / kMomTeam, w = (tid % kMomTeam) >> 6;
+  double2(*za)[kMomPad] = reinterpret_cast<double2(*)[kMomPad]>(sm.z) + team * (kWideA + kWideB);
+  double2(*zb)[kMomPad] = za + kWideA;
+  const int i16 = lane & 15, k4 = lane >> 4;
+  const int tile = w % p.tiles, slice = w / p.tiles;  // slice < ks: this wave multiplies
+  const int steps = (kMomGroup / 4) / p.ks;
+  const int M = p.M;
+  const double inv_L = 1.0 / L;
+  // values of a this mode block needs
+  const int na = (M - (kWideB - 1) + kWideStep - 1) / kWideStep + 1 - kWideA * mb;
+  const bool gen = 8 * w < na;  // wave w also generates the phases of a = 8 w ..
+  const bool mul = slice < p.ks && 8 * tile < na;
+  const double m_a = double(kWideStep * (kWideA * mb + 8 * w));
+  f64x4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+  const int groups = int((hi - lo + kMomGroup - 1) / kMomGroup);
+  const double* arow = reinterpret_cast<const double*>(&za[8 * tile + (i16 & 7)][0]) + (i16 >> 3);
+  const double2* brow = zb[i16];
+  const int p0 = 4 * steps * slice + k4;
+  int64_t j = lo + team * kMomGroup + lane;
+  T xn = j < hi ? x[j] : T(0);
+  // interval t: the team of t's parity generates group t, the other
+  // multiplies group t - 1
+  for (int t = 0; t <= groups; ++t) {
+    if ((t & 1) == team) {
+      if (t < groups) {
+        const bool valid = j < hi;
+        const double xv = double(xn);
+        j += 2 * kMomGroup;
+        xn = j < hi ? x[j] : T(0);  // this team's next group, in flight over this one's work
+        if (mb == 0 && w == 0) note_numeric(status, !isfinite(xv), false);
+        const double f = period_fraction(xv, L, inv_L);
+        const double2 z1 = table_phase(1.0, f, sm.unit);
+        double2 z = table_phase(double(4 * w), f, sm.unit);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          zb[4 * w + k][lane] = valid ? z : double2{0.0, 0.0};
+          z = rotate(z, z1);
+        }
+        if (gen) {
+          const double2 zs = table_phase(double(kWideStep), f, sm.unit);
+          z = table_phase(m_a, f, sm.unit);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            za[8 * w + k][lane] = z;
+            z = rotate(z, zs);
+          }
+        }
+      }
+    } else if (t >= 1 && mul) {
+      auto product = [&](auto count) {
+        constexpr int kSteps = decltype(count)::value;
+        double av[kSteps];
+        double2 bv[kSteps];
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+          av[u] = arow[2 * (p0 + 4 * u)];
+          bv[u] = brow[p0 + 4 * u];
+        }
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) {
+          acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u].x, acc0, 0, 0, 0);
+          acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u].y, acc1, 0, 0, 0);
+        }
+      };
+      if (p.ks == 1)
+        product(std::integral_constant<int, kMomGroup / 4>{});
+      else if (p.ks == 2)
+        product(std::integral_constant<int, kMomGroup / 8>{});
+      else
+        product(std::integral_constant<int, kMomGroup / 16>{});
+    }
+    __syncthreads();
+  }
+  // the second team's sums are added to the first's
+  double* red = reinterpret_cast<double*>(sm.z);
+  if (team == 1) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      red[r * kMomTeam + tid - kMomTeam] = acc0[r];
+      red[(4 + r) * kMomTeam + tid - kMomTeam] = acc1[r];
+    }
+  }
+  __syncthreads();
+  if (team == 0 && mul) {
+    double* out = rows + int64_t(slice) * 2 * M;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      acc0[r] += red[r * kMomTeam + tid];
+      acc1[r] += red[(4 + r) * kMomTeam + tid];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int a = kWideA * mb + 8 * tile + 4 * h + k4, b = i16;
+      const double cc = acc0[h], sc = acc0[h + 2], cs = acc1[h], ss = acc1[h + 2];
+      const int mp = kWideStep * a + b, mm = kWideStep * a - b;
+      if (mp >= 1 && mp <= M) {
+        out[2 * (mp - 1)] = cc - ss;
+        out[2 * (mp - 1) + 1] = sc + cs;
+      }
+      if (a >= 1 && b >= 1 && mm <= M) {
+        out[2 * (mm - 1)] = cc + ss;
+        out[2 * (mm - 1) + 1] = sc - cs;
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// One chunk of the narrow form; writes the chunk's row of 2 M doubles.
+template <typename T>
+__device__ __forceinline__ void moments_narrow(const T* __restrict__ x, int64_t lo, int64_t hi, double L,
+                                               const MomentPlan& p, double* __restrict__ out, MomSmem& sm,
+                                               uint32_t* status) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  double2(*za)[kMomPad] = reinterpret_cast<double2(*)[kMomPad]>(sm.z) + w * (kNarrowA + kNarrowB);
+  double2(*zb)[kMomPad] = za + kNarrowA;
+  const int i16 = lane & 15, k4 = lane >> 4;
+  const double* arow = reinterpret_cast<const double*>(&za[i16 & 7][0]) + (i16 >> 3);
+  const double* brow = reinterpret_cast<const double*>(&zb[i16 & 7][0]) + (i16 >> 3);
+  const double inv_L = 1.0 / L;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  int64_t j = lo + tid;
+  T xn = j < hi ? x[j] : T(0);
+  for (int64_t g = lo + 64 * w; g < hi; g += kMomBlock) {
+    const bool valid = j < hi;
+    const double xv = double(xn);
+    j += kMomBlock;
+    xn = j < hi ? x[j] : T(0);  // the next group's, in flight over this one's work
+    note_numeric(status, !isfinite(xv), false);
+    const double f = period_fraction(xv, L, inv_L);
+    const double2 z1 = table_phase(1.0, f, sm.unit);
+    const double2 zs = table_phase(double(kNarrowStep), f, sm.unit);
+    double2 z = {1.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kNarrowB; ++k) {
+      zb[k][lane] = valid ? z : double2{0.0, 0.0};
+      z = k == 0 ? z1 : rotate(z, z1);
+    }
+    z = {1.0, 0.0};
+    for (int k = 0; k < p.na; ++k) {
+      za[k][lane] = z;
+      z = rotate(z, zs);
+    }
+    // a wave's LDS accesses complete in order; the fences keep the compiler
+    // from moving them across each other
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < kMomGroup / 4; ++t)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(arow[2 * (4 * t + k4)], brow[2 * (4 * t + k4)], acc, 0, 0, 0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  // the waves' sums in wave order, then the modes from the products
+  double* red = reinterpret_cast<double*>(sm.z);  // the phases are no longer needed
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[(w * 64 + lane) * 4 + r] = acc[r];
+  __syncthreads();
+  if (w == 0) {
+    double v[4], u[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      v[r] = 0.0;
+      for (int q = 0; q < kMomWaves; ++q) v[r] += red[(q * 64 + lane) * 4 + r];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) u[r] = __shfl_xor(v[r], 8, 64);  // the sines' columns
+    const int b = i16;
+    if (b < kNarrowB) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int a = 4 * h + k4;
+        const double cc = v[h], sc = v[h + 2], cs = u[h], ss = u[h + 2];
+        const int mp = kNarrowStep * a + b, mm = kNarrowStep * a - b;
+        if (a < p.na && mp >= 1 && mp <= p.M) {
+          out[2 * (mp - 1)] = cc - ss;
+          out[2 * (mp - 1) + 1] = sc + cs;
+        }
+        if (a < p.na && a >= 1 && b >= 1 && mm <= p.M) {
+          out[2 * (mm - 1)] = cc + ss;
+          out[2 * (mm - 1) + 1] = sc - cs;
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Unit (chunk, mode block) of a set's moments into its partial rows, by a
+// workgroup of kMomBlock threads; sm.unit must be filled and visible.
+template <typename T>
+__device__ __forceinline__ void moments_unit(const T* __restrict__ x, int64_t n, double L, const MomentPlan& p,
+                                             int64_t chunk, int mb, double* __restrict__ partials, MomSmem& sm,
+                                             uint32_t* status) {
+  const int64_t lo = chunk * p.per, hi = min(n, lo + p.per);
+  if (p.narrow)
+    moments_narrow(x, lo, hi, L, p, partials + chunk * 2 * int64_t(p.M), sm, status);
+  else
+    moments_wide(x, lo, hi, L, p, mb, partials + chunk * p.ks * 2 * int64_t(p.M), sm, status);
+}
+
+// Sum of the partial rows, kRedCols columns per workgroup: thread (y, c)
+// adds rows y, y + 16, ... in order, then the 16 partial sums are added in
+// order. (Rows read by 16 threads side by side: the serial chain of a
+// column is rows / 16 additions.)
+constexpr int kRedCols = 16;
+
+__device__ __forceinline__ void moments_reduce(const double* __restrict__ partials, int64_t rows, int cols, int64_t cb,
+                                               double* __restrict__ S, double* red) {
+  const int c = threadIdx.x % kRedCols, y = threadIdx.x / kRedCols;
+  constexpr int ny = kBlock / kRedCols;
+  const int64_t col = cb * kRedCols + c;
+  double v = 0.0;
+  if (col < cols) {
+#pragma unroll 4
+    for (int64_t r = y; r < rows; r += ny) v += partials[r * cols + col];
+  }
+  red[threadIdx.x] = v;
+  __syncthreads();
+  if (y == 0 && col < cols) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < ny; ++q) t += red[q * kRedCols + c];
+    S[col] = t;
+  }
+  __syncthreads();
+}
+
+// -------------------------------------------------------------- the series
+
+// a b rescaled by a power of two (exact) so that products of many of these
+// non-negative matrices stay in range.
+struct Mat2 {
+  double a, b, c, d;
+};
+__device__ __forceinline__ Mat2 mat_norm(const Mat2& m) {
+  const double mx = fmax(fmax(m.a, m.b), fmax(m.c, m.d));
+  const int e = __builtin_amdgcn_frexp_exp(mx);  // 0 for zero
+  return Mat2{ldexp(m.a, -e), ldexp(m.b, -e), ldexp(m.c, -e), ldexp(m.d, -e)};
+}
+__device__ __forceinline__ Mat2 mat_mul(const Mat2& x, const Mat2& y) {
+  return mat_norm(Mat2{fma(x.a, y.a, x.b * y.c), fma(x.a, y.b, x.b * y.d), fma(x.c, y.a, x.d * y.c),
+                       fma(x.c, y.b, x.d * y.d)});
+}
+
+// Static LDS of the series of one concentration; its dynamic part is 2 (M +
+// 1) doubles (series_lds): the ratios, then |S_m|^2.
+struct ScanSmem {
+  Mat2 tot[kBlock / 64];
+  double ptot[kBlock / 64];
+  double red[kBlock / 64][3];
+};
+__host__ __device__ inline size_t series_lds(int M) { return size_t(2) * size_t(M + 1) * sizeof(double); }
+
+// A = sum_m rho_m^2 P_m, A0 = sum_m rho_m^2 (P_m - n), C = sum_m rho_m (P_m -
+// n), m = 1..M, P_m = |S_m|^2, for one concentration, by the whole workgroup
+// (the results reach thread 0).
+//
+// The backward recurrence r_m = kappa / (2m + kappa r_{m+1}) of r_m =
+// I_m/I_{m-1}, started at r_{Ms+1} = 0, applies the Mobius maps with matrices
+// [[0, kappa], [kappa, 2m]] to the vector (0, 1). Thread t composes the maps
+// of its run of consecutive m (non-negative matrices rescaled by powers of
+// two: no cancellation); a suffix product over the workgroup, by shuffles
+// inside a wave and one exchange between the waves, gives every run the
+// vector entering it; each thread walks its run on that vector (so the
+// divisions do not wait for each other) and keeps the ratios in LDS; rho_m
+// is their prefix product. The composition is a reassociation of the
+// recurrence; its rounding grows with the depth of the tree and not with
+// the length of the chain.
+__device__ __forceinline__ void series_sums(double kappa, int M, const double* __restrict__ S, double n,
+                                            double* __restrict__ dyn, ScanSmem& sm, double& A, double& A0, double& C) {
+  double* ratio = dyn;
+  double* pw = dyn + (M + 1);
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  constexpr int kWaves = kBlock / 64;
+  for (int m = 1 + t; m <= M; m += kBlock) {
+    const double sr = S[2 * (m - 1)], si = S[2 * (m - 1) + 1];
+    pw[m] = fma(sr, sr, si * si);
+  }
+  const int Ms = int(ceil(sqrt(double(M) * double(M) + 40.0 * kappa))) + 16;
+  const int len = (Ms + kBlock - 1) / kBlock;
+  const int lo = 1 + t * len, hi = min(Ms, (t + 1) * len);  // empty when lo > hi
+  Mat2 P{1.0, 0.0, 0.0, 1.0};
+  for (int m = hi; m >= lo; --m) {
+    const double m2 = 2.0 * double(m);
+    P = mat_norm(Mat2{kappa * P.c, kappa * P.d, fma(kappa, P.a, m2 * P.c), fma(kappa, P.b, m2 * P.d)});
+  }
+  // inclusive suffix products inside the wave
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const Mat2 o{__shfl_down(P.a, d, 64), __shfl_down(P.b, d, 64), __shfl_down(P.c, d, 64), __shfl_down(P.d, d, 64)};
+    const Mat2 q = mat_mul(P, o);
+    if (lane + d < 64) P = q;
+  }
+  if (lane == 0) sm.tot[w] = P;
+  __syncthreads();
+  // the vector entering this wave from the waves above, then this thread
+  double vx = 0.0, vy = 1.0;
+  for (int k = kWaves - 1; k > w; --k) {
+    const Mat2 T = sm.tot[k];
+    const double nx = fma(T.a, vx, T.b * vy), ny = fma(T.c, vx, T.d * vy);
+    const int e = __builtin_amdgcn_frexp_exp(fmax(nx, ny));
+    vx = ldexp(nx, -e);
+    vy = ldexp(ny, -e);
+  }
+  {
+    const Mat2 o{__shfl_down(P.a, 1, 64), __shfl_down(P.b, 1, 64), __shfl_down(P.c, 1, 64), __shfl_down(P.d, 1, 64)};
+    if (lane < 63) {
+      const double nx = fma(o.a, vx, o.b * vy), ny = fma(o.c, vx, o.d * vy);
+      vx = nx;
+      vy = ny;
+    }
+  }
+  double sp = 1.0;
+  for (int m = hi; m >= lo; --m) {
+    // (x, y) <- (kappa y, kappa x + 2m y), r_m = x / y; rescaled so that y ~ 1
+    const double nx = kappa * vy, ny = fma(kappa, vx, 2.0 * double(m) * vy);
+    const int e = __builtin_amdgcn_frexp_exp(ny);
+    vx = ldexp(nx, -e);
+    vy = ldexp(ny, -e);
+    if (m <= M) {
+      const double r = vx / vy;
+      ratio[m] = r;
+      sp *= r;
+    }
+  }
+  // exclusive prefix products of the runs' products
+  double pp = sp;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double o = __shfl_up(pp, d, 64);
+    if (lane >= d) pp *= o;
+  }
+  if (lane == 63) sm.ptot[w] = pp;
+  __syncthreads();  // also: every ratio and |S_m|^2 is in LDS
+  double p = __shfl_up(pp, 1, 64);
+  if (lane == 0) p = 1.0;
+  for (int k = 0; k < w; ++k) p *= sm.ptot[k];
+  const int hm = min(hi, M);
+  double a = 0.0, a0 = 0.0, c = 0.0;
+  for (int m = lo; m <= hm; ++m) {
+    p *= ratio[m];
+    const double Pm = pw[m], q = Pm - n, p2 = p * p;
+    a = fma(p2, Pm, a);
+    a0 = fma(p2, q, a0);
+    c = fma(p, q, c);
+  }
+  a = wave_sum(a);
+  a0 = wave_sum(a0);
+  c = wave_sum(c);
+  if (lane == 0) {
+    sm.red[w][0] = a;
+    sm.red[w][1] = a0;
+    sm.red[w][2] = c;
+  }
+  __syncthreads();
+  A = A0 = C = 0.0;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    A += sm.red[k][0];
+    A0 += sm.red[k][1];
+    C += sm.red[k][2];
+  }
+  __syncthreads();
+}
+
+// The objective and the pair sums of one concentration from the series.
+__device__ __forceinline__ double cv_of_series(double A, double C, double n, double L) {
+  return (2.0 * A / (n * n) - 4.0 * C / (n * (n - 1.0)) - 1.0) / L;
+}
+__device__ __forceinline__ double pair_sum_of_series(double D, double n, double L) {
+  return (n * n - n + 2.0 * D) / (2.0 * L);
+}
+
+// -------------------------------------------------------------------- host
+
+// Order at which the series of a concentration is cut: the smallest m with
+//   m asinh(m/k) - (sqrt(m^2 + k^2) - k) >= -log(kFourierTail),
+// from where on rho_m < kFourierTail: Amos's bounds I_nu(k) / I_{nu-1}(k) <=
+// k / (t + sqrt(t^2 + k^2)) = exp(-asinh(t/k)), t = nu - 1/2, give -log rho_m
+// >= the sum of asinh((nu - 1/2)/k) over nu <= m, and the midpoint sum of the
+// concave asinh is at least its integral over [0, m], the left-hand side.
+// Newton's method from above (the left-hand side is convex). rho_m grows
+// with kappa, so the order of the largest concentration serves a whole list.
+inline int fourier_order(double k) {
+  if (!(k > 0.0)) return 1;
+  static const double lim = -std::log(kFourierTail);
+  double m = std::sqrt(2.0 * lim * k) + 12.0;
+  for (int it = 0; it < 4; ++it) {
+    const double u = m / k, as = std::log(u + std::sqrt(u * u + 1.0));
+    m -= (m * as - m * m / (std::sqrt(m * m + k * k) + k) - lim) / as;
+  }
+  return int(std::ceil(m)) < 1 ? 1 : int(std::ceil(m));
+}
+
+// Concentrations with their series orders (fourier_order of each; the
+// order grows with kappa, so a bracket's upper end bounds it inside).
+struct FKappas {
+  double k[KDE_MAX_KAPPAS];
+  int order[KDE_MAX_KAPPAS];
+};
+inline FKappas fourier_list(const double* k, int B) {
+  FKappas f{};
+  for (int b = 0; b < B; ++b) {
+    f.k[b] = k[b];
+    f.order[b] = fourier_order(k[b]);
+  }
+  return f;
+}
+
+// Largest (rows x 2 M) partial array, in doubles, of n particles over the
+// orders up to Mmax: rows x M grows with M inside each form, so its largest
+// value lies at the end of a form's range.
+inline size_t moment_partials_max(int64_t n, int Mmax) {
+  size_t most = 0;
+  auto take = [&](int M) {
+    if (M > Mmax) M = Mmax;
+    const MomentPlan p = moment_plan(n, M);
+    const size_t v = size_t(p.rows) * 2 * size_t(M);
+    if (v > most) most = v;
+  };
+  take(kNarrowMax);
+  for (int t = 1; t <= 4; ++t) take(kWideStep * (8 * t - 1) + kWideB - 1);
+  for (int mb = 2; kWideModes * (mb - 1) < Mmax; ++mb) take(kWideModes * mb - kWideStep + kWideB - 1);
+  take(Mmax);
+  return most;
+}
+
+// Workspace of the scan of n particles to order M: partial rows, moments.
+struct ScanBufs {
+  double* partials;
+  double* S;
+  unsigned int* done;  // workgroups of the series that have written their value
+};
+inline ScanBufs carve_scan(Carver& c, int64_t n, int Mmax) {
+  ScanBufs b{};
+  b.partials = c.take<double>(moment_partials_max(n, Mmax));
+  b.S = c.take<double>(size_t(2) * size_t(Mmax));
+  b.done = c.take<unsigned int>(1);
+  return b;
+}
+
+// Moments of x into b.S (fourier.hip). The launches record t0 as their
+// start, `done` is zeroed.
+template <typename T>
+kde_status launch_moments(const T* x, int64_t n, double L, int M, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
+                          hipEvent_t t1, uint32_t* status);
+// The series of concentrations [0, B) of a list of Ball: cv[b], sums[b],
+// sums[Ball + b] (sums may be NULL), and the first minimum into *argmin when
+// it is not NULL.
+kde_status launch_series(const ScanBufs& b, int M, int64_t n, double L, const FKappas& kap, int B, int Ball,
+                         double* cv, double* sums, int32_t* argmin, hipStream_t s, hipEvent_t t1);
+
+}  // namespace kde

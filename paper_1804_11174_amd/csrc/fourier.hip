@@ -10,21 +10,19 @@
 // per concentration, instead of O(N^2) per concentration.
 //
 // Kernels:
-//   moments_kernel   -- block (particle chunk, 16 consecutive m): per
-//                       particle the phase exp(i m0 theta) with the product
-//                       m0 * (x/L) reduced mod 1 exactly (its rounding error
-//                       recovered by an FMA), then 15 rotations by
-//                       exp(i theta); per-m sums reduced in the workgroup in
-//                       a fixed order into the chunk's slot; the chunks are
-//                       summed by the shared fixed-order column sum.
+//   moments_kernel   -- workgroup (particle chunk, mode block): the chunk's
+//                       moments as a matrix product of phases on the FP64
+//                       matrix cores (dev_fourier.hpp), into the chunk's
+//                       partial rows, which moments_reduce_kernel sums in a
+//                       fixed order.
 //   series_kernel    -- one workgroup per concentration: the backward
 //                       recurrence of the ratios r_m = I_m/I_{m-1},
 //                       r_m = kappa / (2 m + kappa r_{m+1}) (stable downwards,
 //                       started where the neglected tail has decayed below
 //                       e^-40), as a scan of Mobius maps over the workgroup
-//                       (bessel_series), the ratios multiplied up to rho_m by
-//                       a prefix scan; then all threads form the series in a
-//                       fixed order.
+//                       (series_sums), the ratios multiplied up to rho_m by
+//                       a prefix scan, the sums of the series in a fixed
+//                       order; the last workgroup takes the first minimum.
 //   newton_start_kernel -- three workgroups side by side: the objective
 //                       and its derivatives at the two ends of the bracket
 //                       around the scan's first minimum and at the first
@@ -55,70 +53,21 @@
 #include <cmath>
 #include <limits>
 
-#include "dev_layout.hpp"
-#include "kde_internal.hpp"
+#include "dev_fourier.hpp"
 
 namespace kde {
 
 namespace {
 
-constexpr double kFourierTail = 1e-18;  // rho_M below this ends the series
-constexpr int kMomM = 16;               // consecutive m per moment block
-constexpr int kMomChunks = 64;          // moment partials' budget: kMomChunks x kMaxOrder (re, im) pairs
-constexpr int64_t kMomBlocks = 4096;    // workgroups a moment launch aims for
-constexpr int kMomPerThread = 8;        // fewest particles per thread of a moment workgroup
 constexpr int kPilotRun = 64;           // rotations between exact phase restarts
 constexpr int kMaxNewton = 100;
 constexpr int kStartEvals = 3;          // refine: bracket ends and first iterate, evaluated side by side
 
-// Concentrations with their series orders (fourier_order of each; the
-// order grows with kappa, so a bracket's upper end bounds it inside).
-struct FKappas {
-  double k[KDE_MAX_KAPPAS];
-  int order[KDE_MAX_KAPPAS];
-};
-
-// Smallest m at which the product of Amos's upper bounds
-//   I_nu(k) / I_{nu-1}(k) <= k / (nu - 1/2 + sqrt((nu - 1/2)^2 + k^2))
-// falls below kFourierTail: rho_m(kmax) is below it from there on, and
-// rho_m grows with kappa, so the series for every kappa <= kmax is cut there.
-int fourier_order(double kmax) {
-  if (!(kmax > 0.0)) return 1;
-  const double lim = std::log(kFourierTail);
-  double lg = 0.0;
-  for (int m = 1;; ++m) {
-    const double nu = double(m) - 0.5;
-    lg += std::log(kmax / (nu + std::sqrt(nu * nu + kmax * kmax)));
-    if (lg < lim) return m;
-  }
-}
-
 const int kMaxOrder = fourier_order(KDE_MAX_FOURIER_KAPPA);
 
-// Moment partials' budget for N particles, in units of kMaxOrder (re, im)
-// pairs: one per kBlock x kMomPerThread particles, at least 1, at most
-// kMomChunks.
-int64_t moment_budget(int64_t n) {
-  return std::max<int64_t>(1, std::min<int64_t>(kMomChunks, n / (int64_t(kBlock) * kMomPerThread)));
-}
-
-// Particle chunks of the moments of N particles to order M: about
-// kMomBlocks workgroups over the ceil(M / kMomM) mode groups (a low order
-// still fills the GPU), at least kMomPerThread particles per thread (so the
-// workgroup's fixed-order reduction of 2 kMomM sums stays a small part of
-// its work), and chunks x M within the partials' budget.
-int64_t moment_chunks(int64_t n, int M) {
-  int64_t c = ceil_div(kMomBlocks, ceil_div(M, kMomM));
-  c = std::min<int64_t>(c, n / (int64_t(kBlock) * kMomPerThread));
-  c = std::min<int64_t>(c, moment_budget(n) * kMaxOrder / M);
-  return std::max<int64_t>(1, c);
-}
-
 struct FourierBufs {
-  double* partials;  // [chunks][2 M]
-  double* colsum;    // column-sum scratch
-  double* S;         // [2 M] moments (re, im)
-  double* rho;       // [B][M + 1] (scan) or [3][M + 1] (refine, pilot)
+  ScanBufs scan;     // partial rows and moments [2 M] (re, im)
+  double* rho;       // [3 kStartEvals][M + 1] (refine) or [M + 1] (pilot)
   double* cvgrid;    // [B]
   double* start;     // refine: (cv, g, g') at the bracket ends and the first iterate, then that iterate's u
   double* w;         // [2 M] pilot weights
@@ -131,14 +80,8 @@ struct FourierBufs {
 FourierBufs carve_fourier(Carver& c, int op, int64_t n, int B) {
   FourierBufs b{};
   const int M = kMaxOrder;
-  // any order's chunks x 2 M partials fit the budget; its column-sum
-  // scratch, ceil(chunks / R) x 2 M for R rows per level-1 block, is at
-  // most (chunks x 2 M) / R + 2 M
-  const int64_t budget = moment_budget(n);
-  b.partials = c.take<double>(size_t(budget) * 2 * M);
-  b.colsum = c.take<double>((column_sum_scratch(budget * M, 2) + column_sum_scratch(1, 2 * M)) / sizeof(double) + 1);
-  b.S = c.take<double>(size_t(2) * M);
-  const int slots = (op == KDE_OP_CV_FOURIER) ? B : (op == KDE_OP_CV_REFINE ? std::max(B, 3 * kStartEvals) : 1);
+  b.scan = carve_scan(c, n, M);
+  const int slots = (op == KDE_OP_CV_FOURIER) ? 0 : (op == KDE_OP_CV_REFINE ? 3 * kStartEvals : 1);
   b.rho = c.take<double>(size_t(slots) * (M + 1));
   if (op == KDE_OP_CV_REFINE) {
     b.cvgrid = c.take<double>(size_t(B));
@@ -153,16 +96,6 @@ FourierBufs carve_fourier(Carver& c, int op, int64_t n, int B) {
     b.sums2 = c.take<double>(2);
   }
   return b;
-}
-
-// Phase exp(i 2 pi m f) for f in [0, 1]: m f reduced mod 1 with its
-// rounding error recovered, so the angle is exact to a few units of f's
-// last place times m.
-__device__ __forceinline__ void phase(int m, double f, double& c, double& s) {
-  const double t = double(m) * f;
-  const double e = fma(double(m), f, -t);
-  const double fr = (t - floor(t)) + e;
-  sincospi(2.0 * fr, &s, &c);
 }
 
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -199,52 +132,27 @@ __device__ __forceinline__ void block_sum6(double (&v)[6], double (*red)[6]) {
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kBlock) moments_kernel(const T* __restrict__ x, int64_t n, double L, int M,
-                                                        int64_t per_chunk, double* __restrict__ partials,
+__global__ void __launch_bounds__(kMomBlock) moments_kernel(const T* __restrict__ x, int64_t n, double L, MomentPlan p,
+                                                        double* __restrict__ partials, unsigned int* done,
                                                         uint32_t* status) {
-  __shared__ double red[kBlock / 64][2 * kMomM];
-  const int64_t ch = blockIdx.x;
-  const int m0 = 1 + int(blockIdx.y) * kMomM;
-  double re[kMomM], im[kMomM];
-#pragma unroll
-  for (int k = 0; k < kMomM; ++k) re[k] = im[k] = 0.0;
-  const int64_t lo = ch * per_chunk, hi = min(n, lo + per_chunk);
-  uint32_t* const st = blockIdx.y == 0 ? status : nullptr;  // one column of blocks notes the positions
-  for (int64_t j = lo + threadIdx.x; j < hi; j += kBlock) {
-    note_numeric(st, !isfinite(double(x[j])), false);
-    const double f = wrap_d(double(x[j]), L) / L;
-    double c, s, c1, s1;
-    phase(m0, f, c, s);
-    sincospi(2.0 * f, &s1, &c1);
-#pragma unroll
-    for (int k = 0; k < kMomM; ++k) {
-      re[k] += c;
-      im[k] += s;
-      const double nc = c * c1 - s * s1;
-      s = fma(s, c1, c * s1);
-      c = nc;
-    }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < kMomM; ++k) {
-    const double a = wave_sum(re[k]);
-    const double b = wave_sum(im[k]);
-    if (lane == 0) {
-      red[wave][2 * k] = a;
-      red[wave][2 * k + 1] = b;
-    }
-  }
+  __shared__ MomSmem sm;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *done = 0u;
+  unit_table_fill(sm.unit);
   __syncthreads();
-  const int t = threadIdx.x;
-  if (t < 2 * kMomM) {
-    const int m = m0 + (t >> 1);
-    if (m <= M) {
-      double v = 0.0;
-      for (int w = 0; w < kBlock / 64; ++w) v += red[w][t];
-      partials[ch * 2 * int64_t(M) + 2 * (m - 1) + (t & 1)] = v;
-    }
-  }
+  moments_unit<T>(x, n, L, p, blockIdx.x, blockIdx.y, partials, sm, status);
+}
+
+__global__ void __launch_bounds__(kBlock) moments_reduce_kernel(const double* __restrict__ partials, int64_t rows,
+                                                               int cols, double* __restrict__ S) {
+  __shared__ double red[kBlock];
+  moments_reduce(partials, rows, cols, blockIdx.x, S, red);
+}
+
+__device__ __forceinline__ int first_min(const double* v, int B) {
+  int best = 0;
+  for (int t = 1; t < B; ++t)
+    if (v[t] < v[best]) best = t;
+  return best;
 }
 
 // Shared memory of the workgroup-wide series (double-buffered scans).
@@ -446,47 +354,39 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
   __syncthreads();
 }
 
+// Workgroup b: concentration b. The last workgroup to finish takes the
+// first minimum (its place among the others changes nothing: the values are
+// fixed).
 __global__ void __launch_bounds__(kBlock) series_kernel(const double* __restrict__ S, int M, double n, double L,
-                                                       FKappas kap, int B, double* __restrict__ rho_all,
-                                                       double* __restrict__ cv, double* __restrict__ sums) {
-  __shared__ SeriesSmem sm;
-  double* red = sm.red;
-  const int b = blockIdx.x;
-  double* rho = rho_all + int64_t(b) * (M + 1);
-  const int Mb = min(M, kap.order[b]);
-  bessel_series<false>(kap.k[b], Mb, rho, nullptr, nullptr, sm);
-  double a = 0.0, a0 = 0.0, c = 0.0;
-  for (int m = 1 + threadIdx.x; m <= Mb; m += kBlock) {
-    const double sr = S[2 * (m - 1)], si = S[2 * (m - 1) + 1];
-    const double P = fma(sr, sr, si * si);
-    const double q = P - n;
-    const double r = rho[m];
-    const double r2 = r * r;
-    a = fma(r2, P, a);
-    a0 = fma(r2, q, a0);
-    c = fma(r, q, c);
-  }
-  a = block_sum(a, red);
-  a0 = block_sum(a0, red);
-  c = block_sum(c, red);
+                                                       FKappas kap, int Ball, double* __restrict__ cv,
+                                                       double* __restrict__ sums, int32_t* __restrict__ argmin,
+                                                       unsigned int* done) {
+  __shared__ ScanSmem sm;
+  __shared__ double v[KDE_MAX_KAPPAS];
+  __shared__ int last;
+  extern __shared__ __align__(16) double dyn_series[];
+  const int b = blockIdx.x, B = gridDim.x;
+  double A, A0, C;
+  series_sums(kap.k[b], min(M, kap.order[b]), S, n, dyn_series, sm, A, A0, C);
   if (threadIdx.x == 0) {
-    cv[b] = (2.0 * a / (n * n) - 4.0 * c / (n * (n - 1.0)) - 1.0) / L;
+    __hip_atomic_store(&cv[b], cv_of_series(A, C, n, L), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (sums) {
-      sums[b] = (n * n - n + 2.0 * a0) / (2.0 * L);
-      sums[B + b] = (n * n - n + 2.0 * c) / (2.0 * L);
+      sums[b] = pair_sum_of_series(A0, n, L);
+      sums[Ball + b] = pair_sum_of_series(C, n, L);
+    }
+    if (argmin) {
+      __threadfence();
+      last = atomicAdd(done, 1u) == unsigned(B - 1) ? 1 : 0;
     }
   }
-}
-
-__device__ __forceinline__ int first_min(const double* v, int B) {
-  int best = 0;
-  for (int t = 1; t < B; ++t)
-    if (v[t] < v[best]) best = t;
-  return best;
-}
-
-__global__ void argmin_kernel(const double* __restrict__ cv, int B, int32_t* __restrict__ argmin) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *argmin = first_min(cv, B);
+  if (!argmin) return;
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  if (threadIdx.x < B)
+    v[threadIdx.x] = __hip_atomic_load(&cv[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (threadIdx.x == 0) *argmin = first_min(v, B);
 }
 
 struct Eval {
@@ -739,24 +639,14 @@ __global__ void __launch_bounds__(kBlock) pilot_apply_kernel(const double* __res
   }
 }
 
-template <typename T>
-kde_status launch_moments(const T* x, int64_t n, double L, int M, const FourierBufs& b, hipStream_t s) {
-  const int64_t chunks = moment_chunks(n, M);
-  const int64_t per = ceil_div(n, chunks);
-  const dim3 grid{unsigned(chunks), unsigned(ceil_div(M, kMomM))};
-  {
-    TimedLaunch timed(KDE_KERNEL_MOMENTS, s);
-    hipExtLaunchKernelGGL((moments_kernel<T>), grid, dim3(kBlock), 0, s, timed.start(), timed.stop(), 0, x, n, L,
-                          M, per, b.partials, plain_numeric_word());
-  }
-  KDE_CHECK_LAUNCH();
-  return launch_column_sum(b.partials, chunks, 2 * M, b.colsum, b.S, s);
-}
-
 kde_status moments_any(const kde_domain* dom, int64_t n, const void* x, int M, const FourierBufs& b,
                        hipStream_t s) {
-  if (dom->prec == KDE_F64) return launch_moments(static_cast<const double*>(x), n, dom->L, M, b, s);
-  return launch_moments(static_cast<const float*>(x), n, dom->L, M, b, s);
+  TimedLaunch timed(KDE_KERNEL_MOMENTS, s);
+  if (dom->prec == KDE_F64)
+    return launch_moments(static_cast<const double*>(x), n, dom->L, M, b.scan, s, timed.start(), timed.stop(),
+                          plain_numeric_word());
+  return launch_moments(static_cast<const float*>(x), n, dom->L, M, b.scan, s, timed.start(), timed.stop(),
+                        plain_numeric_word());
 }
 
 kde_status check_fourier_common(const kde_domain* dom, int64_t N, const void* x, int64_t nmin) {
@@ -779,16 +669,32 @@ kde_status check_fourier_kappas(int B, const double* kappas_h) {
   return KDE_OK;
 }
 
-FKappas to_list(const double* k, int B) {
-  FKappas f{};
-  for (int b = 0; b < B; ++b) {
-    f.k[b] = k[b];
-    f.order[b] = fourier_order(k[b]);
-  }
-  return f;
-}
-
 }  // namespace
+
+template <typename T>
+kde_status launch_moments(const T* x, int64_t n, double L, int M, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
+                          hipEvent_t t1, uint32_t* status) {
+  const MomentPlan p = moment_plan(n, M);
+  hipExtLaunchKernelGGL((moments_kernel<T>), dim3(unsigned(p.chunks), unsigned(p.mblocks)), dim3(kMomBlock), 0, s, t0,
+                        nullptr, 0, x, n, L, p, b.partials, b.done, status);
+  KDE_CHECK_LAUNCH();
+  hipExtLaunchKernelGGL(moments_reduce_kernel, dim3(unsigned(ceil_div(2 * M, kRedCols))), dim3(kBlock), 0, s, nullptr,
+                        t1, 0, (const double*)b.partials, p.rows, 2 * M, b.S);
+  KDE_CHECK_LAUNCH();
+  return KDE_OK;
+}
+template kde_status launch_moments<double>(const double*, int64_t, double, int, const ScanBufs&, hipStream_t,
+                                           hipEvent_t, hipEvent_t, uint32_t*);
+template kde_status launch_moments<float>(const float*, int64_t, double, int, const ScanBufs&, hipStream_t,
+                                          hipEvent_t, hipEvent_t, uint32_t*);
+
+kde_status launch_series(const ScanBufs& b, int M, int64_t n, double L, const FKappas& kap, int B, int Ball,
+                         double* cv, double* sums, int32_t* argmin, hipStream_t s, hipEvent_t t1) {
+  hipExtLaunchKernelGGL(series_kernel, dim3(unsigned(B)), dim3(kBlock), series_lds(M), s, nullptr, t1, 0,
+                        (const double*)b.S, M, double(n), L, kap, Ball, cv, sums, argmin, b.done);
+  KDE_CHECK_LAUNCH();
+  return KDE_OK;
+}
 
 size_t fourier_workspace_bytes(int op, int64_t n, int B) {
   Carver c(nullptr, 0);
@@ -814,14 +720,7 @@ kde_status kde_cv_scan_fourier(const kde_domain* dom, int64_t N, const void* x, 
   const FourierBufs b = carve_fourier(c, KDE_OP_CV_FOURIER, N, B);
   const int M = fourier_order(kappas_h[B - 1]);
   KDE_RETURN_IF(moments_any(dom, N, x, M, b, s));
-  hipLaunchKernelGGL(series_kernel, dim3(B), dim3(kBlock), 0, s, (const double*)b.S, M, double(N), dom->L,
-                     to_list(kappas_h, B), B, b.rho, cv, sums);
-  KDE_CHECK_LAUNCH();
-  if (argmin) {
-    hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, s, (const double*)cv, B, argmin);
-    KDE_CHECK_LAUNCH();
-  }
-  return KDE_OK;
+  return launch_series(b.scan, M, N, dom->L, fourier_list(kappas_h, B), B, B, cv, sums, argmin, s, nullptr);
 }
 
 kde_status kde_cv_refine(const kde_domain* dom, int64_t N, const void* x, int32_t B, const double* kappas_h,
@@ -837,14 +736,12 @@ kde_status kde_cv_refine(const kde_domain* dom, int64_t N, const void* x, int32_
   const int M = fourier_order(kappas_h[B - 1]);
   KDE_RETURN_IF(moments_any(dom, N, x, M, b, s));
   double* grid = cv ? cv : b.cvgrid;
-  const FKappas kl = to_list(kappas_h, B);
-  hipLaunchKernelGGL(series_kernel, dim3(B), dim3(kBlock), 0, s, (const double*)b.S, M, double(N), dom->L, kl, B,
-                     b.rho, grid, (double*)nullptr);
-  KDE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(newton_start_kernel, dim3(kStartEvals), dim3(kBlock), 0, s, (const double*)b.S, M, double(N),
+  const FKappas kl = fourier_list(kappas_h, B);
+  KDE_RETURN_IF(launch_series(b.scan, M, N, dom->L, kl, B, B, grid, nullptr, nullptr, s, nullptr));
+  hipLaunchKernelGGL(newton_start_kernel, dim3(kStartEvals), dim3(kBlock), 0, s, (const double*)b.scan.S, M, double(N),
                      dom->L, kl, B, (const double*)grid, b.rho, b.start);
   KDE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(newton_kernel, dim3(1), dim3(kBlock), 0, s, (const double*)b.S, M, double(N), dom->L, kl, B,
+  hipLaunchKernelGGL(newton_kernel, dim3(1), dim3(kBlock), 0, s, (const double*)b.scan.S, M, double(N), dom->L, kl, B,
                      (const double*)grid, (const double*)b.start, b.rho, result, argmin);
   KDE_CHECK_LAUNCH();
   return KDE_OK;
@@ -865,7 +762,7 @@ kde_status kde_adapt_widths_exact(const kde_domain* dom, int64_t N, const void* 
   const FourierBufs b = carve_fourier(c, KDE_OP_ADAPT_EXACT, N, 0);
   const int M = fourier_order(kappa_star);
   KDE_RETURN_IF(moments_any(dom, N, x, M, b, s));
-  hipLaunchKernelGGL(pilot_weights_kernel, dim3(1), dim3(kBlock), 0, s, (const double*)b.S, M, kappa_star, b.rho, b.w);
+  hipLaunchKernelGGL(pilot_weights_kernel, dim3(1), dim3(kBlock), 0, s, (const double*)b.scan.S, M, kappa_star, b.rho, b.w);
   KDE_CHECK_LAUNCH();
   const int64_t blocks = ceil_div(N, kBlock);
   const dim3 grid{unsigned(blocks)};
