@@ -594,29 +594,46 @@ def main():
 
     pair_evals = B * n_cv * (n_cv - 1) / 2
     value = pair_evals / (ms_step * 1e-3)
-    ops, evaluated, pure_terms = pair_kernel_ops(prob.x[:n_cv], L, kappas, args.prec)
-    pair_ms = kern["cv_pairs"]["avg_ms"]
-    achieved = ops / (pair_ms * 1e-3)
-    peak = PEAK_LANE_OPS[args.prec]
+    pair_ms = kern["cv_pairs"]["avg_ms"]  # the sums of the scan, whichever way they are taken
     pe_rate = pair_evals / (pair_ms * 1e-3)
-    roofline = {"bound": "alu", "kernel": "cv_pairs_kernel", "achieved": achieved / 1e12,
-                "peak": peak / 1e12, "unit": "T lane-ops/s (FMA = 1)",
-                "frac": achieved / peak, "traffic": pair_kernel_traffic(args.prec),
-                "traffic_unit": "bytes per launch",
-                "basis": "algorithmic lane-operations of the method's formulas in FMA-issue slots (a float exp2 "
-                         "as 4, one add per accumulated sum) over the terms at or above e^-70 of their sum's "
-                         "scale, counted from the sorted positions: large-argument terms at ops_per_term, "
-                         "small-argument terms (2 kappa below the Bessel split) at their own formulas",
-                "evaluated_terms_per_launch": evaluated, "evaluated_fraction": evaluated / pair_evals,
-                "small_argument_terms_per_launch": pure_terms, "ops_per_launch": ops,
-                "ops_per_term": OPS_PER_TERM[args.prec], "ops_per_evaluated_term": ops / evaluated,
-                "kernel_avg_ms": pair_ms,
-                "pair_evals_per_s": pe_rate, "planning_ideal_pair_evals_per_s": PLANNING_IDEAL_PAIR_EVALS[args.prec],
-                "frac_of_planning_ideal": pe_rate / PLANNING_IDEAL_PAIR_EVALS[args.prec],
-                "issue": pair_kernel_issue(args.prec)}
+    peak = PEAK_LANE_OPS[args.prec]
+    if scan_through_moments(args.prec, n_cv, kappas):
+        order = fourier_order(float(kappas[-1]))
+        ops = n_cv * order * MOMENT_OPS
+        achieved = ops / (pair_ms * 1e-3)
+        roofline = {"bound": "alu", "kernel": "moments_kernel, moments_reduce_kernel, series_kernel",
+                    "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "T lane-ops/s (FMA = 1)",
+                    "frac": achieved / peak, "traffic": None,
+                    "basis": "two multiply-adds per particle and mode of the sample's moments, to the series order "
+                             "of the largest concentration; the time is that of the scan's three kernels and the "
+                             "gaps between them",
+                    "series_order": order, "ops_per_particle_mode": MOMENT_OPS, "ops_per_launch": ops,
+                    "kernel_avg_ms": pair_ms, "pair_evals_per_s": pe_rate}
+        value_kind = ("CV pair terms answered per second, B n (n - 1) / 2 over the step's time; the double scan "
+                      "takes them through the sample's Fourier moments, so no pairs are evaluated")
+    else:
+        ops, evaluated, pure_terms = pair_kernel_ops(prob.x[:n_cv], L, kappas, args.prec)
+        achieved = ops / (pair_ms * 1e-3)
+        roofline = {"bound": "alu", "kernel": "cv_pairs_kernel", "achieved": achieved / 1e12,
+                    "peak": peak / 1e12, "unit": "T lane-ops/s (FMA = 1)",
+                    "frac": achieved / peak, "traffic": pair_kernel_traffic(args.prec),
+                    "traffic_unit": "bytes per launch",
+                    "basis": "algorithmic lane-operations of the method's formulas in FMA-issue slots (a float exp2 "
+                             "as 4, one add per accumulated sum) over the terms at or above e^-70 of their sum's "
+                             "scale, counted from the sorted positions: large-argument terms at ops_per_term, "
+                             "small-argument terms (2 kappa below the Bessel split) at their own formulas",
+                    "evaluated_terms_per_launch": evaluated, "evaluated_fraction": evaluated / pair_evals,
+                    "small_argument_terms_per_launch": pure_terms, "ops_per_launch": ops,
+                    "ops_per_term": OPS_PER_TERM[args.prec], "ops_per_evaluated_term": ops / evaluated,
+                    "kernel_avg_ms": pair_ms,
+                    "pair_evals_per_s": pe_rate, "planning_ideal_pair_evals_per_s": PLANNING_IDEAL_PAIR_EVALS[args.prec],
+                    "frac_of_planning_ideal": pe_rate / PLANNING_IDEAL_PAIR_EVALS[args.prec],
+                    "issue": pair_kernel_issue(args.prec)}
+        value_kind = "CV pair terms per second, B n (n - 1) / 2 over the step's time"
     line = {
         "metric": METRIC,
         "value": value,
+        "value_kind": value_kind,
         "unit": "CV pair-evals/s",
         "n_gpus": 1,
         "steps": args.steps,
@@ -866,11 +883,16 @@ def bench_tri(args, kde, W, torch, dev):
             f.write(out + "\n")
 
 
-# Fourier moments, algorithmic lane-operations per (particle, m): the
-# rotation of exp(i m theta) by exp(i theta) (two products, two FMAs) and
-# the two accumulations. The exact phase at the start of each run of 16 m
-# (two sincos per particle) is not counted.
-MOMENT_OPS = 6
+# Fourier moments, algorithmic lane-operations per (particle, m): both modes s
+# a + b and s a - b come from four products of the phases of s a and b (a
+# matrix product over the particles), so two multiply-adds each.
+MOMENT_OPS = 2
+
+
+def scan_through_moments(prec, n, kappas):
+    """Whether the CV scan takes every concentration through the moments: in
+    double, up to min(1e6, (n / 3 pi)^2)."""
+    return prec == "f64" and float(kappas[-1]) <= min(1e6, (n / (3.0 * math.pi)) ** 2)
 
 
 def fourier_order(kmax):
@@ -891,8 +913,7 @@ def bench_fourier(args, kde, W, torch, dev):
     on the first 65,536 particles (scan of 32 kappas + Newton on log kappa,
     all on the device; the host reads kappa*), the exact pilot widths of all
     1,048,576 particles (kde_adapt_widths_exact), the adaptive deposit and
-    the gather. Also times the Fourier scan alone against the pair-kernel
-    scan of the same positions and concentrations."""
+    the gather. Also times the Fourier scan alone."""
     prob = W.plain_paper_scale()
     L, M, kappas, n, n_cv = prob.L, prob.M, prob.kappas, prob.x.shape[0], prob.n_cv
     B = len(kappas)

@@ -200,10 +200,15 @@ kde_status kde_workspace_size(int32_t op, const kde_domain* dom, int64_t N, int3
  *   ws, ws_bytes: device workspace of at least
  *              kde_workspace_size(KDE_OP_CV_SCAN, dom, N, B) bytes.
  *   stream   : hipStream_t or NULL.
- * Terms whose exponent lies below -70 (each smaller than e^-70 times the
- * largest term of its sum) may be left out: the kernel skips them where
- * that saves work and keeps them where it does not (the sums differ from
- * the full ones by at most that bound per term). For the triangle, pairs
+ * In double (von Mises) the concentrations up to min(1e6, (N / 3 pi)^2) are
+ * evaluated through the sample's Fourier moments (below), the same sums in
+ * O(N M) work; there the diagonal that separates the double sums from S1 and
+ * S2 is at most a few times S2 wherever the particles lie, so they keep their
+ * accuracy. Larger ones, and the float form, are summed over the pairs.
+ * Of the pair sums, terms whose exponent lies below -70 (each smaller than
+ * e^-70 times the largest term of its sum) may be left out: the kernel skips
+ * them where that saves work and keeps them where it does not (the sums
+ * differ from the full ones by at most that bound per term). For the triangle, pairs
  * outside the support of a width (d >= 2 h) contribute exactly 0 and are
  * skipped.
  */

@@ -23,7 +23,7 @@ extern "C" {
  * allocated. Enabling costs two event records per bracketed launch.
  */
 enum kde_kernel_id {
-  KDE_KERNEL_CV_PAIRS = 0,   /* the O(N^2) pair-sum kernel of kde_cv_scan   */
+  KDE_KERNEL_CV_PAIRS = 0,   /* the sums of kde_cv_scan: moments or pairs    */
   KDE_KERNEL_DEPOSIT = 1,    /* the per-chunk grid kernel of kde_deposit     */
   KDE_KERNEL_GATHER = 2,     /* the per-particle kernel of kde_gather        */
   KDE_KERNEL_ADAPT = 3,      /* both per-particle passes of kde_adapt_widths */

@@ -3,10 +3,15 @@
 // set's kappa*, adaptive widths, adaptive deposit) in one hipGraph launch.
 //
 // The graph holds one kernel per phase over the work units of every set
-// -- (set), (set, sort block), (set, pair slot, concentration group),
+// -- (set), (set, moment chunk, mode block), (set, moment columns), (set,
+// concentration), (set, sort block), (set, pair slot, concentration group),
 // (set, particle chunk) or (set, row block) -- with the sets ordered by
-// decreasing CV cost so that the long pair-sum work starts first. The pair
-// phase runs one workgroup per unit; the light phases run about as many
+// decreasing CV cost so that the long work starts first. In double a set's
+// leading concentrations go through its moments, the rest over its pairs
+// (scan_kappa_limit): sets whose whole list is in the first part have no
+// sort, pair and finalize units, and the kernels of phases without units
+// are left out of the graph. The moment, series, pair and deposit phases
+// run one workgroup per unit; the other light phases run about as many
 // workgroups as the device keeps resident, pulling units from the phase's
 // own device counter. Phases follow each other in the graph, so no
 // workgroup ever waits on another. Every unit runs the same device code as
@@ -25,6 +30,7 @@
 #include "batch_internal.hpp"
 #include "dev_cv.hpp"
 #include "dev_density.hpp"
+#include "dev_fourier.hpp"
 #include "dev_layout.hpp"
 #include "dev_reduce.hpp"
 
@@ -47,6 +53,11 @@ struct SetDev {
   const void* x;
   double L;
   int M, cells, chunk, sblocks;  // sblocks: blocks of the cell sort
+  int b0;                         // leading concentrations taken through the moments
+  MomentPlan mom;
+  double* mom_part;   // mom.rows x 2 mom.M
+  double* S;          // 2 mom.M
+  unsigned int* done; // series units that have finished (zeroed by the first kernel)
   int gsize, groups;              // pair units: concentrations per unit, units per slot
   int64_t schunk;                 // particles per sort block
   int64_t slots, g_cv, chunks, g_dep, blocks, g_ad;  // slots: rows of CV partial sums (cv_slots)
@@ -62,20 +73,24 @@ struct SetDev {
   double* ad_sums;    // 2
   void* kappa_i;      // N (prec)
   double* rho;        // M
-  double* cv;         // B or NULL
+  double* cv;         // B
   double* kstar;      // 1
   double* kstar_user; // 1 or NULL
   uint32_t* status;   // the set's numeric status word (KDE_NUMERIC_* bits)
 };
 
 // Unit prefix sums, one array of nsets + 1 per multi-unit phase.
-enum Prefix { PF_PAIRS, PF_CV_L1, PF_CHUNKS, PF_DEP_L1, PF_BLOCKS, PF_AD_L1, PF_SORT, PF_COUNT };
+enum Prefix {
+  PF_PAIRS, PF_CV_L1, PF_CHUNKS, PF_DEP_L1, PF_BLOCKS, PF_AD_L1, PF_SORT, PF_MOMENTS, PF_MOM_SUM, PF_SERIES, PF_FIN,
+  PF_COUNT
+};
 
 struct BatchArgs {
   const SetDev* sets;
   const int64_t* prefix;  // PF_COUNT x (nsets + 1)
   unsigned long long* counters;
   uint32_t* statuses;     // nsets numeric status words, in the caller's set order
+  unsigned int* done;     // nsets counters of finished series units
   int nsets;
   int B;
   double alpha;
@@ -117,9 +132,68 @@ __device__ __forceinline__ int64_t claim(unsigned long long* counter, int64_t* s
 }
 
 __global__ void __launch_bounds__(kBlock) batch_zero_kernel(unsigned long long* counters, uint32_t* statuses,
-                                                            int nsets) {
+                                                            unsigned int* done, int nsets) {
   if (threadIdx.x < kCounters) counters[threadIdx.x] = 0ull;
-  for (int k = threadIdx.x; k < nsets; k += kBlock) statuses[k] = 0u;
+  for (int k = threadIdx.x; k < nsets; k += kBlock) {
+    statuses[k] = 0u;
+    done[k] = 0u;
+  }
+}
+
+// The moments of every set, their row sums, and the series of the leading
+// concentrations; the last series unit of a set that has no pair sums
+// finds its first minimum.
+template <typename T>
+__global__ void __launch_bounds__(kMomBlock) batch_moments_kernel(BatchArgs a) {
+  __shared__ MomSmem sm;
+  const int64_t* pf = a.prefix + PF_MOMENTS * (a.nsets + 1);
+  const int64_t u = int64_t(blockIdx.x);
+  if (u >= pf[a.nsets]) return;
+  unit_table_fill(sm.unit);
+  const int si = uni32(find_set(pf, a.nsets, u));
+  const SetDev& s = a.sets[si];
+  const int64_t q = u - uni64(pf[si]);
+  MomentPlan p;
+  p.M = uni32(s.mom.M);
+  p.narrow = uni32(s.mom.narrow);
+  p.mblocks = uni32(s.mom.mblocks);
+  p.tiles = uni32(s.mom.tiles);
+  p.ks = uni32(s.mom.ks);
+  p.na = uni32(s.mom.na);
+  p.per = uni64(s.mom.per);
+  p.chunks = uni64(s.mom.chunks);
+  p.rows = uni64(s.mom.rows);
+  __syncthreads();
+  const int64_t chunk = q / p.mblocks;
+  moments_unit<T>(uni_ptr(static_cast<const T*>(s.x)), uni64(s.n_cv), s.L, p, chunk, int(q - chunk * p.mblocks),
+                  uni_ptr(s.mom_part), sm, uni_ptr(s.status));
+}
+
+__global__ void __launch_bounds__(kBlock) batch_moment_sum_kernel(BatchArgs a) {
+  __shared__ double red[kBlock];
+  const int64_t* pf = a.prefix + PF_MOM_SUM * (a.nsets + 1);
+  const int64_t u = int64_t(blockIdx.x);
+  if (u >= pf[a.nsets]) return;
+  const int si = uni32(find_set(pf, a.nsets, u));
+  const SetDev& s = a.sets[si];
+  moments_reduce(uni_ptr(s.mom_part), uni64(s.mom.rows), 2 * uni32(s.mom.M), u - uni64(pf[si]), uni_ptr(s.S), red);
+}
+
+__global__ void __launch_bounds__(kBlock) batch_series_kernel(BatchArgs a, FKappas kap) {
+  __shared__ SeriesSmem sm;
+  extern __shared__ __align__(16) double dyn_series[];
+  const int64_t* pf = a.prefix + PF_SERIES * (a.nsets + 1);
+  const int64_t u = int64_t(blockIdx.x);
+  if (u >= pf[a.nsets]) return;
+  const int si = uni32(find_set(pf, a.nsets, u));
+  const SetDev& s = a.sets[si];
+  const int b = int(u - uni64(pf[si])), b0 = uni32(s.b0);
+  const int best = series_unit(kap.k[b], min(uni32(s.mom.M), kap.order[b]), uni_ptr(s.S), double(s.n_cv), s.L, b, b0,
+                               a.B, uni_ptr(s.cv), nullptr, b0 == a.B ? uni_ptr(s.done) : nullptr, dyn_series, sm);
+  if (best >= 0 && threadIdx.x == 0) {
+    *s.kstar = kap.k[best];
+    if (s.kstar_user) *s.kstar_user = kap.k[best];
+  }
 }
 
 // The stable cell sort of every set's CV prefix in three phases, with the
@@ -146,10 +220,11 @@ __global__ void __launch_bounds__(kBlock) batch_sort_hist_kernel(BatchArgs a) {
 __global__ void __launch_bounds__(kBlock) batch_sort_scan_kernel(BatchArgs a) {
   __shared__ int64_t slot;
   __shared__ int tot[kBlock / 64];
+  const int64_t* pf = a.prefix + PF_FIN * (a.nsets + 1);  // the sets with pair sums
   for (;;) {
     const int64_t u = claim(&a.counters[PH_SORT_SCAN], &slot);
-    if (u >= a.nsets) break;
-    const SetDev& s = a.sets[u];
+    if (u >= pf[a.nsets]) break;
+    const SetDev& s = a.sets[find_set(pf, a.nsets, u)];
     block_scan_global(s.hist, int64_t(s.cells) * s.sblocks, tot);
   }
 }
@@ -191,9 +266,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Pai
     const int64_t q = u - uni64(pf[si]);
     const int groups = uni32(s.groups), gsize = uni32(s.gsize);
     const int64_t r = q / groups;
-    const int b_lo = int(q - r * groups) * gsize;
-    cv_slot<T, BC>(uni_ptr(static_cast<const P*>(s.packed)), uni64(s.n_cv), uni32(s.cells), s.L, r, uni64(s.slots),
-                   K, b_lo, min(K.B, b_lo + gsize), uni_ptr(s.partials) + r * 2 * K.B, sm);
+    cv_slot_group<T, BC>(uni_ptr(static_cast<const P*>(s.packed)), uni64(s.n_cv), uni32(s.cells), s.L, r,
+                         uni64(s.slots), K, uni32(s.b0), int(q - r * groups), gsize,
+                         uni_ptr(s.partials) + r * 2 * K.B, sm);
   }
 }
 
@@ -232,13 +307,14 @@ __global__ void __launch_bounds__(kBlock) batch_cv_finalize_kernel(BatchArgs a, 
   __shared__ double raw[2 * KDE_MAX_KAPPAS];
   __shared__ double v[KDE_MAX_KAPPAS];
   __shared__ int best;
+  const int64_t* pf = a.prefix + PF_FIN * (a.nsets + 1);  // the sets with pair sums
   for (;;) {
     const int64_t u = claim(&a.counters[PH_CV_FIN], &slot);
-    if (u >= a.nsets) break;
-    const SetDev& s = a.sets[u];
+    if (u >= pf[a.nsets]) break;
+    const SetDev& s = a.sets[find_set(pf, a.nsets, u)];
     for (int c = threadIdx.x; c < 2 * a.B; c += kBlock) raw[c] = colsum_level2(s.cv_l1, s.g_cv, 2 * a.B, c, 1.0);
     __syncthreads();
-    cv_finalize_block(raw, a.B, double(s.n_cv), s.L, kap, s.cv, nullptr, nullptr, v, &best);
+    cv_finalize_block(raw, a.B, s.b0, double(s.n_cv), s.L, kap, s.cv, nullptr, nullptr, v, &best);
     if (threadIdx.x == 0) {
       *s.kstar = kap.k[best];
       if (s.kstar_user) *s.kstar_user = kap.k[best];
@@ -327,11 +403,12 @@ __global__ void __launch_bounds__(kBlock) batch_adapt_apply_kernel(BatchArgs a) 
 // images of the descriptors and prefix arrays.
 static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* descs, std::vector<int64_t>* prefix,
                            unsigned long long** counters, SetDev** dev_sets, int64_t** dev_prefix,
-                           uint32_t** statuses_out = nullptr) {
+                           uint32_t** statuses_out = nullptr, unsigned int** done_out = nullptr) {
   Carver c(ws, ~size_t(0));
   const int ns = int(b.sets.size());
   unsigned long long* cnt = c.take<unsigned long long>(kCounters);
   uint32_t* statuses = c.take<uint32_t>(size_t(ns));
+  unsigned int* done = c.take<unsigned int>(size_t(ns));
   SetDev* ds = c.take<SetDev>(ns);
   int64_t* dp = c.take<int64_t>(size_t(PF_COUNT) * (ns + 1));
   if (descs) descs->assign(ns, SetDev{});
@@ -351,20 +428,32 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
     d.sblocks = sp.blocks;
     d.schunk = sp.chunk;
     d.chunk = deposit_chunk(in.N);
+    d.b0 = scan_fourier_count(b.prec, d.n_cv, b.kappas.data(), b.B);
+    const bool pairs = d.b0 < b.B;
+    if (d.b0 > 0) {
+      d.mom = moment_plan(d.n_cv, fourier_order(b.kappas[size_t(d.b0) - 1]));
+      d.mom_part = c.take<double>(size_t(d.mom.rows) * 2 * size_t(d.mom.M));
+      d.S = c.take<double>(2 * size_t(d.mom.M));
+    }
+    d.done = done + r;
     d.slots = cv_slots(d.n_cv);
-    const PairTuning tp = tuned_pass(b.prec, d.n_cv);
-    d.gsize = pair_group_size(tp, b.B);
-    d.groups = pair_groups(tp, b.B);
+    if (pairs) {
+      const PairTuning tp = tuned_pass(b.prec, d.n_cv);
+      d.gsize = pair_group_size(tp, b.B - d.b0);
+      d.groups = pair_groups(tp, b.B - d.b0);
+    }
     d.g_cv = ceil_div(d.slots, kSumRows);
     d.chunks = ceil_div(in.N, d.chunk);
     d.g_dep = ceil_div(d.chunks, kSumRows);
     d.blocks = ceil_div(in.N, kBlock);
     d.g_ad = ceil_div(d.blocks, kSumRows);
-    d.hist = c.take<int32_t>(size_t(d.cells) * size_t(d.sblocks));
-    d.packed = b.prec == KDE_F64 ? static_cast<void*>(c.take<double>(Packed<double>::per_particle * size_t(d.n_cv)))
-                                 : static_cast<void*>(c.take<uint32_t>(size_t(d.n_cv)));
-    d.partials = c.take<double>(size_t(d.slots) * 2 * b.B);
-    d.cv_l1 = c.take<double>(size_t(d.g_cv) * 2 * b.B);
+    if (pairs) {
+      d.hist = c.take<int32_t>(size_t(d.cells) * size_t(d.sblocks));
+      d.packed = b.prec == KDE_F64 ? static_cast<void*>(c.take<double>(Packed<double>::per_particle * size_t(d.n_cv)))
+                                   : static_cast<void*>(c.take<uint32_t>(size_t(d.n_cv)));
+      d.partials = c.take<double>(size_t(d.slots) * 2 * b.B);
+      d.cv_l1 = c.take<double>(size_t(d.g_cv) * 2 * b.B);
+    }
     d.dep_part = c.take<double>(size_t(d.chunks) * in.M);
     d.dep_l1 = c.take<double>(size_t(d.g_dep) * in.M);
     d.pilot = in.pilot ? in.pilot : c.take<double>(size_t(in.M));
@@ -373,12 +462,15 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
     d.ad_sums = c.take<double>(2);
     d.kappa_i = in.kappa_i ? in.kappa_i : static_cast<void*>(c.take<char>(size_t(in.N) * es));
     d.rho = in.rho;
-    d.cv = in.cv;
+    d.cv = in.cv ? in.cv : c.take<double>(size_t(b.B));
     d.kstar = c.take<double>(1);
     d.kstar_user = in.kappa_star;
     d.status = statuses + b.order[r];
     if (descs) (*descs)[r] = d;
-    const int64_t per[PF_COUNT] = {d.slots * d.groups, d.g_cv, d.chunks, d.g_dep, d.blocks, d.g_ad, int64_t(d.sblocks)};
+    const int64_t per[PF_COUNT] = {pairs ? d.slots * d.groups : 0, pairs ? d.g_cv : 0, d.chunks, d.g_dep, d.blocks,
+                                   d.g_ad, pairs ? int64_t(d.sblocks) : 0,
+                                   d.b0 > 0 ? d.mom.chunks * d.mom.mblocks : 0,
+                                   d.b0 > 0 ? ceil_div(2 * d.mom.M, kRedCols) : 0, int64_t(d.b0), pairs ? 1 : 0};
     for (int k = 0; k < PF_COUNT; ++k) {
       if (prefix) (*prefix)[size_t(k) * (ns + 1) + r] = acc[k];
       acc[k] += per[k];
@@ -388,6 +480,7 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
     if (prefix) (*prefix)[size_t(k) * (ns + 1) + ns] = acc[k];
   if (counters) *counters = cnt;
   if (statuses_out) *statuses_out = statuses;
+  if (done_out) *done_out = done;
   if (dev_sets) *dev_sets = ds;
   if (dev_prefix) *dev_prefix = dp;
   return c.used;
@@ -422,21 +515,16 @@ static unsigned launch_grid(const BatchPlan& b, K kernel, size_t dyn_lds, int64_
   return unsigned(g < 1 ? 1 : g);
 }
 
-template <typename T, int G>
-static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const std::vector<int64_t>& prefix, hipStream_t s) {
+// The pair sums of the sets that have any: sort, pairs, row sums, objective.
+template <typename T>
+static kde_status enqueue_pairs(const BatchPlan& b, const BatchArgs& a, const std::vector<int64_t>& prefix,
+                                const CvConsts<T>& K, const KappaList& kl, size_t pack_lds, hipStream_t s) {
   const int ns = int(b.sets.size());
   auto total = [&](int pf) { return prefix[size_t(pf) * (ns + 1) + ns]; };
-  const CvConsts<T> K = make_consts<T>(b.kappas.data(), b.B);
-  const KappaList kl = make_kappa_list<T>(b.kappas.data(), b.B);
-  const size_t dep_lds = 2 * size_t(b.max_M) * sizeof(T);
-  const size_t pack_lds = size_t(b.max_cells) * sizeof(int);
-
-  hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(kBlock), 0, s, a.counters, a.statuses, ns);
-  KDE_CHECK_LAUNCH();
   hipLaunchKernelGGL(batch_sort_hist_kernel<T>, dim3(launch_grid(b, batch_sort_hist_kernel<T>, pack_lds, total(PF_SORT))),
                      dim3(kBlock), pack_lds, s, a);
   KDE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(batch_sort_scan_kernel, dim3(launch_grid(b, batch_sort_scan_kernel, 0, ns)), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(batch_sort_scan_kernel, dim3(launch_grid(b, batch_sort_scan_kernel, 0, total(PF_FIN))), dim3(kBlock), 0, s, a);
   KDE_CHECK_LAUNCH();
   hipLaunchKernelGGL(batch_sort_scatter_kernel<T>,
                      dim3(launch_grid(b, batch_sort_scatter_kernel<T>, pack_lds, total(PF_SORT))), dim3(kBlock),
@@ -445,6 +533,7 @@ static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const st
   for (size_t k = 0; k < b.bucket_bc.size(); ++k) {
     const int64_t lo = prefix[size_t(PF_PAIRS) * (ns + 1) + b.bucket_begin[k]];
     const int64_t hi = prefix[size_t(PF_PAIRS) * (ns + 1) + b.bucket_begin[k + 1]];
+    if (hi == lo) continue;
     if (hi - lo > int64_t(0x7fffffff)) return fail(KDE_E_INVALID_ARG, "too many pair units for one launch");
     const dim3 grid{unsigned(hi - lo)};
     with_pass_size<T>(b.bucket_bc[k], [&](auto bc) {
@@ -456,9 +545,34 @@ static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const st
                      dim3(launch_grid(b, batch_level1_kernel<SRC_CV>, 0, total(PF_CV_L1))), dim3(kBlock), 0, s, a,
                      int(PH_CV_L1), int(PF_CV_L1));
   KDE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(batch_cv_finalize_kernel, dim3(launch_grid(b, batch_cv_finalize_kernel, 0, ns)), dim3(kBlock), 0,
+  hipLaunchKernelGGL(batch_cv_finalize_kernel, dim3(launch_grid(b, batch_cv_finalize_kernel, 0, total(PF_FIN))), dim3(kBlock), 0,
                      s, a, kl);
   KDE_CHECK_LAUNCH();
+  return KDE_OK;
+}
+
+template <typename T, int G>
+static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const std::vector<int64_t>& prefix, hipStream_t s) {
+  const int ns = int(b.sets.size());
+  auto total = [&](int pf) { return prefix[size_t(pf) * (ns + 1) + ns]; };
+  const CvConsts<T> K = make_consts<T>(b.kappas.data(), b.B);
+  const KappaList kl = make_kappa_list<T>(b.kappas.data(), b.B);
+  const size_t dep_lds = 2 * size_t(b.max_M) * sizeof(T);
+  const size_t pack_lds = size_t(b.max_cells) * sizeof(int);
+
+  hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(kBlock), 0, s, a.counters, a.statuses, a.done, ns);
+  KDE_CHECK_LAUNCH();
+  if (total(PF_MOMENTS) > 0) {
+    const FKappas fk = fourier_list(b.kappas.data(), b.max_b0);
+    hipLaunchKernelGGL(batch_moments_kernel<T>, dim3(unsigned(total(PF_MOMENTS))), dim3(kMomBlock), 0, s, a);
+    KDE_CHECK_LAUNCH();
+    hipLaunchKernelGGL(batch_moment_sum_kernel, dim3(unsigned(total(PF_MOM_SUM))), dim3(kBlock), 0, s, a);
+    KDE_CHECK_LAUNCH();
+    hipLaunchKernelGGL(batch_series_kernel, dim3(unsigned(total(PF_SERIES))), dim3(kBlock),
+                       series_lds(fk.order[b.max_b0 - 1]), s, a, fk);
+    KDE_CHECK_LAUNCH();
+  }
+  if (total(PF_FIN) > 0) KDE_RETURN_IF(enqueue_pairs<T>(b, a, prefix, K, kl, pack_lds, s));
   for (int pass = 0; pass < 2; ++pass) {
     const bool adaptive = pass == 1;
     if (adaptive) {
@@ -518,8 +632,9 @@ static void batch_images(const BatchPlan& b, void* ws, std::vector<SetDev>& desc
   SetDev* dsets = nullptr;
   int64_t* dpref = nullptr;
   uint32_t* statuses = nullptr;
-  layout_batch(b, ws, &descs, &prefix, &counters, &dsets, &dpref, &statuses);
-  a = BatchArgs{dsets, dpref, counters, statuses, int(b.sets.size()), b.B, b.alpha};
+  unsigned int* done = nullptr;
+  layout_batch(b, ws, &descs, &prefix, &counters, &dsets, &dpref, &statuses, &done);
+  a = BatchArgs{dsets, dpref, counters, statuses, done, int(b.sets.size()), b.B, b.alpha};
 }
 
 kde_status batch_plan_make(const kde_batch_set* sets_h, int nsets, int prec, int B, const double* kappas_h,
@@ -545,6 +660,7 @@ kde_status batch_plan_make(const kde_batch_set* sets_h, int nsets, int prec, int
     im.max_M = std::max(im.max_M, int(in.M));
     im.max_n = std::max(im.max_n, in.N);
     im.max_cells = std::max(im.max_cells, make_sort_plan(in.n_cv ? in.n_cv : in.N).cells);
+    im.max_b0 = std::max(im.max_b0, scan_fourier_count(prec, in.n_cv ? in.n_cv : in.N, kappas_h, B));
   }
   im.prec = prec;
   im.B = B;

@@ -17,6 +17,7 @@ struct BatchPlan {
   std::vector<int> order;           // cost order (largest CV first) -> caller index
   int max_M = 0, max_cells = 1;
   int64_t max_n = 0;
+  int max_b0 = 0;  // most leading concentrations any set takes through its moments
   // pass-size buckets over the cost order: sets [bucket_begin[k], bucket_begin[k+1]) use bucket_bc[k]
   std::vector<int> bucket_begin, bucket_bc;
   size_t ws_need = 0;

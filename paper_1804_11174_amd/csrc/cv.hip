@@ -34,6 +34,10 @@
 // exponent scales with kappa, so once every lane of a wave is below the
 // bound for one concentration, the wave skips the rest for that j.
 //
+// In double the concentrations up to scan_kappa_limit (every one of ordinary
+// lists) do not go over the pairs: their sums come from the sample's Fourier
+// moments (dev_fourier.hpp), and the pair kernel takes the rest of the list.
+//
 // The first-order (triangular) shape of adjustable width (dev_tri.hpp)
 // takes the same path: sort, tile pairs, fixed-order sums, finalize, with
 // its own pair function and normalisation; the candidates are half-widths.
@@ -42,6 +46,7 @@
 #include <vector>
 
 #include "dev_cv.hpp"
+#include "dev_fourier.hpp"
 #include "dev_tri.hpp"
 
 namespace kde {
@@ -87,26 +92,27 @@ __global__ void __launch_bounds__(KDE_MAX_KAPPAS) tri_finalize_kernel(const doub
   }
 }
 
-// Block (slot r, concentration group g) with r = blockIdx.x / groups.
+// Block (slot r, concentration group g) with r = blockIdx.x / groups, for the
+// concentrations [b0, B).
 template <typename T, int BC>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PairWaves<T, BC>::value))) cv_pairs_kernel(const typename Packed<T>::type* __restrict__ packed,
-                                                         int64_t n, int cells, double L, int64_t nslots, int groups,
-                                                         int gsize, CvConsts<T> K, double* __restrict__ partials) {
+                                                         int64_t n, int cells, double L, int64_t nslots, int b0,
+                                                         int groups, int gsize, CvConsts<T> K,
+                                                         double* __restrict__ partials) {
   __shared__ CvSmem<T, BC> sm;
   const int64_t r = int64_t(blockIdx.x) / groups;
   const int g = int(int64_t(blockIdx.x) - r * groups);
-  const int b_lo = g * gsize;
-  cv_slot<T, BC>(packed, n, cells, L, r, nslots, K, b_lo, min(K.B, b_lo + gsize), partials + r * 2 * K.B, sm);
+  cv_slot_group<T, BC>(packed, n, cells, L, r, nslots, K, b0, g, gsize, partials + r * 2 * K.B, sm);
 }
 
-// raw[0..B): Kbar sums, raw[B..2B): K sums (unnormalised); one block.
+// raw[0..B): Kbar sums, raw[B..2B): K sums (unnormalised) of the
+// concentrations from b0 on; cv holds the values of those before; one block.
 __global__ void __launch_bounds__(KDE_MAX_KAPPAS) cv_finalize_kernel(const double* __restrict__ raw, int B,
-                                                                    double n, double L, KappaList kap,
-                                                                    double* __restrict__ cv,
-                                                                    double* __restrict__ sums,
+                                                                    int b0, double n, double L, KappaList kap,
+                                                                    double* cv, double* __restrict__ sums,
                                                                     int32_t* __restrict__ argmin) {
   __shared__ double v[KDE_MAX_KAPPAS];
-  cv_finalize_block(raw, B, n, L, kap, cv, sums, argmin, v, nullptr);
+  cv_finalize_block(raw, B, b0, n, L, kap, cv, sums, argmin, v, nullptr);
 }
 
 // ------------------------------------------------------------------ host
@@ -183,40 +189,60 @@ static CvBuffers carve_cv(Carver& cv, const CvPlan& p, int64_t n, int B, int pre
   return b;
 }
 
+// Series order the moments of a scan of n particles are sized for.
+static int scan_order(int64_t n) { return fourier_order(scan_kappa_limit(n)); }
+
+// The two parts of a scan follow each other on the stream and share the
+// workspace: the larger of their needs.
 size_t cv_workspace_bytes(int64_t n, int B, int prec) {
   CvPlan p = make_cv_plan(n);
-  Carver c(nullptr, 0);
-  carve_cv(c, p, n, B, prec);
-  return c.used;
+  Carver pairs(nullptr, 0), moments(nullptr, 0);
+  carve_cv(pairs, p, n, B, prec);
+  if (prec == KDE_F64) carve_scan(moments, n, scan_order(n));
+  return pairs.used > moments.used ? pairs.used : moments.used;
 }
 
+// The leading concentrations through the moments (double form,
+// scan_kappa_limit), the rest over pairs; the objective and the first minimum are those of the
+// whole list.
 template <typename T>
 static kde_status run_cv(const kde_domain* dom, int64_t n, const T* x, int B, const double* kappas,
                          double* cv, double* sums, int32_t* argmin, void* ws, size_t ws_bytes,
                          hipStream_t s, uint32_t* status) {
+  if (ws_bytes < cv_workspace_bytes(n, B, dom->prec))
+    return fail(KDE_E_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, cv_workspace_bytes(n, B, dom->prec));
+  const int b0 = scan_fourier_count(dom->prec, n, kappas, B);
+  TimedLaunch timed(KDE_KERNEL_CV_PAIRS, s);  // the sums of every concentration
+  if (b0 > 0) {
+    Carver c(ws, ws_bytes);
+    const ScanBufs buf = carve_scan(c, n, scan_order(n));
+    const int M = fourier_order(kappas[b0 - 1]);
+    KDE_RETURN_IF(launch_moments(x, n, dom->L, M, buf, s, timed.start(), nullptr, status));
+    KDE_RETURN_IF(launch_series(buf, M, n, dom->L, fourier_list(kappas, b0), b0, B, cv, sums,
+                                b0 == B ? argmin : nullptr, s, b0 == B ? timed.stop() : nullptr));
+    if (b0 == B) return KDE_OK;
+  }
   CvPlan p = make_cv_plan(n);
   Carver c(ws, ws_bytes);
   CvBuffers buf = carve_cv(c, p, n, B, dom->prec);
-  if (!c.fits()) return fail(KDE_E_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, c.used);
   using P = typename Packed<T>::type;
   P* packed = static_cast<P*>(buf.packed);
   KDE_RETURN_IF(launch_pack_sorted<T>(x, n, dom->L, p.sort, buf.hist, packed, nullptr, s, status));
   CvConsts<T> K = make_consts<T>(kappas, B);
   const PairTuning tp = tuned_pass(dom->prec, n);
-  const int groups = pair_groups(tp, B), gsize = pair_group_size(tp, B);
+  const int groups = pair_groups(tp, B - b0), gsize = pair_group_size(tp, B - b0);
   {
-    TimedLaunch timed(KDE_KERNEL_CV_PAIRS, s);
     const dim3 grid{unsigned(p.slots * groups)}, block{unsigned(kBlock)};
     with_pass_size<T>(tp.chunk, [&](auto bc) {
-      hipExtLaunchKernelGGL((cv_pairs_kernel<T, decltype(bc)::value>), grid, block, 0, s, timed.start(),
-                            timed.stop(), 0, (const P*)packed, n, p.sort.cells, dom->L, p.slots, groups, gsize, K,
-                            buf.partials);
+      hipExtLaunchKernelGGL((cv_pairs_kernel<T, decltype(bc)::value>), grid, block, 0, s,
+                            b0 == 0 ? timed.start() : nullptr, timed.stop(), 0, (const P*)packed, n, p.sort.cells,
+                            dom->L, p.slots, b0, groups, gsize, K, buf.partials);
     });
   }
   KDE_CHECK_LAUNCH();
   KDE_RETURN_IF(launch_column_sum(buf.partials, p.slots, 2 * B, buf.colsum, buf.raw, s));
   const KappaList kl = make_kappa_list<T>(kappas, B);
-  hipLaunchKernelGGL(cv_finalize_kernel, dim3(1), dim3(KDE_MAX_KAPPAS), 0, s, (const double*)buf.raw, B,
+  hipLaunchKernelGGL(cv_finalize_kernel, dim3(1), dim3(KDE_MAX_KAPPAS), 0, s, (const double*)buf.raw, B, b0,
                      double(n), dom->L, kl, cv, sums, argmin);
   KDE_CHECK_LAUNCH();
   return KDE_OK;

@@ -813,6 +813,21 @@ __device__ __forceinline__ void cv_slot(const typename Packed<T>::type* __restri
   __syncthreads();
 }
 
+// Group g of gsize concentrations of a slot, of the concentrations [b0, B):
+// their entries of the slot's row; the first group writes zeros for those
+// before b0 (which the moments take), so that the row sums are defined.
+template <typename T, int BC>
+__device__ __forceinline__ void cv_slot_group(const typename Packed<T>::type* __restrict__ packed, int64_t n,
+                                              int cells, double L, int64_t slot, int64_t nslots,
+                                              const CvConsts<T>& K, int b0, int g, int gsize,
+                                              double* __restrict__ out, CvSmem<T, BC>& sm) {
+  if (g == 0) {
+    for (int k = threadIdx.x; k < b0; k += kBlock) out[k] = out[K.B + k] = 0.0;
+  }
+  const int b_lo = b0 + g * gsize;
+  cv_slot<T, BC>(packed, n, cells, L, slot, nslots, K, b_lo, min(K.B, b_lo + gsize), out, sm);
+}
+
 // Whether a term of concentration k may take the small-argument Bessel
 // branch (2 kappa |c| < X0) without being negligible: such a term carries
 // weight exp(-2 kappa (1 - |c|)) <= exp(-(2 kappa - X0)), below the skip
@@ -878,15 +893,18 @@ inline KappaList make_kappa_list(const double* kappas, int B) {
 
 // The objective from the unordered pair sums of one set, by one workgroup
 // (thread b handles concentration b): raw[0..B) = sum_{i<j} exp(-2k(1-c))
-// I0e(2kc), raw[B..2B) = sum_{i<j} exp(-2k s^2). Normalisers in double;
-// writes cv[B], optional sums[2B] (normalised), and returns nothing; the
-// first-minimum index is written by thread 0 into *argmin (if not NULL)
-// and into `v` (LDS, B doubles) the objective values.
-__device__ __forceinline__ void cv_finalize_block(const double* __restrict__ raw, int B, double n, double L,
-                                                  const KappaList& kap, double* __restrict__ cv,
+// I0e(2kc), raw[B..2B) = sum_{i<j} exp(-2k s^2), for the concentrations [b0,
+// B); cv[0..b0) holds the values of the others (cv may be NULL when b0 = 0).
+// Normalisers in double; writes cv, optional sums[2B] (normalised), and
+// returns nothing; the first-minimum index of the whole list is written by
+// thread 0 into *argmin (if not NULL) and into `v` (LDS, B doubles) the
+// objective values.
+__device__ __forceinline__ void cv_finalize_block(const double* __restrict__ raw, int B, int b0, double n, double L,
+                                                  const KappaList& kap, double* cv,
                                                   double* __restrict__ sums, int32_t* __restrict__ argmin,
                                                   double* v, int* best_out) {
-  for (int b = threadIdx.x; b < B; b += blockDim.x) {
+  for (int b = threadIdx.x; b < b0; b += blockDim.x) v[b] = cv[b];
+  for (int b = b0 + threadIdx.x; b < B; b += blockDim.x) {
     const double k = kap.k[b];
     const double ik = i0e_f64(k);
     const double i2k = i0e_f64(2.0 * k);

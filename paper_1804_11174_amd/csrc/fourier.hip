@@ -148,15 +148,8 @@ __global__ void __launch_bounds__(kBlock) moments_reduce_kernel(const double* __
   moments_reduce(partials, rows, cols, blockIdx.x, S, red);
 }
 
-__device__ __forceinline__ int first_min(const double* v, int B) {
-  int best = 0;
-  for (int t = 1; t < B; ++t)
-    if (v[t] < v[best]) best = t;
-  return best;
-}
-
 // Shared memory of the workgroup-wide series (double-buffered scans).
-struct SeriesSmem {
+struct BesselSmem {
   double mat[2][kBlock][4];  // Mobius matrices (row-major 2x2)
   double aff[2][kBlock][2];  // affine maps x -> a + b x
   double pre[2][kBlock][3];  // segment totals (product, sum, sum)
@@ -193,7 +186,7 @@ __device__ __forceinline__ void mat_mul_norm(const double* a, const double* b, d
 // length of the chain.
 template <bool DER>
 __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, double* __restrict__ d1,
-                              double* __restrict__ d2, SeriesSmem& sm) {
+                              double* __restrict__ d2, BesselSmem& sm) {
   const int t = threadIdx.x;
   const int Ms = int(ceil(sqrt(double(M) * double(M) + 40.0 * kappa))) + 16;
   const int len = (Ms + kBlock - 1) / kBlock;
@@ -354,39 +347,16 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
   __syncthreads();
 }
 
-// Workgroup b: concentration b. The last workgroup to finish takes the
-// first minimum (its place among the others changes nothing: the values are
-// fixed).
+// Workgroup b: concentration b; the last to finish writes the first minimum.
 __global__ void __launch_bounds__(kBlock) series_kernel(const double* __restrict__ S, int M, double n, double L,
-                                                       FKappas kap, int Ball, double* __restrict__ cv,
-                                                       double* __restrict__ sums, int32_t* __restrict__ argmin,
-                                                       unsigned int* done) {
-  __shared__ ScanSmem sm;
-  __shared__ double v[KDE_MAX_KAPPAS];
-  __shared__ int last;
+                                                       FKappas kap, int Ball, double* cv, double* __restrict__ sums,
+                                                       int32_t* __restrict__ argmin, unsigned int* done) {
+  __shared__ SeriesSmem sm;
   extern __shared__ __align__(16) double dyn_series[];
-  const int b = blockIdx.x, B = gridDim.x;
-  double A, A0, C;
-  series_sums(kap.k[b], min(M, kap.order[b]), S, n, dyn_series, sm, A, A0, C);
-  if (threadIdx.x == 0) {
-    __hip_atomic_store(&cv[b], cv_of_series(A, C, n, L), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (sums) {
-      sums[b] = pair_sum_of_series(A0, n, L);
-      sums[Ball + b] = pair_sum_of_series(C, n, L);
-    }
-    if (argmin) {
-      __threadfence();
-      last = atomicAdd(done, 1u) == unsigned(B - 1) ? 1 : 0;
-    }
-  }
-  if (!argmin) return;
-  __syncthreads();
-  if (!last) return;
-  __threadfence();
-  if (threadIdx.x < B)
-    v[threadIdx.x] = __hip_atomic_load(&cv[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  if (threadIdx.x == 0) *argmin = first_min(v, B);
+  const int b = blockIdx.x;
+  const int best = series_unit(kap.k[b], min(M, kap.order[b]), S, n, L, b, gridDim.x, Ball, cv, sums,
+                               argmin ? done : nullptr, dyn_series, sm);
+  if (best >= 0 && threadIdx.x == 0) *argmin = best;
 }
 
 struct Eval {
@@ -396,7 +366,7 @@ struct Eval {
 // Objective and its first two derivatives in u = log(kappa), all threads,
 // with the series cut at order Mk (that of a kappa at least as large).
 __device__ Eval eval_u(double u, const double* __restrict__ S, int Mk, double n, double L, double* rho, double* d1,
-                       double* d2, SeriesSmem& sm) {
+                       double* d2, BesselSmem& sm) {
   const double kappa = exp(u);
   bessel_series<true>(kappa, Mk, rho, d1, d2, sm);
   double A = 0.0, C = 0.0, A1 = 0.0, C1 = 0.0, A2 = 0.0, C2 = 0.0;
@@ -491,7 +461,7 @@ __global__ void __launch_bounds__(kBlock) newton_start_kernel(const double* __re
                                                              double L, FKappas kap, int B,
                                                              const double* __restrict__ cvgrid,
                                                              double* __restrict__ rho, double* __restrict__ start) {
-  __shared__ SeriesSmem sm;
+  __shared__ BesselSmem sm;
   const Bracket br = make_bracket(cvgrid, B, kap, M);
   if (!br.valid) return;
   const int w = blockIdx.x;
@@ -513,7 +483,7 @@ __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict
                                                        FKappas kap, int B, const double* __restrict__ cvgrid,
                                                        const double* __restrict__ start, double* __restrict__ rho3,
                                                        double* __restrict__ result, int32_t* __restrict__ argmin) {
-  __shared__ SeriesSmem sm;
+  __shared__ BesselSmem sm;
   double* rho = rho3;
   double* d1 = rho3 + (M + 1);
   double* d2 = rho3 + 2 * (M + 1);
@@ -571,7 +541,7 @@ __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict
 // w_m = rho_m(kappa) S_m, m = 1..M (one workgroup).
 __global__ void __launch_bounds__(kBlock) pilot_weights_kernel(const double* __restrict__ S, int M, double kappa,
                                                               double* __restrict__ rho, double* __restrict__ w) {
-  __shared__ SeriesSmem sm;
+  __shared__ BesselSmem sm;
   bessel_series<false>(kappa, M, rho, nullptr, nullptr, sm);
   for (int m = 1 + threadIdx.x; m <= M; m += kBlock) {
     w[2 * (m - 1)] = rho[m] * S[2 * (m - 1)];

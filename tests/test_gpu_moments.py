@@ -23,7 +23,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n", [2, 63, 65, 128, 129, 511, 513, 1100])
 @pytest.mark.parametrize("top", [0.3, 130.0, 160.0, 600.0, 700.0, 2600.0, 2900.0, 6200.0, 6700.0, 11000.0, 12000.0,
-                                 5e4])
+                                 5e4, 1e6])
 def test_orders_and_counts_at_the_kernel_edges(gpu, n, top):
     L = 4 * math.pi
     x = W.cosine_positions(np.random.default_rng([41, n]), n, L, 0.4, 0.5)
