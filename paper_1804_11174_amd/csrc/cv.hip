@@ -38,9 +38,10 @@
 // lists) do not go over the pairs: their sums come from the sample's Fourier
 // moments (dev_fourier.hpp), and the pair kernel takes the rest of the list.
 //
-// The first-order (triangular) shape of adjustable width (dev_tri.hpp)
-// takes the same path: sort, tile pairs, fixed-order sums, finalize, with
+// The first-order (triangular) shape of adjustable width (dev_tri.hpp; in
+// double tri_cells.hip) takes in float the same path: sort, tile pairs, fixed-order sums, finalize, with
 // its own pair function and normalisation; the candidates are half-widths.
+#include <algorithm>
 #include <climits>
 #include <mutex>
 #include <vector>
@@ -193,13 +194,18 @@ static CvBuffers carve_cv(Carver& cv, const CvPlan& p, int64_t n, int B, int pre
 static int scan_order(int64_t n) { return fourier_order(scan_kappa_limit(n)); }
 
 // The two parts of a scan follow each other on the stream and share the
-// workspace: the larger of their needs.
+// workspace, and the triangle's scan takes the same size: the largest of
+// their needs.
 size_t cv_workspace_bytes(int64_t n, int B, int prec) {
   CvPlan p = make_cv_plan(n);
   Carver pairs(nullptr, 0), moments(nullptr, 0);
   carve_cv(pairs, p, n, B, prec);
-  if (prec == KDE_F64) carve_scan(moments, n, scan_order(n));
-  return pairs.used > moments.used ? pairs.used : moments.used;
+  size_t need = pairs.used;
+  if (prec == KDE_F64) {
+    carve_scan(moments, n, scan_order(n));
+    need = std::max(need, std::max(moments.used, tri_scan_workspace_bytes(n, B)));
+  }
+  return need;
 }
 
 // The leading concentrations through the moments (double form,
@@ -248,11 +254,9 @@ static kde_status run_cv(const kde_domain* dom, int64_t n, const T* x, int B, co
   return KDE_OK;
 }
 
-// Passes of the triangle pair kernel: widths per pass, 4 in both
-// precisions. In float the three registers of each compensated sum make a
-// pass of 8 spill at eight waves, and at five or six it runs slower (5.0
-// against 4.4 ms at the paper-scale scan); in double 4 runs 4 % faster
-// than 8 (6.93 against 7.19 ms).
+// Passes of the triangle pair kernel: 4 widths per pass. The three registers
+// of each compensated sum make a pass of 8 spill at eight waves, and at five
+// or six it runs slower (5.0 against 4.4 ms at the paper-scale scan).
 template <typename T>
 constexpr int kTriPass = 4;
 
@@ -288,8 +292,7 @@ kde_status cv_scan(const kde_domain* dom, int64_t n, const void* x, int B, const
                    double* sums, int32_t* argmin, void* ws, size_t ws_bytes, hipStream_t s, uint32_t* status) {
   if (dom->shape == KDE_SHAPE_TRIANGLE) {
     if (dom->prec == KDE_F64)
-      return run_cv_tri<double>(dom, n, static_cast<const double*>(x), B, kappas, cv, sums, argmin, ws, ws_bytes, s,
-                                status);
+      return tri_scan_f64(dom, n, static_cast<const double*>(x), B, kappas, cv, sums, argmin, ws, ws_bytes, s, status);
     return run_cv_tri<float>(dom, n, static_cast<const float*>(x), B, kappas, cv, sums, argmin, ws, ws_bytes, s,
                              status);
   }

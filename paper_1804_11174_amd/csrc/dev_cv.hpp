@@ -136,12 +136,9 @@ struct I0eBounds<float> {
 
 // Position of packed particle i as a fraction of the period, from its
 // packed form: the wrapped position w (third component of the double
-// form) times 1/L, the double position fraction, or the 32-bit phase.
+// form) times 1/L, or the 32-bit phase.
 __device__ __forceinline__ double packed_frac(const double* __restrict__ packed, int64_t i, double inv_L) {
   return packed[3 * i + 2] * inv_L;
-}
-__device__ __forceinline__ double packed_frac(const FracPos* __restrict__ packed, int64_t i, double) {
-  return packed[i].f;
 }
 __device__ __forceinline__ double packed_frac(const uint32_t* __restrict__ packed, int64_t i, double) {
   return double(packed[i]) * (1.0 / 4294967296.0);

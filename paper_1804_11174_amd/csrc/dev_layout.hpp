@@ -42,10 +42,6 @@ __device__ __forceinline__ void store_packed(double* packed, int64_t dest, doubl
   packed[3 * dest + 2] = w;
 }
 
-__device__ __forceinline__ void store_packed(FracPos* packed, int64_t dest, double w, double L) {
-  packed[dest].f = w / L;
-}
-
 __device__ __forceinline__ void store_packed(uint32_t* packed, int64_t dest, double w, double L) {
   // w / L in [0, 1): the nearest multiple of 2^-32, wrapped
   const double v = floor((w / L) * 4294967296.0 + 0.5);

@@ -16,10 +16,10 @@
 // within a pair of tiles, a wave stops at the first width (widest first)
 // for which every pair of the wave lies outside the support.
 //
-// Pair distances are periodic and in fractions of the period: from the
-// wrapped position / L in double, or from the 32-bit fixed-point phase in
-// float (the phase difference in wrapping integer arithmetic is the exact
-// periodic separation). With a = max(0, 1 - u/2) and c = max(0, 1 - u),
+// The pair kernel below is the float form's (the double form's scan is
+// tri_cells.hip). Pair distances are periodic and in fractions of the period,
+// from the 32-bit fixed-point phase (the phase difference in wrapping integer
+// arithmetic is the exact periodic separation). With a = max(0, 1 - u/2) and c = max(0, 1 - u),
 // 6 B(u) = 8 (a^3 - c^3 / 2): each of a and c is one multiply-add of the
 // distance clamped to [0, 1]. The image term needs only its a (its u is at
 // least L / (2 h) >= 1), the same multiply-add of the image distance
@@ -68,10 +68,6 @@ inline TriConsts<T> make_tri_consts(const double* widths, int B, double L) {
 }
 
 // Periodic distance of two packed particles in the packed unit.
-__device__ __forceinline__ double tri_dist(FracPos a, FracPos b) {
-  const double r = fabs(a.f - b.f);
-  return fmin(r, 1.0 - r);
-}
 __device__ __forceinline__ float tri_dist(uint32_t a, uint32_t b) {
   const int32_t dd = int32_t(a - b);
   const uint32_t m = dd < 0 ? uint32_t(-int64_t(dd)) : uint32_t(dd);
@@ -109,29 +105,18 @@ __device__ __forceinline__ void tri_add(T r, T rp, T a, T kc, T ka, bool live, A
   }
 }
 
-// Whether the pair kernel votes at every width (double) or once per j and
-// pass (float). A vote lets the wave stop at the first width, widest
-// first, whose support no lane reaches (the narrower ones are zero as
-// well); it costs a compare and about seven scalar instructions and
-// branches. Float terms issue at twice the rate of double ones, and there
-// the scalar issue of a vote per width bounded the loop (7.2 ms against
-// 4.4 ms with one vote per j at the paper-scale scan); in double the
-// terms a vote per width saves are worth more (6.8 ms against 7.4 ms).
-template <typename T>
-constexpr bool kTriVoteEach = std::is_same<T, double>::value;
-
-// One pass of a tile pair over widths [b_lo, b_hi). With a vote per width
-// the wave stops at the first one, widest first, that no lane reaches.
-// With one vote per j, on the pass's widest width, a j that no lane
-// reaches is skipped and otherwise every width of the pass adds its terms,
-// zero outside their supports; a pass narrower than BC evaluates its last
-// width in the spare slots, whose sums are dropped. Either way a skipped
-// term is an exact zero, so the sums do not depend on the voting.
+// One pass of a tile pair over widths [b_lo, b_hi). With one vote per j, on
+// the pass's widest width, a j that no lane reaches is skipped and otherwise
+// every width of the pass adds its terms, zero outside their supports (a vote
+// per width and the scalar instructions it takes bounded the loop: 7.2 ms
+// against 4.4 ms at the paper-scale scan); a pass narrower than BC evaluates
+// its last width in the spare slots, whose sums are dropped. A skipped term is
+// an exact zero, so the sums do not depend on the voting.
 // LIVE_ALL: every (i, j) of the pair is counted (an off-diagonal pair of
 // full tiles), so no per-term mask. IMG: the pass holds a width that
 // reaches its image; no vote stops such a width, and every width of the
 // pass adds the image term, exactly 0 for those that do not reach their
-// image (a branch per width on the image bit was 9 % slower in double).
+// image.
 // A pass without one has no image code (as a select per term it cost five
 // instructions in float).
 template <typename T, int BC, bool LIVE_ALL, bool IMG>
@@ -153,19 +138,7 @@ __device__ __forceinline__ void tri_pass(typename TriPacked<T>::type pi, bool va
     const bool live = LIVE_ALL || (valid_i && (!diag || jj > tid));
     const T r = tri_dist(pi, tj[jj]);
     const T rp = K.period - r;  // the image's distance
-    if (kTriVoteEach<T>) {
-      bool go = true;  // uniform across the wave
-#pragma unroll
-      for (int bb = BC - 1; bb >= 0; --bb) {
-        const int b = b_lo + bb;
-        if (b < b_hi && go) {
-          const T a = clamp01(fma(r, ka[bb], T(1)));
-          const bool img = IMG && ((K.image >> b) & 1);
-          go = img || !__all(!live || a == T(0));
-          if (go) tri_add<T, LIVE_ALL, IMG>(r, rp, a, kc[bb], ka[bb], live, s1[bb], s2[bb]);
-        }
-      }
-    } else if (IMG || !__all(!live || clamp01(fma(r, ktop, T(1))) == T(0))) {
+    if (IMG || !__all(!live || clamp01(fma(r, ktop, T(1))) == T(0))) {
 #pragma unroll
       for (int bb = 0; bb < BC; ++bb)
         tri_add<T, LIVE_ALL, IMG>(r, rp, clamp01(fma(r, ka[bb], T(1))), kc[bb], ka[bb], live, s1[bb], s2[bb]);

@@ -192,18 +192,10 @@ struct Packed<float> {
   static constexpr int per_particle = 1;
 };
 
-// Packed particle of the triangle-shape pair kernel: the wrapped position
-// as a fraction of the period in double (the float form uses the 32-bit
-// phase of Packed<float>).
-struct FracPos {
-  double f;
-};
+// Packed particle of the triangle-shape pair kernel (float form): the 32-bit
+// phase of Packed<float>.
 template <typename T>
 struct TriPacked;
-template <>
-struct TriPacked<double> {
-  using type = FracPos;
-};
 template <>
 struct TriPacked<float> {
   using type = uint32_t;
@@ -227,6 +219,10 @@ inline kde_status launch_pack_sorted(const T* x, int64_t n, double L, const Sort
 size_t cv_workspace_bytes(int64_t n, int B, int prec);
 kde_status cv_scan(const kde_domain* dom, int64_t n, const void* x, int B, const double* kappas, double* cv,
                    double* sums, int32_t* argmin, void* ws, size_t ws_bytes, hipStream_t s, uint32_t* status);
+// The triangle's scan in double (tri_cells.hip).
+size_t tri_scan_workspace_bytes(int64_t n, int B);
+kde_status tri_scan_f64(const kde_domain* dom, int64_t n, const double* x, int B, const double* widths, double* cv,
+                        double* sums, int32_t* argmin, void* ws, size_t ws_bytes, hipStream_t s, uint32_t* status);
 size_t deposit_workspace_bytes(int64_t n, int M);
 size_t adapt_workspace_bytes(int64_t n);
 kde_status deposit(const kde_domain* dom, int64_t n, const void* x, const void* kap, double kappa, double* rho,

@@ -79,8 +79,6 @@ template kde_status launch_pack_sorted_as<double, double>(const double*, int64_t
                                                           double*, int32_t*, hipStream_t, uint32_t*);
 template kde_status launch_pack_sorted_as<float, uint32_t>(const float*, int64_t, double, const SortPlan&, int32_t*,
                                                            uint32_t*, int32_t*, hipStream_t, uint32_t*);
-template kde_status launch_pack_sorted_as<double, FracPos>(const double*, int64_t, double, const SortPlan&, int32_t*,
-                                                           FracPos*, int32_t*, hipStream_t, uint32_t*);
 
 // ------------------------------------------------------ deterministic sums
 
