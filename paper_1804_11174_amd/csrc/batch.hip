@@ -75,6 +75,10 @@ struct SetDev {
   double* rho;        // M
   double* cv;         // B
   double* kstar;      // 1
+  int* kbest;         // 1: its index in the list
+  int pil_mom;        // the pilot tries the moments first (deposit_tries_moments)
+  double* pil_S;      // 2 kNarrowMax
+  unsigned int* pil_ok;  // they gave the pilot (zeroed by the first kernel)
   double* kstar_user; // 1 or NULL
   uint32_t* status;   // the set's numeric status word (KDE_NUMERIC_* bits)
 };
@@ -82,7 +86,7 @@ struct SetDev {
 // Unit prefix sums, one array of nsets + 1 per multi-unit phase.
 enum Prefix {
   PF_PAIRS, PF_CV_L1, PF_CHUNKS, PF_DEP_L1, PF_BLOCKS, PF_AD_L1, PF_SORT, PF_MOMENTS, PF_MOM_SUM, PF_SERIES, PF_FIN,
-  PF_COUNT
+  PF_PIL_MOMENTS, PF_PIL_SUM, PF_PIL_SYNTH, PF_COUNT
 };
 
 struct BatchArgs {
@@ -90,7 +94,7 @@ struct BatchArgs {
   const int64_t* prefix;  // PF_COUNT x (nsets + 1)
   unsigned long long* counters;
   uint32_t* statuses;     // nsets numeric status words, in the caller's set order
-  unsigned int* done;     // nsets counters of finished series units
+  unsigned int* done;     // nsets counters of finished series units, then nsets pil_ok words
   int nsets;
   int B;
   double alpha;
@@ -137,6 +141,7 @@ __global__ void __launch_bounds__(kBlock) batch_zero_kernel(unsigned long long* 
   for (int k = threadIdx.x; k < nsets; k += kBlock) {
     statuses[k] = 0u;
     done[k] = 0u;
+    done[nsets + k] = 0u;
   }
 }
 
@@ -191,6 +196,7 @@ __global__ void __launch_bounds__(kBlock) batch_series_kernel(BatchArgs a, FKapp
   const int best = series_unit(kap.k[b], min(uni32(s.mom.M), kap.order[b]), uni_ptr(s.S), double(s.n_cv), s.L, b, b0,
                                a.B, uni_ptr(s.cv), nullptr, b0 == a.B ? uni_ptr(s.done) : nullptr, dyn_series, sm);
   if (best >= 0 && threadIdx.x == 0) {
+    *s.kbest = best;
     *s.kstar = kap.k[best];
     if (s.kstar_user) *s.kstar_user = kap.k[best];
   }
@@ -273,7 +279,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Pai
 }
 
 // Level-1 row blocks of a [rows x cols] partial array of every set.
-enum L1Source { SRC_CV, SRC_DEP, SRC_AD };
+enum L1Source { SRC_CV, SRC_PILOT, SRC_DEP, SRC_AD };
 
 template <int SRC>
 __global__ void __launch_bounds__(kBlock) batch_level1_kernel(BatchArgs a, int phase, int pf_index) {
@@ -292,7 +298,8 @@ __global__ void __launch_bounds__(kBlock) batch_level1_kernel(BatchArgs a, int p
     int cols;
     if (SRC == SRC_CV) {
       in = s.partials; l1 = s.cv_l1; rows = s.slots; cols = 2 * a.B;
-    } else if (SRC == SRC_DEP) {
+    } else if (SRC == SRC_PILOT || SRC == SRC_DEP) {
+      if (SRC == SRC_PILOT && s.pil_mom && *s.pil_ok) continue;
       in = s.dep_part; l1 = s.dep_l1; rows = s.chunks; cols = s.M;
     } else {
       in = s.ad_part; l1 = s.ad_l1; rows = s.blocks; cols = 2;
@@ -316,11 +323,58 @@ __global__ void __launch_bounds__(kBlock) batch_cv_finalize_kernel(BatchArgs a, 
     __syncthreads();
     cv_finalize_block(raw, a.B, s.b0, double(s.n_cv), s.L, kap, s.cv, nullptr, nullptr, v, &best);
     if (threadIdx.x == 0) {
+      *s.kbest = best;
       *s.kstar = kap.k[best];
       if (s.kstar_user) *s.kstar_user = kap.k[best];
     }
     __syncthreads();
   }
+}
+
+// The pilot of the sets that try the moments (double): moments of all N
+// particles to the order of kappa*, row sums, grid; nothing where that order
+// is beyond the narrow form.
+template <typename T>
+__global__ void __launch_bounds__(kMomBlock) batch_pilot_moments_kernel(BatchArgs a, FKappas kap) {
+  __shared__ MomSmem sm;
+  const int64_t* pf = a.prefix + PF_PIL_MOMENTS * (a.nsets + 1);
+  const int64_t u = int64_t(blockIdx.x);
+  if (u >= pf[a.nsets]) return;
+  const int si = uni32(find_set(pf, a.nsets, u));
+  const SetDev& s = a.sets[si];
+  const int order = uni32(kap.order[*s.kbest]);
+  if (order > kNarrowMax) return;
+  unit_table_fill(sm.unit);
+  __syncthreads();
+  moments_unit<T>(uni_ptr(static_cast<const T*>(s.x)), uni64(s.n), s.L, moment_plan(uni64(s.n), order),
+                  u - uni64(pf[si]), 0, uni_ptr(s.dep_part), sm, uni_ptr(s.status));
+}
+
+__global__ void __launch_bounds__(kBlock) batch_pilot_sum_kernel(BatchArgs a, FKappas kap) {
+  __shared__ double red[kBlock];
+  const int64_t* pf = a.prefix + PF_PIL_SUM * (a.nsets + 1);
+  const int64_t u = int64_t(blockIdx.x);
+  if (u >= pf[a.nsets]) return;
+  const int si = uni32(find_set(pf, a.nsets, u));
+  const SetDev& s = a.sets[si];
+  const int order = uni32(kap.order[*s.kbest]);
+  if (order > kNarrowMax) return;
+  moments_reduce(uni_ptr(s.dep_part), moment_plan(uni64(s.n), order).rows, 2 * order, u - uni64(pf[si]),
+                 uni_ptr(s.pil_S), red);
+}
+
+__global__ void __launch_bounds__(kBlock) batch_pilot_synthesis_kernel(BatchArgs a, FKappas kap) {
+  __shared__ SynthSmem sm;
+  extern __shared__ __align__(16) unsigned char dyn[];
+  const int64_t* pf = a.prefix + PF_PIL_SYNTH * (a.nsets + 1);
+  const int64_t u = int64_t(blockIdx.x);
+  if (u >= pf[a.nsets]) return;
+  const SetDev& s = a.sets[uni32(find_set(pf, a.nsets, u))];
+  const int order = uni32(kap.order[*s.kbest]);
+  if (order > kNarrowMax) return;
+  const bool good = deposit_synthesis(*s.kstar, order, uni_ptr(s.pil_S), double(s.n), s.L, uni32(s.M),
+                                      uni_ptr(s.pilot), reinterpret_cast<double2*>(dyn), sm);
+  if (good && threadIdx.x == 0) *s.pil_ok = 1u;
 }
 
 // Deposit chunks of every set: the pilot at kappa* (PER = false) or the
@@ -335,6 +389,7 @@ __global__ void __launch_bounds__(kBlock) batch_deposit_kernel(BatchArgs a) {
   if (u >= pf[a.nsets]) return;
   const int si = uni32(find_set(pf, a.nsets, u));
   const SetDev& s = a.sets[si];
+  if (!PER && uni32(s.pil_mom) && *s.pil_ok) return;  // the moments gave the pilot
   const int64_t c = u - uni64(pf[si]);
   const int M = uni32(s.M);
   const int chunk = uni32(s.chunk);
@@ -357,6 +412,7 @@ __global__ void __launch_bounds__(kBlock) batch_level2_kernel(BatchArgs a, int p
     if (WHAT == 1) {
       for (int c = threadIdx.x; c < 2; c += kBlock) s.ad_sums[c] = colsum_level2(s.ad_l1, s.g_ad, 2, c, 1.0);
     } else {
+      if (WHAT == 0 && s.pil_mom && *s.pil_ok) continue;
       double* out = (WHAT == 0) ? s.pilot : s.rho;
       const double scale = 1.0 / double(s.n);
       for (int c = threadIdx.x; c < s.M; c += kBlock) out[c] = colsum_level2(s.dep_l1, s.g_dep, s.M, c, scale);
@@ -408,7 +464,7 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
   const int ns = int(b.sets.size());
   unsigned long long* cnt = c.take<unsigned long long>(kCounters);
   uint32_t* statuses = c.take<uint32_t>(size_t(ns));
-  unsigned int* done = c.take<unsigned int>(size_t(ns));
+  unsigned int* done = c.take<unsigned int>(2 * size_t(ns));
   SetDev* ds = c.take<SetDev>(ns);
   int64_t* dp = c.take<int64_t>(size_t(PF_COUNT) * (ns + 1));
   if (descs) descs->assign(ns, SetDev{});
@@ -464,13 +520,20 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
     d.rho = in.rho;
     d.cv = in.cv ? in.cv : c.take<double>(size_t(b.B));
     d.kstar = c.take<double>(1);
+    d.kbest = c.take<int>(1);
+    d.pil_mom = deposit_tries_moments(b.prec, in.N, in.M) ? 1 : 0;
+    d.pil_S = d.pil_mom ? c.take<double>(2 * kNarrowMax) : nullptr;
+    d.pil_ok = done + ns + r;
+    const MomentPlan pil = moment_plan(in.N, kNarrowMax);  // (the narrow form's chunks do not depend on the order)
     d.kstar_user = in.kappa_star;
     d.status = statuses + b.order[r];
     if (descs) (*descs)[r] = d;
     const int64_t per[PF_COUNT] = {pairs ? d.slots * d.groups : 0, pairs ? d.g_cv : 0, d.chunks, d.g_dep, d.blocks,
                                    d.g_ad, pairs ? int64_t(d.sblocks) : 0,
                                    d.b0 > 0 ? d.mom.chunks * d.mom.mblocks : 0,
-                                   d.b0 > 0 ? ceil_div(2 * d.mom.M, kRedCols) : 0, int64_t(d.b0), pairs ? 1 : 0};
+                                   d.b0 > 0 ? ceil_div(2 * d.mom.M, kRedCols) : 0, int64_t(d.b0), pairs ? 1 : 0,
+                                   d.pil_mom ? pil.chunks : 0, d.pil_mom ? ceil_div(2 * kNarrowMax, kRedCols) : 0,
+                                   int64_t(d.pil_mom)};
     for (int k = 0; k < PF_COUNT; ++k) {
       if (prefix) (*prefix)[size_t(k) * (ns + 1) + r] = acc[k];
       acc[k] += per[k];
@@ -591,6 +654,17 @@ static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const st
                          a);
       KDE_CHECK_LAUNCH();
     }
+    if (!adaptive && total(PF_PIL_SYNTH) > 0) {
+      const FKappas fk = fourier_list(b.kappas.data(), b.B);
+      hipLaunchKernelGGL(batch_pilot_moments_kernel<T>, dim3(unsigned(total(PF_PIL_MOMENTS))), dim3(kMomBlock), 0, s,
+                         a, fk);
+      KDE_CHECK_LAUNCH();
+      hipLaunchKernelGGL(batch_pilot_sum_kernel, dim3(unsigned(total(PF_PIL_SUM))), dim3(kBlock), 0, s, a, fk);
+      KDE_CHECK_LAUNCH();
+      hipLaunchKernelGGL(batch_pilot_synthesis_kernel, dim3(unsigned(total(PF_PIL_SYNTH))), dim3(kBlock),
+                         sizeof(double2) * size_t(b.max_M), s, a, fk);
+      KDE_CHECK_LAUNCH();
+    }
     {
       if (adaptive)
         hipLaunchKernelGGL((batch_deposit_kernel<T, true, G>), dim3(unsigned(total(PF_CHUNKS))), dim3(kBlock),
@@ -600,9 +674,14 @@ static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const st
                            dep_lds, s, a);
     }
     KDE_CHECK_LAUNCH();
-    hipLaunchKernelGGL(batch_level1_kernel<SRC_DEP>,
-                       dim3(launch_grid(b, batch_level1_kernel<SRC_DEP>, 0, total(PF_DEP_L1))), dim3(kBlock), 0, s, a,
-                       int(adaptive ? PH_RHO_L1 : PH_PIL_L1), int(PF_DEP_L1));
+    if (adaptive)
+      hipLaunchKernelGGL(batch_level1_kernel<SRC_DEP>,
+                         dim3(launch_grid(b, batch_level1_kernel<SRC_DEP>, 0, total(PF_DEP_L1))), dim3(kBlock), 0, s,
+                         a, int(PH_RHO_L1), int(PF_DEP_L1));
+    else
+      hipLaunchKernelGGL(batch_level1_kernel<SRC_PILOT>,
+                         dim3(launch_grid(b, batch_level1_kernel<SRC_PILOT>, 0, total(PF_DEP_L1))), dim3(kBlock), 0,
+                         s, a, int(PH_PIL_L1), int(PF_DEP_L1));
     KDE_CHECK_LAUNCH();
     if (adaptive)
       hipLaunchKernelGGL(batch_level2_kernel<2>, dim3(launch_grid(b, batch_level2_kernel<2>, 0, ns)), dim3(kBlock), 0,
@@ -792,6 +871,7 @@ kde_status kde_batch_run(kde_batch* b, void* ws, size_t ws_bytes, void* stream) 
   if (!b) return fail(KDE_E_NOT_FOUND, "batch is NULL");
   const BatchPlan& im = b->plan;
   KDE_RETURN_IF(check_workspace(ws, ws_bytes, im.ws_need));
+  if (im.prec == KDE_F64) KDE_RETURN_IF(check_lds(sizeof(double2) * size_t(im.max_M) + sizeof(SynthSmem)));
   KDE_RETURN_IF(check_lds(2 * size_t(im.max_M) * elem_size(im.prec) +
                           (im.prec == KDE_F64 ? sizeof(DepSmem<double>) : sizeof(DepSmem<float>))));
   if (!b->graph.exec || b->graph.ws != ws || b->graph.ws_bytes != ws_bytes)

@@ -24,6 +24,7 @@
 // deposits and gathers with the same decomposition; its per-particle
 // parameter is the half-width h_i. Adaptive widths are von Mises only.
 #include "dev_density.hpp"
+#include "dev_fourier.hpp"
 #include "dev_tri.hpp"
 
 namespace kde {
@@ -32,14 +33,27 @@ namespace kde {
 template <typename T, bool PER, int G>
 __global__ void __launch_bounds__(kBlock) deposit_kernel(const T* __restrict__ x, const T* __restrict__ kap,
                                                         double kappa_g, int64_t n, int M, double L, int chunk,
-                                                        double* __restrict__ partials, uint32_t* status) {
+                                                        double* __restrict__ partials, uint32_t* status,
+                                                        const unsigned int* skip) {
   __shared__ DepSmem<T> sm;
+  if (skip && *skip) return;  // the moments gave the grid
   extern __shared__ __align__(16) unsigned char dyn[];
   SinCos<T>* tab = reinterpret_cast<SinCos<T>*>(dyn);
   node_table(M, tab);
   const int64_t lo = int64_t(blockIdx.x) * chunk;
   const int cnt = int(min(int64_t(chunk), n - lo));
   deposit_block<T, PER, G>(x, kap, kappa_g, M, L, lo, cnt, partials + int64_t(blockIdx.x) * M, tab, sm, status);
+}
+
+// The grid from the particles' moments (dev_fourier.hpp); *ok stays 0 where
+// the sum over the particles has to follow. Dynamic LDS: Mg unit vectors.
+__global__ void __launch_bounds__(kBlock) deposit_synthesis_kernel(const double* __restrict__ S, int M, double kappa,
+                                                                  double n, double L, int Mg,
+                                                                  double* __restrict__ rho, unsigned int* ok) {
+  __shared__ SynthSmem sm;
+  extern __shared__ __align__(16) unsigned char dyn[];
+  const bool good = deposit_synthesis(kappa, M, S, n, L, Mg, rho, reinterpret_cast<double2*>(dyn), sm);
+  if (good && threadIdx.x == 0) *ok = 1u;
 }
 
 // S adjacent lanes per particle (S = 1, 2, 4 or 8, from gather_split), lane
@@ -220,24 +234,23 @@ size_t adapt_workspace_bytes(int64_t n) {
 
 template <typename T, bool PER>
 static kde_status launch_deposit_t(const kde_domain* dom, int64_t n, const T* x, const T* kap, double kappa,
-                                   double* rho, double* partials, int chunk, int64_t chunks, hipStream_t s,
-                                   uint32_t* status) {
+                                   double* partials, int chunk, int64_t chunks, hipStream_t s, uint32_t* status,
+                                   TimedLaunch& timed, hipEvent_t start, const unsigned int* skip) {
   const int M = dom->M;
   const dim3 grid{unsigned(chunks)}, block{unsigned(kBlock)};
   const double kg = kappa;
   const size_t lds = 2 * size_t(M) * sizeof(T);
   KDE_RETURN_IF(check_lds(lds + sizeof(DepSmem<T>)));
-  TimedLaunch timed(KDE_KERNEL_DEPOSIT, s);
   if (M <= kBlock) {
-    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 1>), grid, block, lds, s, timed.start(), timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status);
+    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 1>), grid, block, lds, s, start, timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status, skip);
   } else if (M <= 2 * kBlock) {
-    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 2>), grid, block, lds, s, timed.start(), timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status);
+    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 2>), grid, block, lds, s, start, timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status, skip);
   } else if (M <= 4 * kBlock) {
-    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 4>), grid, block, lds, s, timed.start(), timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status);
+    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 4>), grid, block, lds, s, start, timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status, skip);
   } else if (M <= 8 * kBlock) {
-    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 8>), grid, block, lds, s, timed.start(), timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status);
+    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 8>), grid, block, lds, s, start, timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status, skip);
   } else {
-    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 16>), grid, block, lds, s, timed.start(), timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status);
+    hipExtLaunchKernelGGL((deposit_kernel<T, PER, 16>), grid, block, lds, s, start, timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status, skip);
   }
   KDE_CHECK_LAUNCH();
   return KDE_OK;
@@ -272,8 +285,10 @@ kde_status deposit(const kde_domain* dom, int64_t n, const void* x, const void* 
   const int64_t chunks = ceil_div(n, chunk);
   Carver c(ws, ws_bytes);
   double* partials = c.take<double>(size_t(chunks) * dom->M);
-  double* scratch = c.take<double>(column_sum_scratch(chunks, dom->M) / sizeof(double) + 1);
+  const size_t sums = column_sum_scratch(chunks, dom->M) / sizeof(double);
+  double* scratch = c.take<double>(sums + 1);
   if (!c.fits()) return fail(KDE_E_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, c.used);
+  const unsigned int* skip = nullptr;
   if (dom->shape == KDE_SHAPE_TRIANGLE) {
     if (dom->prec == KDE_F64) {
       const double* xx = static_cast<const double*>(x);
@@ -286,18 +301,40 @@ kde_status deposit(const kde_domain* dom, int64_t n, const void* x, const void* 
       KDE_RETURN_IF((hh ? launch_tri_deposit_t<float, true>(dom, n, xx, hh, kappa, partials, chunk, chunks, s, status)
                         : launch_tri_deposit_t<float, false>(dom, n, xx, hh, kappa, partials, chunk, chunks, s, status)));
     }
-  } else if (dom->prec == KDE_F64) {
-    const double* xx = static_cast<const double*>(x);
-    const double* kk = static_cast<const double*>(kap);
-    KDE_RETURN_IF((kk ? launch_deposit_t<double, true>(dom, n, xx, kk, kappa, rho, partials, chunk, chunks, s, status)
-                      : launch_deposit_t<double, false>(dom, n, xx, kk, kappa, rho, partials, chunk, chunks, s, status)));
   } else {
-    const float* xx = static_cast<const float*>(x);
-    const float* kk = static_cast<const float*>(kap);
-    KDE_RETURN_IF((kk ? launch_deposit_t<float, true>(dom, n, xx, kk, kappa, rho, partials, chunk, chunks, s, status)
-                      : launch_deposit_t<float, false>(dom, n, xx, kk, kappa, rho, partials, chunk, chunks, s, status)));
+    TimedLaunch timed(KDE_KERNEL_DEPOSIT, s);
+    hipEvent_t start = timed.start();
+    const int order = kap ? 0 : fourier_order(kappa);
+    if (!kap && deposit_tries_moments(dom->prec, n, dom->M) && order <= kNarrowMax) {
+      // their partial rows (at most 256 of 2 kNarrowMax) and sums fit the rows
+      // of the sum over the particles (n M >= 2^25: at least 2^16 doubles),
+      // which overwrites them if it has to run; the word behind the column
+      // sums' scratch is nobody else's
+      static_assert(size_t(kMomChunks + 1) * 2 * kNarrowMax <= (size_t(1) << 25) / kDepMaxChunk);
+      double* S = partials + size_t(kMomChunks) * 2 * kNarrowMax;
+      unsigned int* ok = reinterpret_cast<unsigned int*>(scratch + sums);
+      const ScanBufs mom{partials, S, ok};
+      KDE_RETURN_IF(check_lds(sizeof(double2) * size_t(dom->M) + sizeof(SynthSmem)));
+      KDE_RETURN_IF(launch_moments(static_cast<const double*>(x), n, dom->L, order, mom, s, start, nullptr, status));
+      hipLaunchKernelGGL(deposit_synthesis_kernel, dim3(1), dim3(kBlock), sizeof(double2) * size_t(dom->M), s,
+                         (const double*)S, order, kappa, double(n), dom->L, dom->M, rho, ok);
+      KDE_CHECK_LAUNCH();
+      start = nullptr;
+      skip = ok;
+    }
+    if (dom->prec == KDE_F64) {
+      const double* xx = static_cast<const double*>(x);
+      const double* kk = static_cast<const double*>(kap);
+      KDE_RETURN_IF((kk ? launch_deposit_t<double, true>(dom, n, xx, kk, kappa, partials, chunk, chunks, s, status, timed, start, skip)
+                        : launch_deposit_t<double, false>(dom, n, xx, kk, kappa, partials, chunk, chunks, s, status, timed, start, skip)));
+    } else {
+      const float* xx = static_cast<const float*>(x);
+      const float* kk = static_cast<const float*>(kap);
+      KDE_RETURN_IF((kk ? launch_deposit_t<float, true>(dom, n, xx, kk, kappa, partials, chunk, chunks, s, status, timed, start, skip)
+                        : launch_deposit_t<float, false>(dom, n, xx, kk, kappa, partials, chunk, chunks, s, status, timed, start, skip)));
+    }
   }
-  return launch_column_sum(partials, chunks, dom->M, scratch, rho, s, 1.0 / double(n));
+  return launch_column_sum(partials, chunks, dom->M, scratch, rho, s, 1.0 / double(n), skip);
 }
 
 // Lanes per particle for the gather: split the node loop while the

@@ -67,7 +67,7 @@ const int kMaxOrder = fourier_order(KDE_MAX_FOURIER_KAPPA);
 
 struct FourierBufs {
   ScanBufs scan;     // partial rows and moments [2 M] (re, im)
-  double* rho;       // [3 kStartEvals][M + 1] (refine) or [M + 1] (pilot)
+  double* rho;       // [3 kStartEvals][M + 1] (refine)
   double* cvgrid;    // [B]
   double* start;     // refine: (cv, g, g') at the bracket ends and the first iterate, then that iterate's u
   double* w;         // [2 M] pilot weights
@@ -81,7 +81,7 @@ FourierBufs carve_fourier(Carver& c, int op, int64_t n, int B) {
   FourierBufs b{};
   const int M = kMaxOrder;
   b.scan = carve_scan(c, n, M);
-  const int slots = (op == KDE_OP_CV_FOURIER) ? 0 : (op == KDE_OP_CV_REFINE ? 3 * kStartEvals : 1);
+  const int slots = op == KDE_OP_CV_REFINE ? 3 * kStartEvals : 0;
   b.rho = c.take<double>(size_t(slots) * (M + 1));
   if (op == KDE_OP_CV_REFINE) {
     b.cvgrid = c.take<double>(size_t(B));
@@ -538,14 +538,15 @@ __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict
   }
 }
 
-// w_m = rho_m(kappa) S_m, m = 1..M (one workgroup).
+// w_m = rho_m(kappa) S_m, m = 1..M (one workgroup; dynamic LDS: series_lds).
 __global__ void __launch_bounds__(kBlock) pilot_weights_kernel(const double* __restrict__ S, int M, double kappa,
-                                                              double* __restrict__ rho, double* __restrict__ w) {
-  __shared__ BesselSmem sm;
-  bessel_series<false>(kappa, M, rho, nullptr, nullptr, sm);
+                                                              double* __restrict__ w) {
+  __shared__ ScanSmem sm;
+  extern __shared__ __align__(16) double dyn_series[];
+  series_rho(kappa, M, dyn_series, sm);
   for (int m = 1 + threadIdx.x; m <= M; m += kBlock) {
-    w[2 * (m - 1)] = rho[m] * S[2 * (m - 1)];
-    w[2 * (m - 1) + 1] = rho[m] * S[2 * (m - 1) + 1];
+    w[2 * (m - 1)] = dyn_series[m] * S[2 * (m - 1)];
+    w[2 * (m - 1) + 1] = dyn_series[m] * S[2 * (m - 1) + 1];
   }
 }
 
@@ -732,7 +733,8 @@ kde_status kde_adapt_widths_exact(const kde_domain* dom, int64_t N, const void* 
   const FourierBufs b = carve_fourier(c, KDE_OP_ADAPT_EXACT, N, 0);
   const int M = fourier_order(kappa_star);
   KDE_RETURN_IF(moments_any(dom, N, x, M, b, s));
-  hipLaunchKernelGGL(pilot_weights_kernel, dim3(1), dim3(kBlock), 0, s, (const double*)b.scan.S, M, kappa_star, b.rho, b.w);
+  hipLaunchKernelGGL(pilot_weights_kernel, dim3(1), dim3(kBlock), series_lds(M), s, (const double*)b.scan.S, M,
+                     kappa_star, b.w);
   KDE_CHECK_LAUNCH();
   const int64_t blocks = ceil_div(N, kBlock);
   const dim3 grid{unsigned(blocks)};

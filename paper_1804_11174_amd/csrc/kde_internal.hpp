@@ -74,7 +74,7 @@ struct Carver {
 };
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+__host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ------------------------------------------------------------------ timing
 
@@ -239,8 +239,9 @@ size_t fourier_workspace_bytes(int op, int64_t n, int B);
 
 // Deterministic column sums: out[c] = scale * sum_r in[r][c], fixed order.
 // `scratch` must hold column_sum_scratch(rows, cols) bytes.
+// With `skip` the kernels do nothing where *skip is not 0 (a device word).
 kde_status launch_column_sum(const double* in, int64_t rows, int cols, double* scratch,
-                             double* out, hipStream_t s, double scale = 1.0);
+                             double* out, hipStream_t s, double scale = 1.0, const unsigned int* skip = nullptr);
 size_t column_sum_scratch(int64_t rows, int cols);
 
 // ----------------------------------------------------------- device helpers

@@ -88,13 +88,17 @@ template kde_status launch_pack_sorted_as<float, uint32_t>(const float*, int64_t
 constexpr int kSumCols = 64;
 
 __global__ void __launch_bounds__(kSumCols) colsum_level1_kernel(const double* __restrict__ in, int64_t rows,
-                                                                int cols, double* __restrict__ l1) {
+                                                                int cols, double* __restrict__ l1,
+                                                                const unsigned int* skip) {
+  if (skip && *skip) return;
   const int c = int(blockIdx.y) * kSumCols + threadIdx.x;
   if (c < cols) l1[int64_t(blockIdx.x) * cols + c] = colsum_level1(in, rows, cols, blockIdx.x, c);
 }
 
 __global__ void __launch_bounds__(kSumCols) colsum_level2_kernel(const double* __restrict__ l1, int64_t g, int cols,
-                                                                double scale, double* __restrict__ out) {
+                                                                double scale, double* __restrict__ out,
+                                                                const unsigned int* skip) {
+  if (skip && *skip) return;
   const int c = int(blockIdx.x) * kSumCols + threadIdx.x;
   if (c < cols) out[c] = colsum_level2(l1, g, cols, c, scale);
 }
@@ -103,7 +107,9 @@ __global__ void __launch_bounds__(kSumCols) colsum_level2_kernel(const double* _
 // level-1 row is 0 + l1, exactly l1, so out[c] = l1 * scale has the
 // two-kernel result's bits.
 __global__ void __launch_bounds__(kSumCols) colsum_single_kernel(const double* __restrict__ in, int64_t rows,
-                                                                int cols, double scale, double* __restrict__ out) {
+                                                                int cols, double scale, double* __restrict__ out,
+                                                                const unsigned int* skip) {
+  if (skip && *skip) return;
   const int c = int(blockIdx.x) * kSumCols + threadIdx.x;
   if (c < cols) out[c] = colsum_level1(in, rows, cols, 0, c) * scale;
 }
@@ -113,18 +119,18 @@ size_t column_sum_scratch(int64_t rows, int cols) {
 }
 
 kde_status launch_column_sum(const double* in, int64_t rows, int cols, double* scratch, double* out, hipStream_t s,
-                             double scale) {
+                             double scale, const unsigned int* skip) {
   const int64_t g = ceil_div(rows, kSumRows);
   const unsigned cb = unsigned(ceil_div(cols, kSumCols));
   if (g == 1) {
-    hipLaunchKernelGGL(colsum_single_kernel, dim3(cb), dim3(kSumCols), 0, s, in, rows, cols, scale, out);
+    hipLaunchKernelGGL(colsum_single_kernel, dim3(cb), dim3(kSumCols), 0, s, in, rows, cols, scale, out, skip);
     KDE_CHECK_LAUNCH();
     return KDE_OK;
   }
-  hipLaunchKernelGGL(colsum_level1_kernel, dim3(unsigned(g), cb), dim3(kSumCols), 0, s, in, rows, cols, scratch);
+  hipLaunchKernelGGL(colsum_level1_kernel, dim3(unsigned(g), cb), dim3(kSumCols), 0, s, in, rows, cols, scratch, skip);
   KDE_CHECK_LAUNCH();
   hipLaunchKernelGGL(colsum_level2_kernel, dim3(cb), dim3(kSumCols), 0, s, (const double*)scratch, g, cols, scale,
-                     out);
+                     out, skip);
   KDE_CHECK_LAUNCH();
   return KDE_OK;
 }
