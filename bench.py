@@ -272,7 +272,21 @@ def pilot_through_moments(prec, n, M, kappa):
     return prec == "f64" and n * M >= 1 << 25 and fourier_order(kappa) <= 112
 
 
-def secondary_rooflines(prec, n, M, kern, kstar):
+# The double gather through the field's modes: operations per particle and
+# mode (recurrence 2, product and rotation 6, magnitude 1), to the order
+# of the largest concentration.
+MODE_OPS = 9
+
+
+def gather_modes(prec, n, M, kmax):
+    """Modes per particle where the library's gather with per-particle
+    concentrations goes through them, else 0."""
+    order = math.ceil(math.sqrt(83.0 * (kmax + 7.0))) + 1
+    through = prec == "f64" and M >= 256 and n >= 8 * M and n * M >= 1 << 25
+    return order if through and order <= min(M + M // 4 * 3, 1023) else 0
+
+
+def secondary_rooflines(prec, n, M, kern, kstar, kmax):
     el = 8 if prec == "f64" else 4
     summed = 0.5 if pilot_through_moments(prec, n, M, kstar) else 1.0
     chunk = min(512, max(64, -(-n // 2048)))
@@ -283,10 +297,13 @@ def secondary_rooflines(prec, n, M, kern, kstar):
         ms = kern[name]["avg_ms"]
         if not ms:
             continue
-        evals = n * M * (summed if name == "deposit" else 1.0)
-        alu = evals * NODE_OPS[prec] / (ms * 1e-3)
+        evals, ops = n * M * (summed if name == "deposit" else 1.0), NODE_OPS[prec]
+        modes = gather_modes(prec, n, M, kmax) if name == "gather" else 0
+        if modes:
+            evals, ops = n * modes, MODE_OPS
+        alu = evals * ops / (ms * 1e-3)
         bw = bytes_ / (ms * 1e-3)
-        out[name] = {"bound": "alu", "ops_per_eval": NODE_OPS[prec], "evals_per_launch": evals,
+        out[name] = {"bound": "alu", "ops_per_eval": ops, "evals_per_launch": evals,
                      "alu_frac": alu / PEAK_LANE_OPS[prec], "hbm_gbs": bw / 1e9, "hbm_frac": bw / HBM_PEAK,
                      "avg_ms": ms}
     ms = kern["adapt"]["avg_ms"]
@@ -602,7 +619,7 @@ def main():
                       ("gather", kde.KDE_KERNEL_GATHER), ("adapt", kde.KDE_KERNEL_ADAPT)):
         tot, cnt = kde.kde_timing_read(kid)
         kern[name] = {"launches": cnt, "avg_ms": tot / cnt if cnt else None}
-    secondary = secondary_rooflines(args.prec, n, M, kern, kstar)
+    secondary = secondary_rooflines(args.prec, n, M, kern, kstar, float(k_i.max().item()))
 
     pair_evals = B * n_cv * (n_cv - 1) / 2
     value = pair_evals / (ms_step * 1e-3)
