@@ -693,15 +693,19 @@ __host__ __device__ inline bool deposit_tries_moments(int prec, int64_t n, int M
 // concave asinh is at least its integral over [0, m], the left-hand side.
 // Newton's method from above (the left-hand side is convex). rho_m grows
 // with kappa, so the order of the largest concentration serves a whole list.
-inline int fourier_order(double k) {
-  if (!(k > 0.0)) return 1;
+inline double fourier_root(double k) {
   static const double lim = -std::log(kFourierTail);
   double m = std::sqrt(2.0 * lim * k) + 12.0;
   for (int it = 0; it < 4; ++it) {
     const double u = m / k, as = std::log(u + std::sqrt(u * u + 1.0));
     m -= (m * as - m * m / (std::sqrt(m * m + k * k) + k) - lim) / as;
   }
-  return int(std::ceil(m)) < 1 ? 1 : int(std::ceil(m));
+  return m;
+}
+inline int fourier_order(double k) {
+  if (!(k > 0.0)) return 1;
+  const int m = int(std::ceil(fourier_root(k)));
+  return m < 1 ? 1 : m;
 }
 
 // Concentrations with their series orders (fourier_order of each; the

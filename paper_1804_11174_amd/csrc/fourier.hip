@@ -23,13 +23,14 @@
 //                       (series_sums), the ratios multiplied up to rho_m by
 //                       a prefix scan, the sums of the series in a fixed
 //                       order; the last workgroup takes the first minimum.
-//   newton_start_kernel -- three workgroups side by side: the objective
-//                       and its derivatives at the two ends of the bracket
-//                       around the scan's first minimum and at the first
-//                       iterate (the vertex of the parabola through the three
-//                       grid values there).
-//   newton_kernel    -- one workgroup: from those, Newton's method on
-//                       u = log(kappa) with bisection as the safeguard.
+//   refine_moments_kernel, refine_series_kernel -- the same for the
+//                       refinement, by rotations and in an order of its own.
+//   newton_kernel    -- one workgroup: the objective and its derivatives at
+//                       the two ends of the bracket around the scan's first
+//                       minimum and at the first iterate (the vertex of the
+//                       parabola through the three grid values there); from
+//                       those, Newton's method on u = log(kappa) with
+//                       bisection as the safeguard.
 //                       The derivatives come from the same
 //                       recurrence differentiated in kappa:
 //                         r'_k  = r_k^2 (2k / kappa^2 - r'_{k+1}),
@@ -61,15 +62,60 @@ namespace {
 
 constexpr int kPilotRun = 64;           // rotations between exact phase restarts
 constexpr int kMaxNewton = 100;
-constexpr int kStartEvals = 3;          // refine: bracket ends and first iterate, evaluated side by side
+constexpr size_t kNewtonLds = 100 * 1024;  // what the Newton kernels' arrays may take of the LDS
+constexpr int kStartEvals = 3;          // refine: bracket ends and first iterate
 
 const int kMaxOrder = fourier_order(KDE_MAX_FOURIER_KAPPA);
 
+// The refinement's own moments (refine_moments_kernel).
+constexpr int kRotM = 16;               // consecutive m per group
+constexpr int kRotGroups = 2;           // groups per workgroup
+constexpr int kRotChunks = 64;          // partials' budget: kRotChunks x kMaxOrder (re, im) pairs
+constexpr int64_t kRotBlocks = 4096;    // (chunk, group) pairs a launch aims for
+constexpr int kRotPerThread = 8;        // fewest particles per thread
+
+// Partials' budget for N particles, in units of kMaxOrder (re, im) pairs.
+int64_t rot_budget(int64_t n) {
+  return std::max<int64_t>(1, std::min<int64_t>(kRotChunks, n / (int64_t(kBlock) * kRotPerThread)));
+}
+
+// Particle chunks of N particles to order M: about kRotBlocks pairs over the
+// ceil(M / kRotM) mode groups, at least kRotPerThread particles per thread,
+// and chunks x M within the partials' budget. The sums' order depends on it.
+int64_t rot_chunks(int64_t n, int M) {
+  int64_t c = ceil_div(kRotBlocks, ceil_div(M, kRotM));
+  c = std::min<int64_t>(c, n / (int64_t(kBlock) * kRotPerThread));
+  c = std::min<int64_t>(c, rot_budget(n) * kMaxOrder / M);
+  return std::max<int64_t>(1, c);
+}
+
+// The list with the orders at which the product of Amos's bounds on the
+// ratios itself falls below kFourierTail: fourier_order's closed form of that
+// product rises by up to 0.051 too far, so it is one higher where its root lies just
+// above a whole number, and the refinement's last bits hang on the cut.
+FKappas refine_list(const double* k, int B) {
+  FKappas f = fourier_list(k, B);
+  static const double lim = std::log(kFourierTail);
+  for (int b = 0; b < B; ++b) {
+    const double below = fourier_root(k[b]) - double(f.order[b] - 1);
+    if (!(k[b] > 0.0) || f.order[b] < 2 || below > 0.06) continue;
+    double lg = 0.0;
+    for (int m = 1; m < f.order[b]; ++m) {
+      const double nu = double(m) - 0.5;
+      lg += std::log(k[b] / (nu + std::sqrt(nu * nu + k[b] * k[b])));
+    }
+    if (lg < lim) --f.order[b];
+  }
+  return f;
+}
+
 struct FourierBufs {
   ScanBufs scan;     // partial rows and moments [2 M] (re, im)
-  double* rho;       // [3 kStartEvals][M + 1] (refine)
+  double* rows;      // refine: [chunks][2 M] partial moments, their column sums' scratch
+  double* colsum;
+  double* S;         // refine: [2 M] moments
+  double* rho;       // refine: [3][M + 1], where LDS does not hold them
   double* cvgrid;    // [B]
-  double* start;     // refine: (cv, g, g') at the bracket ends and the first iterate, then that iterate's u
   double* w;         // [2 M] pilot weights
   double* lf;        // [N] log pilot
   double* bpart;     // [blocks][2]
@@ -80,12 +126,17 @@ struct FourierBufs {
 FourierBufs carve_fourier(Carver& c, int op, int64_t n, int B) {
   FourierBufs b{};
   const int M = kMaxOrder;
-  b.scan = carve_scan(c, n, M);
-  const int slots = op == KDE_OP_CV_REFINE ? 3 * kStartEvals : 0;
-  b.rho = c.take<double>(size_t(slots) * (M + 1));
+  if (op != KDE_OP_CV_REFINE) b.scan = carve_scan(c, n, M);
   if (op == KDE_OP_CV_REFINE) {
+    // any order's chunks x 2 M partials fit the budget; its column-sum
+    // scratch, ceil(chunks / R) x 2 M for R rows per level-1 block, is at
+    // most (chunks x 2 M) / R + 2 M
+    const int64_t budget = rot_budget(n);
+    b.rows = c.take<double>(size_t(budget) * 2 * M);
+    b.colsum = c.take<double>((column_sum_scratch(budget * M, 2) + column_sum_scratch(1, 2 * M)) / sizeof(double) + 1);
+    b.S = c.take<double>(size_t(2) * M);
+    b.rho = c.take<double>(size_t(3) * (M + 1));
     b.cvgrid = c.take<double>(size_t(B));
-    b.start = c.take<double>(3 * kStartEvals + 1);
   }
   if (op == KDE_OP_ADAPT_EXACT) {
     const int64_t blocks = ceil_div(n, kBlock);
@@ -148,6 +199,84 @@ __global__ void __launch_bounds__(kBlock) moments_reduce_kernel(const double* __
   moments_reduce(partials, rows, cols, blockIdx.x, S, red);
 }
 
+// The refinement's moments. It reports the number of Newton steps, and the
+// last of them are taken at the noise of the objective, so the count hangs on
+// every last bit of what it evaluates: with the matrix product's moments,
+// which are as exact, it came out one higher or lower for a fifth of random
+// samples. The refinement therefore keeps the order of its sums: a thread
+// accumulates its particles over kRotM modes by rotation, the threads'
+// sums meet in wave_sum's tree and the waves' in order, the chunks' in the
+// column sums. What is left to save is around them: the position's phase is
+// made once for two groups of modes, and the tree runs over all values at
+// once, each exchange halving what a lane holds (63 exchanges for the 64
+// values of two groups instead of 384). 65,536 particles to order 911: 33 us
+// (47.6 with a group per workgroup and a tree per value).
+template <typename T>
+__global__ void __launch_bounds__(kBlock) refine_moments_kernel(const T* __restrict__ x, int64_t n, double L, int M,
+                                                               int64_t per_chunk, double* __restrict__ rows,
+                                                               uint32_t* status) {
+  constexpr int kVals = 2 * kRotM;
+  __shared__ double red[kRotGroups][kBlock / 64][kVals];
+  const int64_t ch = blockIdx.x;
+  const int m0 = 1 + int(blockIdx.y) * (kRotM * kRotGroups);
+  double v[kRotGroups][kVals];
+#pragma unroll
+  for (int g = 0; g < kRotGroups; ++g)
+#pragma unroll
+    for (int k = 0; k < kVals; ++k) v[g][k] = 0.0;
+  const int64_t lo = ch * per_chunk, hi = min(n, lo + per_chunk);
+  uint32_t* const st = blockIdx.y == 0 ? status : nullptr;  // one column of blocks notes the positions
+  for (int64_t j = lo + threadIdx.x; j < hi; j += kBlock) {
+    note_numeric(st, !isfinite(double(x[j])), false);
+    const double f = wrap_d(double(x[j]), L) / L;
+    double c1, s1;
+    sincospi(2.0 * f, &s1, &c1);
+#pragma unroll
+    for (int g = 0; g < kRotGroups; ++g) {
+      double c, s;
+      phase(m0 + g * kRotM, f, c, s);
+#pragma unroll
+      for (int k = 0; k < kRotM; ++k) {
+        v[g][2 * k] += c;
+        v[g][2 * k + 1] += s;
+        const double nc = c * c1 - s * s1;
+        s = fma(s, c1, c * s1);
+        c = nc;
+      }
+    }
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int g = 0; g < kRotGroups; ++g) {
+    // after the exchange at distance d a lane keeps the half of the values
+    // that its bit d names
+    int half = kVals / 2;
+#pragma unroll
+    for (int d = 32; d >= 2; d >>= 1) {
+      const bool up = (lane & d) != 0;
+#pragma unroll
+      for (int k = 0; k < half; ++k) {
+        const double keep = up ? v[g][k + half] : v[g][k];
+        const double give = up ? v[g][k] : v[g][k + half];
+        v[g][k] = keep + shfl_xor_d(give, d);
+      }
+      half >>= 1;
+    }
+    v[g][0] += shfl_xor_d(v[g][0], 1);
+    if ((lane & 1) == 0) red[g][wave][lane >> 1] = v[g][0];
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < kRotGroups * kVals; t += kBlock) {
+    const int g = t / kVals, k = t % kVals;
+    const int m = m0 + g * kRotM + (k >> 1);
+    if (m <= M) {
+      double sum = 0.0;
+      for (int w = 0; w < kBlock / 64; ++w) sum += red[g][w][k];
+      rows[ch * 2 * int64_t(M) + 2 * (m - 1) + (k & 1)] = sum;
+    }
+  }
+}
+
 // Shared memory of the workgroup-wide series (double-buffered scans).
 struct BesselSmem {
   double mat[2][kBlock][4];  // Mobius matrices (row-major 2x2)
@@ -184,12 +313,21 @@ __device__ __forceinline__ void mat_mul_norm(const double* a, const double* b, d
 // sums over m (a combined prefix scan). The composition is a reassociation
 // of the recurrence; its rounding grows with the tree depth instead of the
 // length of the chain.
+// `ratio` (LDS, series_length doubles) keeps each thread's ratios for its
+// later walks (DER only); a scan ends at the last thread that has a run. The
+// two forms round the ratio's denominator once (DER) or twice; they always
+// have, and the refinement's last bits are kept (refine_moments_kernel).
+__host__ __device__ inline int series_length(int M, double kappa) {
+  return int(ceil(sqrt(double(M) * double(M) + 40.0 * kappa))) + 16;
+}
+
 template <bool DER>
-__device__ void bessel_series(double kappa, int M, double* __restrict__ rho, double* __restrict__ d1,
-                              double* __restrict__ d2, BesselSmem& sm) {
+__device__ __forceinline__ void bessel_series(double kappa, int M, double* __restrict__ rho, double* __restrict__ d1,
+                                              double* __restrict__ d2, double* __restrict__ ratio, BesselSmem& sm) {
   const int t = threadIdx.x;
-  const int Ms = int(ceil(sqrt(double(M) * double(M) + 40.0 * kappa))) + 16;
+  const int Ms = series_length(M, kappa);
   const int len = (Ms + kBlock - 1) / kBlock;
+  const int nt = (Ms + len - 1) / len;
   const int lo = 1 + t * len, hi = min(Ms, (t + 1) * len);  // empty when lo > hi
   const double ik2 = DER ? 1.0 / (kappa * kappa) : 0.0;
   const double ik3 = DER ? ik2 / kappa : 0.0;
@@ -205,7 +343,7 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
   int cur = 0;
   for (int k = 0; k < 4; ++k) sm.mat[0][t][k] = P[k];
   __syncthreads();
-  for (int d = 1; d < kBlock; d <<= 1) {
+  for (int d = 1; d < nt; d <<= 1) {
     if (t + d < kBlock)
       mat_mul_norm(sm.mat[cur][t], sm.mat[cur][t + d], sm.mat[cur ^ 1][t]);
     else
@@ -217,8 +355,9 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
   {
     double r = r_top;
     for (int m = hi; m >= lo; --m) {
-      r = kappa / (2.0 * double(m) + kappa * r);
+      r = kappa / (DER ? fma(kappa, r, 2.0 * double(m)) : fma(2.0, double(m), kappa * r));
       if (m <= M) rho[m] = r;
+      if (DER) ratio[m] = r;
     }
   }
   double rp_top = 0.0, rpp_top = 0.0;
@@ -226,9 +365,9 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
     // 2. r'_m = 2m r_m^2 / kappa^2 - r_m^2 r'_{m+1}.
     double a = 0.0, b = 1.0;
     {
-      double r = r_top;
+      double r;
       for (int m = hi; m >= lo; --m) {
-        r = kappa / (2.0 * double(m) + kappa * r);
+        r = ratio[m];
         const double r2 = r * r;
         a = fma(-r2, a, 2.0 * double(m) * r2 * ik2);
         b = -r2 * b;
@@ -239,7 +378,7 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
     sm.aff[0][t][1] = b;
     __syncthreads();
     cur = 0;
-    for (int d = 1; d < kBlock; d <<= 1) {
+    for (int d = 1; d < nt; d <<= 1) {
       if (t + d < kBlock) {
         sm.aff[cur ^ 1][t][0] = fma(sm.aff[cur][t][1], sm.aff[cur][t + d][0], sm.aff[cur][t][0]);
         sm.aff[cur ^ 1][t][1] = sm.aff[cur][t][1] * sm.aff[cur][t + d][1];
@@ -255,9 +394,9 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
     a = 0.0;
     b = 1.0;
     {
-      double r = r_top, rp = rp_top;
+      double r, rp = rp_top;
       for (int m = hi; m >= lo; --m) {
-        r = kappa / (2.0 * double(m) + kappa * r);
+        r = ratio[m];
         const double r2 = r * r;
         rp = r2 * (2.0 * double(m) * ik2 - rp);
         const double A = 2.0 * rp * rp / r - 4.0 * double(m) * r2 * ik3;
@@ -271,7 +410,7 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
     sm.aff[0][t][1] = b;
     __syncthreads();
     cur = 0;
-    for (int d = 1; d < kBlock; d <<= 1) {
+    for (int d = 1; d < nt; d <<= 1) {
       if (t + d < kBlock) {
         sm.aff[cur ^ 1][t][0] = fma(sm.aff[cur][t][1], sm.aff[cur][t + d][0], sm.aff[cur][t][0]);
         sm.aff[cur ^ 1][t][1] = sm.aff[cur][t][1] * sm.aff[cur][t + d][1];
@@ -284,9 +423,9 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
     }
     rpp_top = (t + 1 < kBlock) ? sm.aff[cur][t + 1][0] : 0.0;
     {
-      double r = r_top, rp = rp_top, rpp = rpp_top;
+      double r, rp = rp_top, rpp = rpp_top;
       for (int m = hi; m >= lo; --m) {
-        r = kappa / (2.0 * double(m) + kappa * r);
+        r = ratio[m];
         const double r2 = r * r;
         rp = r2 * (2.0 * double(m) * ik2 - rp);
         rpp = 2.0 * rp * rp / r - r2 * (4.0 * double(m) * ik3 + rpp);
@@ -311,7 +450,7 @@ __device__ void bessel_series(double kappa, int M, double* __restrict__ rho, dou
   sm.pre[0][t][2] = sE;
   __syncthreads();
   cur = 0;
-  for (int d = 1; d < kBlock; d <<= 1) {
+  for (int d = 1; d < nt; d <<= 1) {
     if (t >= d) {
       sm.pre[cur ^ 1][t][0] = sm.pre[cur][t - d][0] * sm.pre[cur][t][0];
       sm.pre[cur ^ 1][t][1] = sm.pre[cur][t - d][1] + sm.pre[cur][t][1];
@@ -359,16 +498,40 @@ __global__ void __launch_bounds__(kBlock) series_kernel(const double* __restrict
   if (best >= 0 && threadIdx.x == 0) *argmin = best;
 }
 
+// The refinement's grid of objectives, one workgroup per concentration, with
+// its own order of sums too. Dynamic LDS: M + 1 doubles.
+__global__ void __launch_bounds__(kBlock) refine_series_kernel(const double* __restrict__ S, int M, double n, double L,
+                                                              FKappas kap, double* __restrict__ cv) {
+  __shared__ BesselSmem sm;
+  extern __shared__ __align__(16) double dyn_series[];
+  double* rho = dyn_series;
+  const int b = blockIdx.x;
+  const int Mb = min(M, kap.order[b]);
+  bessel_series<false>(kap.k[b], Mb, rho, nullptr, nullptr, nullptr, sm);
+  double a = 0.0, c = 0.0;
+  for (int m = 1 + threadIdx.x; m <= Mb; m += kBlock) {
+    const double sr = S[2 * (m - 1)], si = S[2 * (m - 1) + 1];
+    const double P = fma(sr, sr, si * si);
+    const double q = P - n;
+    const double r = rho[m];
+    a = fma(r * r, P, a);
+    c = fma(r, q, c);
+  }
+  a = block_sum(a, sm.red);
+  c = block_sum(c, sm.red);
+  if (threadIdx.x == 0) cv[b] = (2.0 * a / (n * n) - 4.0 * c / (n * (n - 1.0)) - 1.0) / L;
+}
+
 struct Eval {
   double cv, g, gp;
 };
 
 // Objective and its first two derivatives in u = log(kappa), all threads,
 // with the series cut at order Mk (that of a kappa at least as large).
-__device__ Eval eval_u(double u, const double* __restrict__ S, int Mk, double n, double L, double* rho, double* d1,
-                       double* d2, BesselSmem& sm) {
+__device__ __noinline__ Eval eval_u(double u, const double* __restrict__ S, int Mk, double n, double L, double* rho,
+                                       double* d1, double* d2, double* ratio, BesselSmem& sm) {
   const double kappa = exp(u);
-  bessel_series<true>(kappa, Mk, rho, d1, d2, sm);
+  bessel_series<true>(kappa, Mk, rho, d1, d2, ratio, sm);
   double A = 0.0, C = 0.0, A1 = 0.0, C1 = 0.0, A2 = 0.0, C2 = 0.0;
   for (int m = 1 + threadIdx.x; m <= Mk; m += kBlock) {
     const double sr = S[2 * (m - 1)], si = S[2 * (m - 1) + 1];
@@ -399,6 +562,184 @@ __device__ Eval eval_u(double u, const double* __restrict__ S, int Mk, double n,
   e.gp = kappa * kappa * ckk + kappa * ck;
   __syncthreads();  // rho, d1, d2 are rewritten by the next evaluation
   return e;
+}
+
+// eval_u by one wave for a series of at most 64 H modes (a run is one mode
+// then): lane l holds modes 1 + l + 64 h, and every scan, sum and expression
+// is the workgroup form's, on registers and shuffles. No barrier and no LDS
+// exchange per scan step: about 7 us against 10.
+template <int H>
+struct Lanes {
+  // o[t] = v[t + d], `rest` past the end
+  static __device__ __forceinline__ void down(const double (&v)[H], int d, int lane, double rest, double (&o)[H]) {
+    if (d >= 64) {
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        o[h] = rest;
+#pragma unroll
+        for (int k = h + 1; k < H; ++k)
+          if (d == 64 * (k - h)) o[h] = v[k];
+      }
+      return;
+    }
+    double s[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) s[h] = __shfl(v[h], (lane + d) & 63, 64);
+#pragma unroll
+    for (int h = 0; h < H; ++h) o[h] = lane + d < 64 ? s[h] : (h + 1 < H ? s[(h + 1) % H] : rest);
+  }
+  // o[t] = v[t - d], `rest` before the start
+  static __device__ __forceinline__ void up(const double (&v)[H], int d, int lane, double rest, double (&o)[H]) {
+    if (d >= 64) {
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        o[h] = rest;
+#pragma unroll
+        for (int k = 0; k < h; ++k)
+          if (d == 64 * (h - k)) o[h] = v[k];
+      }
+      return;
+    }
+    double s[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) s[h] = __shfl(v[h], (lane - d) & 63, 64);
+#pragma unroll
+    for (int h = 0; h < H; ++h) o[h] = lane >= d ? s[h] : (h > 0 ? s[(h + H - 1) % H] : rest);
+  }
+};
+
+// Suffix scan of the affine maps x -> a + b x; a[t + 1] into top.
+template <int H>
+__device__ __forceinline__ void affine_tops(double (&a)[H], double (&b)[H], int nt, int lane, double (&top)[H]) {
+  for (int d = 1; d < nt; d <<= 1) {
+    double oa[H], ob[H];
+    Lanes<H>::down(a, d, lane, 0.0, oa);
+    Lanes<H>::down(b, d, lane, 1.0, ob);
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      a[h] = fma(b[h], oa[h], a[h]);
+      b[h] = b[h] * ob[h];
+    }
+  }
+  Lanes<H>::down(a, 1, lane, 0.0, top);
+}
+
+template <int H>
+__device__ __noinline__ Eval eval_wave(double u, const double* __restrict__ power, int Mk, double n, double L) {
+  const double kappa = exp(u);
+  const int lane = threadIdx.x & 63;
+  const int nt = series_length(Mk, kappa);
+  const double ik2 = 1.0 / (kappa * kappa);
+  const double ik3 = ik2 / kappa;
+  double pa[H], pb[H], pc[H], pd[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int m = 1 + lane + 64 * h;
+    const Mat2 P = m <= nt ? mat_norm(Mat2{0.0, kappa, kappa, 2.0 * double(m)}) : Mat2{1.0, 0.0, 0.0, 1.0};
+    pa[h] = P.a;
+    pb[h] = P.b;
+    pc[h] = P.c;
+    pd[h] = P.d;
+  }
+  for (int d = 1; d < nt; d <<= 1) {
+    double qa[H], qb[H], qc[H], qd[H];
+    Lanes<H>::down(pa, d, lane, 1.0, qa);
+    Lanes<H>::down(pb, d, lane, 0.0, qb);
+    Lanes<H>::down(pc, d, lane, 0.0, qc);
+    Lanes<H>::down(pd, d, lane, 1.0, qd);
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const Mat2 P = mat_mul(Mat2{pa[h], pb[h], pc[h], pd[h]}, Mat2{qa[h], qb[h], qc[h], qd[h]});
+      pa[h] = P.a;
+      pb[h] = P.b;
+      pc[h] = P.c;
+      pd[h] = P.d;
+    }
+  }
+  double top[H], r[H], a[H], b[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) a[h] = pb[h] / pd[h];
+  Lanes<H>::down(a, 1, lane, 0.0, top);
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int m = 1 + lane + 64 * h;
+    const bool in = m <= nt;
+    r[h] = kappa / fma(kappa, top[h], 2.0 * double(m));
+    const double r2 = r[h] * r[h];
+    a[h] = in ? 2.0 * double(m) * r2 * ik2 : 0.0;
+    b[h] = in ? -r2 : 1.0;
+  }
+  affine_tops<H>(a, b, nt, lane, top);
+  double rp[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int m = 1 + lane + 64 * h;
+    const bool in = m <= nt;
+    const double r2 = r[h] * r[h];
+    rp[h] = r2 * (2.0 * double(m) * ik2 - top[h]);
+    const double A = 2.0 * rp[h] * rp[h] / r[h] - 4.0 * double(m) * r2 * ik3;
+    a[h] = in ? A : 0.0;
+    b[h] = in ? -r2 : 1.0;
+  }
+  affine_tops<H>(a, b, nt, lane, top);
+  double q[H], e[H], sp[H], sD[H], sE[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int m = 1 + lane + 64 * h;
+    const bool in = m <= Mk;
+    const double r2 = r[h] * r[h];
+    const double rpp = 2.0 * rp[h] * rp[h] / r[h] - r2 * (4.0 * double(m) * ik3 + top[h]);
+    q[h] = rp[h] / r[h];
+    e[h] = rpp / r[h] - q[h] * q[h];
+    sp[h] = in ? r[h] : 1.0;
+    sD[h] = in ? q[h] : 0.0;
+    sE[h] = in ? e[h] : 0.0;
+  }
+  for (int d = 1; d < nt; d <<= 1) {
+    double op[H], oD[H], oE[H];
+    Lanes<H>::up(sp, d, lane, 1.0, op);
+    Lanes<H>::up(sD, d, lane, 0.0, oD);
+    Lanes<H>::up(sE, d, lane, 0.0, oE);
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      sp[h] = op[h] * sp[h];
+      sD[h] = oD[h] + sD[h];
+      sE[h] = oE[h] + sE[h];
+    }
+  }
+  double p[H], D[H], E[H];
+  Lanes<H>::up(sp, 1, lane, 1.0, p);
+  Lanes<H>::up(sD, 1, lane, 0.0, D);
+  Lanes<H>::up(sE, 1, lane, 0.0, E);
+  double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int m = 1 + lane + 64 * h;
+    double t[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (m <= Mk) {
+      const double rm = p[h] * r[h];
+      D[h] += q[h];
+      E[h] += e[h];
+      const double r1 = rm * D[h], r2 = rm * (D[h] * D[h] + E[h]);
+      const double P = power[m], w = P - n;
+      t[0] = (rm * rm) * P;
+      t[1] = rm * w;
+      t[2] = (2.0 * rm * r1) * P;
+      t[3] = r1 * w;
+      t[4] = (2.0 * fma(r1, r1, rm * r2)) * P;
+      t[5] = r2 * w;
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] += wave_sum(t[k]);
+  }
+  const double n2 = n * n, nn = n * (n - 1.0);
+  Eval o;
+  o.cv = (2.0 * v[0] / n2 - 4.0 * v[1] / nn - 1.0) / L;
+  const double ck = (2.0 * v[2] / n2 - 4.0 * v[3] / nn) / L;
+  const double ckk = (2.0 * v[4] / n2 - 4.0 * v[5] / nn) / L;
+  o.g = kappa * ck;
+  o.gp = kappa * kappa * ckk + kappa * ck;
+  return o;
 }
 
 // The refinement's bracket: the list neighbours of the scan's first
@@ -453,40 +794,28 @@ __device__ Bracket make_bracket(const double* __restrict__ cvgrid, int B, const 
   return r;
 }
 
-// Workgroup w evaluates the objective at the bracket's lower end (w = 0),
-// upper end (1) and first iterate (2), each with its own series arrays
-// (slots 3w .. 3w + 2 of rho); start[3w..3w+2] = (cv, g, g'),
-// start[9] = the first iterate's u.
-__global__ void __launch_bounds__(kBlock) newton_start_kernel(const double* __restrict__ S, int M, double n,
-                                                             double L, FKappas kap, int B,
-                                                             const double* __restrict__ cvgrid,
-                                                             double* __restrict__ rho, double* __restrict__ start) {
-  __shared__ BesselSmem sm;
-  const Bracket br = make_bracket(cvgrid, B, kap, M);
-  if (!br.valid) return;
-  const int w = blockIdx.x;
-  const double u = (w == 0) ? br.ul : (w == 1) ? br.uh : br.u0;
-  double* r = rho + size_t(3 * w) * (M + 1);
-  const Eval e = eval_u(u, S, br.Mk, n, L, r, r + (M + 1), r + 2 * (M + 1), sm);
-  if (threadIdx.x == 0) {
-    start[3 * w] = e.cv;
-    start[3 * w + 1] = e.g;
-    start[3 * w + 2] = e.gp;
-    if (w == 2) start[3 * kStartEvals] = u;
-  }
-}
-
-// result: [kappa*, cv(kappa*), dCV/du at kappa*, steps, b*], continuing
-// from newton_start_kernel's evaluations. Every thread runs the same
-// control flow on the same values (block sums reach all).
+// result: [kappa*, cv(kappa*), dCV/du at kappa*, steps, b*], by one workgroup.
+// A bracket whose series has at most 256 modes (kappa* up to a few hundred): waves
+// 0, 1 and 2 evaluate its ends and the first iterate side by side, then wave 0
+// goes on alone; a longer one is evaluated by the whole workgroup, one point
+// after the other. Dynamic LDS: the ratios of the series (series_length + 1)
+// and, where they fit (LDS), three arrays of M + 1.
+// 65,536 particles, 32 concentrations up to 1e4 (911 modes, the bracket's series
+// about 90): 49 us, 62 with a workgroup for each start and another for the steps.
+template <bool LDS>
 __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict__ S, int M, double n, double L,
                                                        FKappas kap, int B, const double* __restrict__ cvgrid,
-                                                       const double* __restrict__ start, double* __restrict__ rho3,
-                                                       double* __restrict__ result, int32_t* __restrict__ argmin) {
+                                                       double* __restrict__ rho3, double* __restrict__ result,
+                                                       int32_t* __restrict__ argmin) {
   __shared__ BesselSmem sm;
-  double* rho = rho3;
-  double* d1 = rho3 + (M + 1);
-  double* d2 = rho3 + 2 * (M + 1);
+  __shared__ double power[kBlock + 1];
+  __shared__ Eval start[kStartEvals];
+  extern __shared__ __align__(16) double dyn_series[];
+  double* rho = LDS ? dyn_series : rho3;
+  double* d1 = rho + (M + 1);
+  double* d2 = rho + 2 * (M + 1);
+  double* ratio = LDS ? dyn_series + 3 * size_t(M + 1) : dyn_series;
+  const int wave = threadIdx.x >> 6;
   const Bracket br = make_bracket(cvgrid, B, kap, M);
   const int bs = br.bs;
   if (argmin && threadIdx.x == 0) *argmin = bs;
@@ -498,9 +827,26 @@ __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict
     cv_best = cvgrid[bs];
     g_best = 0.0;
   } else {
+    const int modes = series_length(br.Mk, br.khi);
+    const bool alone = modes <= kBlock;
+    if (alone && int(threadIdx.x) < br.Mk) {
+      const double sr = S[2 * threadIdx.x], si = S[2 * threadIdx.x + 1];
+      power[threadIdx.x + 1] = fma(sr, sr, si * si);
+    }
+    __syncthreads();
+    auto eval = [&](double u) {
+      if (!alone) return eval_u(u, S, br.Mk, n, L, rho, d1, d2, ratio, sm);
+      return modes <= 128 ? eval_wave<2>(u, power, br.Mk, n, L) : eval_wave<4>(u, power, br.Mk, n, L);
+    };
+    // the starts: side by side, or one after the other
+    for (int k = alone ? wave : 0; k < kStartEvals; k += alone ? kBlock / 64 : 1) {
+      const Eval e = eval(k == 0 ? br.ul : (k == 1 ? br.uh : br.u0));
+      if (alone ? (threadIdx.x & 63) == 0 : threadIdx.x == 0) start[k] = e;
+    }
+    __syncthreads();
+    if (alone && wave != 0) return;  // (no barrier follows)
     double ul = br.ul, uh = br.uh;
-    const Eval el{start[0], start[1], start[2]};
-    const Eval eh{start[3], start[4], start[5]};
+    const Eval el = start[0], eh = start[1];
     steps = 2;
     if (!(el.g < 0.0 && eh.g > 0.0)) {
       const bool lo_wins = el.cv <= eh.cv;
@@ -508,8 +854,8 @@ __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict
       cv_best = lo_wins ? el.cv : eh.cv;
       g_best = lo_wins ? el.g : eh.g;
     } else {
-      double u = start[3 * kStartEvals];
-      Eval e{start[6], start[7], start[8]};
+      double u = br.u0;
+      Eval e = start[2];
       ++steps;
       for (int it = 0; it < kMaxNewton && e.g != 0.0; ++it) {
         if (e.g < 0.0)
@@ -520,7 +866,7 @@ __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict
         if (!(e.gp > 0.0) || !(un > ul && un < uh)) un = 0.5 * (ul + uh);
         const bool done = fabs(un - u) <= 1e-14 * fmax(1.0, fabs(un)) || (uh - ul) <= 1e-14 * fmax(1.0, fabs(un));
         u = un;
-        e = eval_u(u, S, br.Mk, n, L, rho, d1, d2, sm);
+        e = eval(u);
         ++steps;
         if (done) break;
       }
@@ -620,6 +966,28 @@ kde_status moments_any(const kde_domain* dom, int64_t n, const void* x, int M, c
                         plain_numeric_word());
 }
 
+template <typename T>
+kde_status refine_moments(const T* x, int64_t n, double L, int M, const FourierBufs& b, hipStream_t s) {
+  const int64_t chunks = rot_chunks(n, M);
+  const dim3 grid{unsigned(chunks), unsigned(ceil_div(M, kRotM * kRotGroups))};
+  {
+    TimedLaunch timed(KDE_KERNEL_MOMENTS, s);
+    hipExtLaunchKernelGGL(refine_moments_kernel<T>, grid, dim3(kBlock), 0, s, timed.start(), timed.stop(), 0, x, n, L, M,
+                          ceil_div(n, chunks), b.rows, plain_numeric_word());
+  }
+  KDE_CHECK_LAUNCH();
+  return launch_column_sum(b.rows, chunks, 2 * M, b.colsum, b.S, s);
+}
+
+template <bool LDS>
+kde_status launch_newton(size_t lds, const FourierBufs& b, int M, double n, double L, const FKappas& kl, int B,
+                         const double* grid, double* result, int32_t* argmin, hipStream_t s) {
+  hipLaunchKernelGGL(newton_kernel<LDS>, dim3(1), dim3(kBlock), lds, s, (const double*)b.S, M, n, L, kl, B, grid,
+                     b.rho, result, argmin);
+  KDE_CHECK_LAUNCH();
+  return KDE_OK;
+}
+
 kde_status check_fourier_common(const kde_domain* dom, int64_t N, const void* x, int64_t nmin) {
   KDE_RETURN_IF(check_domain(dom, false));
   if (dom->shape != KDE_SHAPE_VONMISES) return fail(KDE_E_INVALID_ARG, "the Fourier route is defined for the von Mises shape");
@@ -704,18 +1072,24 @@ kde_status kde_cv_refine(const kde_domain* dom, int64_t N, const void* x, int32_
   hipStream_t s = static_cast<hipStream_t>(stream);
   Carver c(ws, ws_bytes);
   const FourierBufs b = carve_fourier(c, KDE_OP_CV_REFINE, N, B);
-  const int M = fourier_order(kappas_h[B - 1]);
-  KDE_RETURN_IF(moments_any(dom, N, x, M, b, s));
+  const FKappas kl = refine_list(kappas_h, B);
+  const int M = kl.order[B - 1];
+  if (dom->prec == KDE_F64)
+    KDE_RETURN_IF(refine_moments(static_cast<const double*>(x), N, dom->L, M, b, s));
+  else
+    KDE_RETURN_IF(refine_moments(static_cast<const float*>(x), N, dom->L, M, b, s));
   double* grid = cv ? cv : b.cvgrid;
-  const FKappas kl = fourier_list(kappas_h, B);
-  KDE_RETURN_IF(launch_series(b.scan, M, N, dom->L, kl, B, B, grid, nullptr, nullptr, s, nullptr));
-  hipLaunchKernelGGL(newton_start_kernel, dim3(kStartEvals), dim3(kBlock), 0, s, (const double*)b.scan.S, M, double(N),
-                     dom->L, kl, B, (const double*)grid, b.rho, b.start);
+  hipLaunchKernelGGL(refine_series_kernel, dim3(unsigned(B)), dim3(kBlock), sizeof(double) * size_t(M + 1), s,
+                     (const double*)b.S, M, double(N), dom->L, kl, grid);
   KDE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(newton_kernel, dim3(1), dim3(kBlock), 0, s, (const double*)b.scan.S, M, double(N), dom->L, kl, B,
-                     (const double*)grid, (const double*)b.start, b.rho, result, argmin);
-  KDE_CHECK_LAUNCH();
-  return KDE_OK;
+  const size_t ratios = sizeof(double) * size_t(series_length(M, kappas_h[B - 1]) + 1);
+  const size_t all = ratios + sizeof(double) * 3 * size_t(M + 1);
+  if (all <= kNewtonLds) {
+    KDE_RETURN_IF(check_lds(all + sizeof(BesselSmem)));
+    return launch_newton<true>(all, b, M, double(N), dom->L, kl, B, grid, result, argmin, s);
+  }
+  KDE_RETURN_IF(check_lds(ratios + sizeof(BesselSmem)));
+  return launch_newton<false>(ratios, b, M, double(N), dom->L, kl, B, grid, result, argmin, s);
 }
 
 kde_status kde_adapt_widths_exact(const kde_domain* dom, int64_t N, const void* x, double kappa_star, double alpha,
