@@ -393,11 +393,11 @@ __global__ void __launch_bounds__(kBlock) batch_deposit_kernel(BatchArgs a) {
   const int64_t c = u - uni64(pf[si]);
   const int M = uni32(s.M);
   const int chunk = uni32(s.chunk);
-  node_table(M, tab);
+  deposit_table(uni64(s.n), M, tab);
   const int64_t lo = c * chunk;
   const int cnt = int(min(int64_t(chunk), uni64(s.n) - lo));
   deposit_block<T, PER, G>(uni_ptr(static_cast<const T*>(s.x)), uni_ptr(static_cast<const T*>(s.kappa_i)),
-                           PER ? 0.0 : *s.kstar, M, s.L, lo, cnt, uni_ptr(s.dep_part) + c * M, tab, sm,
+                           PER ? 0.0 : *s.kstar, uni64(s.n), M, s.L, lo, cnt, uni_ptr(s.dep_part) + c * M, tab, sm,
                            uni_ptr(s.status));
 }
 
@@ -620,7 +620,9 @@ static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const st
   auto total = [&](int pf) { return prefix[size_t(pf) * (ns + 1) + ns]; };
   const CvConsts<T> K = make_consts<T>(b.kappas.data(), b.B);
   const KappaList kl = make_kappa_list<T>(b.kappas.data(), b.B);
-  const size_t dep_lds = 2 * size_t(b.max_M) * sizeof(T);
+  // (a float set of at most kBlock nodes may need more than the largest one)
+  const size_t dep_lds = std::max(2 * sizeof(T) * size_t(b.max_M),
+                                  dep_table_bytes<T>(kDepPairParticles, std::min(b.max_M, kBlock) & ~1));
   const size_t pack_lds = size_t(b.max_cells) * sizeof(int);
 
   hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(kBlock), 0, s, a.counters, a.statuses, a.done, ns);
@@ -872,7 +874,7 @@ kde_status kde_batch_run(kde_batch* b, void* ws, size_t ws_bytes, void* stream) 
   const BatchPlan& im = b->plan;
   KDE_RETURN_IF(check_workspace(ws, ws_bytes, im.ws_need));
   if (im.prec == KDE_F64) KDE_RETURN_IF(check_lds(sizeof(double2) * size_t(im.max_M) + sizeof(SynthSmem)));
-  KDE_RETURN_IF(check_lds(2 * size_t(im.max_M) * elem_size(im.prec) +
+  KDE_RETURN_IF(check_lds(2 * size_t(im.max_M) * elem_size(im.prec) + kBlock * sizeof(SinCos<float>) / 2 +
                           (im.prec == KDE_F64 ? sizeof(DepSmem<double>) : sizeof(DepSmem<float>))));
   if (!b->graph.exec || b->graph.ws != ws || b->graph.ws_bytes != ws_bytes)
     KDE_RETURN_IF(build_graph(b->graph, im, ws, ws_bytes));

@@ -39,10 +39,10 @@ __global__ void __launch_bounds__(kBlock) deposit_kernel(const T* __restrict__ x
   if (skip && *skip) return;  // the moments gave the grid
   extern __shared__ __align__(16) unsigned char dyn[];
   SinCos<T>* tab = reinterpret_cast<SinCos<T>*>(dyn);
-  node_table(M, tab);
+  deposit_table(n, M, tab);
   const int64_t lo = int64_t(blockIdx.x) * chunk;
   const int cnt = int(min(int64_t(chunk), n - lo));
-  deposit_block<T, PER, G>(x, kap, kappa_g, M, L, lo, cnt, partials + int64_t(blockIdx.x) * M, tab, sm, status);
+  deposit_block<T, PER, G>(x, kap, kappa_g, n, M, L, lo, cnt, partials + int64_t(blockIdx.x) * M, tab, sm, status);
 }
 
 // The grid from the particles' moments (dev_fourier.hpp); *ok stays 0 where
@@ -97,7 +97,6 @@ __device__ __forceinline__ T gather_nodes(double xw, double kk, int j, int S, in
       if ((q & (kRun - 1)) == kRun - 1) acc.fold();
     }
   } else if (__all(A >= T(-2.0 * kNearKappa))) {
-#pragma unroll 2
     for (int g = j; g < M; g += S) {
       const T s = node_s(gp, g, M, tab);
       acc.add(tf[g] * Flt<T>::ex_in(A * (s * s), etab));
@@ -106,7 +105,6 @@ __device__ __forceinline__ T gather_nodes(double xw, double kk, int j, int S, in
     // sharp kernels in the wave: near nodes take the exact separation
     const double dx = L / double(M);
     const bool sharp = A < T(-2.0 * kNearKappa);
-#pragma unroll 2
     for (int g = j; g < M; g += S) {
       T s = node_s(gp, g, M, tab);
       if (sharp) s = near_node_s(s, g, dx, gp.w, L);
@@ -115,7 +113,6 @@ __device__ __forceinline__ T gather_nodes(double xw, double kk, int j, int S, in
   } else {
     const double dx = L / double(M);
     const bool sharp = A < T(-2.0 * kNearKappa);
-#pragma unroll 2
     for (int g = j; g < M; g += S) {
       T s = node_s(gp, g, M, tab);
       if (sharp) s = near_node_s(s, g, dx, gp.w, L);
@@ -484,7 +481,7 @@ static kde_status launch_deposit_t(const kde_domain* dom, int64_t n, const T* x,
   const int M = dom->M;
   const dim3 grid{unsigned(chunks)}, block{unsigned(kBlock)};
   const double kg = kappa;
-  const size_t lds = 2 * size_t(M) * sizeof(T);
+  const size_t lds = dep_table_bytes<T>(n, M);
   KDE_RETURN_IF(check_lds(lds + sizeof(DepSmem<T>)));
   if (M <= kBlock) {
     hipExtLaunchKernelGGL((deposit_kernel<T, PER, 1>), grid, block, lds, s, start, timed.stop(), 0, x, kap, kg, n, M, dom->L, chunk, partials, status, skip);

@@ -81,6 +81,25 @@ struct SumOf<float> {
 
 constexpr int kDepMaxChunk = 512;
 
+// The float deposit by node pairs (dep_pair_sums): grids of an even number of
+// nodes from kDepPairFrom to the workgroup's threads, so at most kDepStreams
+// sub-streams share a node, and as many particles as give every CU four
+// workgroups: half of a workgroup's threads add pairs, so with fewer the latency of
+// a thread's sum counts (20,000 particles on 128 nodes 15.9 us against 15.4;
+// 65,536 14.4 against 14.9, 1,048,576 56 against 64). Its table holds the first half
+// a second time.
+constexpr int kDepPairFrom = 32, kDepStreams = kBlock / kDepPairFrom;
+constexpr int64_t kDepPairParticles = 65536;
+template <typename T>
+__host__ __device__ constexpr bool dep_pairs(int64_t n, int M) {
+  return std::is_same<T, float>::value && n >= kDepPairParticles && M >= kDepPairFrom && M <= kBlock && M % 2 == 0;
+}
+// Dynamic LDS of the node table of a deposit of n particles.
+template <typename T>
+__host__ __device__ constexpr size_t dep_table_bytes(int64_t n, int M) {
+  return 2 * sizeof(T) * size_t(dep_pairs<T>(n, M) ? M + M / 2 : M);
+}
+
 // Geometry of a (node, particle) pair. Both forms give s = sin(pi (x_g - x_i) / L):
 //   double: global half-angle vectors, s = sin(pi g/M) a_i - cos(pi g/M) b_i with
 //           (a_i, b_i) = (cos(pi x_i/L), sin(pi x_i/L));
@@ -191,8 +210,8 @@ __device__ __forceinline__ float node_s(const PGeo<float>& p, int g, int M, cons
 // LDS of M SinCos<T>).
 template <typename T>
 struct DepSmem {
-  DepRec<T> rec[kDepMaxChunk];
-  T pw[kDepMaxChunk];
+  DepRec<T> rec[kDepMaxChunk + kDepStreams];
+  T pw[kDepMaxChunk + kDepStreams];
   double red[kBlock];
   double etab[std::is_same<T, double>::value ? 256 : 1];  // exponential table (double form)
 };
@@ -214,6 +233,13 @@ __device__ __forceinline__ void node_table(int M, SinCos<T>* t) {
     sincospi(double(k) / double(M), &sv, &cv);
     t[k] = SinCos<T>{T(sv), T(cv)};
   }
+}
+
+// The table of a deposit (dep_table_bytes).
+template <typename T>
+__device__ __forceinline__ void deposit_table(int64_t n, int M, SinCos<T>* t) {
+  node_table(M, t);
+  if (dep_pairs<T>(n, M) && int(threadIdx.x) < M / 2) t[M + threadIdx.x] = t[threadIdx.x];  // (its own entry)
 }
 
 // One deposit chunk: particles [lo, lo + cnt) onto all M nodes, written to
@@ -267,6 +293,63 @@ __device__ __forceinline__ double dep_node_sum(int g, int sub, int S, int cnt, i
   return acc.value();
 }
 
+// The same in float for the nodes g and g + M/2 at once: entry k + M/2 of the
+// table is entry k turned by a quarter (sin <-> cos and a sign that the square
+// drops), so one record, one table read and one index serve two terms. The
+// chunk's sub-streams lie one after the other (Q records each), so a group's
+// reads differ by immediate offsets, and a record holds M - g0, which
+// indexes the table (its first half repeated behind its end) without a wrap. Every
+// term and every sum is dep_node_sum's: the same bits. What bounds it is the
+// vector pipe, 9.5 issue slots a term against 17. 262,147 particles on 128 nodes
+// with widths of their own: 18.4 us (19.4), of which the pairs take 8 and the
+// chunk's records, in double, 4; 262,144 with one width 14.1 (17.1).
+template <bool PER>
+__device__ __forceinline__ void dep_pair_sums(int g, int sub, int S, int Q, int cnt, const SinCos<float>* tab,
+                                              const DepSmem<float>& sm, double& v0, double& v1) {
+  static_assert(kRun == 8, "a group is a run");
+  const DepRec<float>* rec = sm.rec + sub * Q;
+  const float* pw = sm.pw + sub * Q;
+  const int nq = sub < cnt ? (cnt - sub + S - 1) / S : 0;
+  Acc<float> a0, a1;
+  a0.zero();
+  a1.zero();
+  auto term = [&](int q, float& e0, float& e1) {
+    const DepRec<float> r = rec[q];
+    const SinCos<float> e = tab[g + r.g.g0];
+    const float s0 = fmaf(e.s, r.g.cb, -(e.c * r.g.sb));
+    const float s1 = fmaf(e.c, r.g.cb, e.s * r.g.sb);
+    e0 = Flt<float>::ex_in(r.A * (s0 * s0), nullptr);
+    e1 = Flt<float>::ex_in(r.A * (s1 * s1), nullptr);
+  };
+  auto add = [&](int q, float e0, float e1) {
+    if constexpr (PER) {
+      const float w = pw[q];
+      a0.r = fmaf(w, e0, a0.r);
+      a1.r = fmaf(w, e1, a1.r);
+    } else {
+      a0.add(e0);
+      a1.add(e1);
+    }
+  };
+  int q = 0;
+  for (; q + 8 <= nq; q += 8) {
+    float e0[8], e1[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) term(q + u, e0[u], e1[u]);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add(q + u, e0[u], e1[u]);
+    a0.fold();
+    a1.fold();
+  }
+  for (; q < nq; ++q) {
+    float e0, e1;
+    term(q, e0, e1);
+    add(q, e0, e1);
+  }
+  v0 = a0.value();
+  v1 = a1.value();
+}
+
 // The same for G nodes per thread (g = tid + k kBlock), all particles.
 template <typename T, bool PER, int G, bool NEAR, bool CLAMP, typename Sum>
 __device__ __forceinline__ void dep_node_sums(int tid, int cnt, int M, double L, const SinCos<T>* tab,
@@ -296,9 +379,40 @@ __device__ __forceinline__ void dep_node_sums(int tid, int cnt, int M, double L,
 
 template <typename T, bool PER, int G>
 __device__ __forceinline__ void deposit_block(const T* __restrict__ x, const T* __restrict__ kap, double kappa_g,
-                                              int M, double L, int64_t lo, int cnt, double* __restrict__ out,
+                                              int64_t n, int M, double L, int64_t lo, int cnt, double* __restrict__ out,
                                               const SinCos<T>* tab, DepSmem<T>& sm, uint32_t* status) {
   const int tid = threadIdx.x;
+  if constexpr (std::is_same<T, float>::value) {
+    if (dep_pairs<T>(n, M)) {
+      const int S = kBlock / M, Q = (cnt + S - 1) / S, half = M / 2;
+      for (int k = tid; k < cnt; k += kBlock) {
+        const double xi = double(x[lo + k]);
+        const double ki = PER ? double(kap[lo + k]) : 0.0;
+        note_numeric(status, !isfinite(xi), PER && !(isfinite(ki) && ki >= 0.0));
+        const int slot = int(unsigned(k) % unsigned(S)) * Q + int(unsigned(k) / unsigned(S));
+        DepRec<T> r;
+        particle_terms<T, PER>(x, kap, kappa_g, lo + k, L, M, r, sm.pw[slot]);
+        r.g.g0 = M - r.g.g0;
+        sm.rec[slot] = r;
+      }
+      __syncthreads();
+      const int g = tid % half, sub = tid / half;
+      if (sub < S) {
+        double v0, v1;
+        dep_pair_sums<PER>(g, sub, S, Q, cnt, tab, sm, v0, v1);
+        sm.red[sub * M + g] = v0;
+        sm.red[sub * M + g + half] = v1;
+      }
+      __syncthreads();
+      if (tid < M) {
+        double v = 0.0;
+        for (int q = 0; q < S; ++q) v += sm.red[q * M + tid];
+        out[tid] = PER ? v : v * (1.0 / (L * i0e_f64(kappa_g)));
+      }
+      __syncthreads();
+      return;
+    }
+  }
   int sharp = 0, huge = 0;
   for (int k = tid; k < cnt; k += kBlock) {
     const double xi = double(x[lo + k]);
