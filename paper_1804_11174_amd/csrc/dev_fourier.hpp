@@ -694,7 +694,7 @@ __device__ __forceinline__ bool deposit_synthesis(double kappa, int M, const dou
 // the moments first (double form; a concentration whose series fits the
 // narrow form, kappa <= 146): they cost about 20 us with the 3 launches that find
 // nothing to do, plus 12 ps per particle, against 0.65 ps per particle and
-// node (1,048,576 on 256 nodes: 31.8 us against 180; where the grid is refused
+// node (1,048,576 on 256 nodes: 28 us against 174; where the grid is refused
 // they come on top), so the line is drawn where the sum over the particles
 // takes about as long, 2^25 pairs.
 __host__ __device__ inline bool deposit_tries_moments(int prec, int64_t n, int Mg) {
