@@ -526,7 +526,7 @@ __device__ __forceinline__ void adapt_logsum_block(const T* __restrict__ x, int6
   if (i < n) {
     bool floored;
     const T xv = x[i];
-    lsum = log(pilot_at<T>(xv, L, M, pilot, floored));
+    lsum = log_normal(pilot_at<T>(xv, L, M, pilot, floored));  // (floored: a normal number)
     fl = floored ? 1.0 : 0.0;
     note_numeric(status, !isfinite(double(xv)), false);
   }
@@ -560,7 +560,7 @@ __device__ __forceinline__ void adapt_apply_block(const T* __restrict__ x, int64
   const int64_t i = b * kBlock + threadIdx.x;
   if (i < n) {
     bool floored;
-    const double lf = log(pilot_at<T>(x[i], L, M, pilot, floored));
+    const double lf = log_normal(pilot_at<T>(x[i], L, M, pilot, floored));
     kout[i] = T(kappa_star * exp(2.0 * alpha * (lf - log_g)));
   }
 }

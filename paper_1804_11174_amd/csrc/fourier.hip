@@ -907,40 +907,6 @@ __global__ void __launch_bounds__(kBlock) pilot_weights_kernel(const double* __r
 // particle per thread). A sum over all workgroups by the last one to finish
 // instead of the column sums' two launches was 25 us slower: each workgroup's
 // fence writes its logarithms back.
-//
-// log v for a normal v: v = m 2^e with m in [sqrt(1/2), sqrt(2)), log m = 2
-// atanh z, z = (m - 1) / (m + 1), |z| <= 0.172, by its series to z^23 (what is
-// left out is below 1e-19); ln 2 in two parts, the first of 40 bits, so
-// that its multiples are exact. Error below 1.1 units of max(1, |log v|).
-__device__ __forceinline__ double log_normal(double v) {
-  double m = __builtin_amdgcn_frexp_mant(v);
-  int e = __builtin_amdgcn_frexp_exp(v);
-  const bool low = m < 0.70710678118654752;
-  m = low ? m + m : m;
-  e = low ? e - 1 : e;
-  const double d = m + 1.0;
-  double r = __builtin_amdgcn_rcp(d);  // and two Newton steps
-  r = fma(fma(-d, r, 1.0), r, r);
-  r = fma(fma(-d, r, 1.0), r, r);
-  const double q = (m - 1.0) * r;
-  const double z = fma(fma(-d, q, m - 1.0), r, q);
-  const double w = z * z;
-  double p = 1.0 / 23.0;
-  p = fma(p, w, 1.0 / 21.0);
-  p = fma(p, w, 1.0 / 19.0);
-  p = fma(p, w, 1.0 / 17.0);
-  p = fma(p, w, 1.0 / 15.0);
-  p = fma(p, w, 1.0 / 13.0);
-  p = fma(p, w, 1.0 / 11.0);
-  p = fma(p, w, 1.0 / 9.0);
-  p = fma(p, w, 1.0 / 7.0);
-  p = fma(p, w, 1.0 / 5.0);
-  p = fma(p, w, 1.0 / 3.0);
-  const double z2 = z + z;
-  const double ed = double(e);
-  return fma(ed, 0x1.62e42fefa2000p-1, z2 + fma(z2 * w, p, ed * 0x1.9ef35793c7673p-41));
-}
-
 template <typename T, int P>
 __global__ void __launch_bounds__(kBlock) pilot_kernel(const T* __restrict__ x, int64_t n, double L, int M,
                                                       const double2* __restrict__ w, double floor_v,
