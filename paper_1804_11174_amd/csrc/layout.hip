@@ -103,7 +103,8 @@ __global__ void __launch_bounds__(kSumCols) colsum_level2_kernel(const double* _
   if (c < cols) out[c] = colsum_level2(l1, g, cols, c, scale);
 }
 
-// Both levels at once when there is one row block: level 2 over a single
+// Both levels at once when there is one row block (and more columns than the
+// fused kernel takes): level 2 over a single
 // level-1 row is 0 + l1, exactly l1, so out[c] = l1 * scale has the
 // two-kernel result's bits.
 __global__ void __launch_bounds__(kSumCols) colsum_single_kernel(const double* __restrict__ in, int64_t rows,
@@ -126,7 +127,8 @@ __global__ void __launch_bounds__(kSumCols) colsum_single_kernel(const double* _
 // deposit is 8 % slower with it (too few CUs read), with 1024 columns and more
 // (a lane's reads no longer share lines in time) 3 to 7 %; up to 4096 rows of 512
 // columns it is 0 to 60 % faster (20,000 on 64 nodes 13.4 -> 8.3 us, 1,048,576
-// on 256 82.7 -> 72.7).
+// on 256 82.7 -> 72.7). Few rows gain too: the 28 of a 1780-particle float scan
+// took 8.6 us, each waiting for memory in turn, now 4.5 (8000 on 64 nodes 13.7 -> 8.2).
 constexpr int kFuseThreads = 512;
 constexpr int64_t kFuseRows = 4096;
 constexpr int kFuseCols = 512;
@@ -171,15 +173,15 @@ kde_status launch_column_sum(const double* in, int64_t rows, int cols, double* s
                              double scale, const unsigned int* skip) {
   const int64_t g = ceil_div(rows, kSumRows);
   const unsigned cb = unsigned(ceil_div(cols, kSumCols));
-  if (g == 1) {
-    hipLaunchKernelGGL(colsum_single_kernel, dim3(cb), dim3(kSumCols), 0, s, in, rows, cols, scale, out, skip);
-    KDE_CHECK_LAUNCH();
-    return KDE_OK;
-  }
   if (rows <= kFuseRows && cols <= kFuseCols) {
     const unsigned lines = unsigned(ceil_div(ceil_div(cols, kLineCols), kXcds) * kXcds);
     hipLaunchKernelGGL(colsum_fused_kernel, dim3(lines * kLineCols), dim3(kFuseThreads), 0, s, in, int(rows), cols,
                        scale, out, skip);
+    KDE_CHECK_LAUNCH();
+    return KDE_OK;
+  }
+  if (g == 1) {
+    hipLaunchKernelGGL(colsum_single_kernel, dim3(cb), dim3(kSumCols), 0, s, in, rows, cols, scale, out, skip);
     KDE_CHECK_LAUNCH();
     return KDE_OK;
   }
