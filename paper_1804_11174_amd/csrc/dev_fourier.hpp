@@ -43,6 +43,7 @@
 // C): lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and, in element r,
 // C[4 r + l / 16][l % 16]. Of the 4 x 4 one, with block b = l / 4 % 4: A_b[l %
 // 4][l / 16], B_b[l / 16][l % 4], C_b[l / 16][l % 4].
+#include <climits>
 #include <cmath>
 
 #include "dev_layout.hpp"
@@ -692,7 +693,7 @@ __device__ __forceinline__ bool deposit_synthesis(double kappa, int M, const dou
 
 // Whether the deposit of n particles on Mg nodes with one concentration tries
 // the moments first (double form; a concentration whose series fits the
-// narrow form, kappa <= 146): they cost about 20 us with the 3 launches that find
+// narrow form, kappa up to about 144.8): they cost about 20 us with the 3 launches that find
 // nothing to do, plus 12 ps per particle, against 0.65 ps per particle and
 // node (1,048,576 on 256 nodes: 28 us against 174; where the grid is refused
 // they come on top), so the line is drawn where the sum over the particles
@@ -709,6 +710,11 @@ __host__ __device__ inline bool deposit_tries_moments(int prec, int64_t n, int M
 // concave asinh is at least its integral over [0, m], the left-hand side.
 // Newton's method from above (the left-hand side is convex). rho_m grows
 // with kappa, so the order of the largest concentration serves a whole list.
+// The root is taken where it is a number that an int holds: below
+// kOrderKappaMin (rho_1 < kappa / 2) the order is 1, and no series is evaluated
+// above KDE_MAX_FOURIER_KAPPA, whose concentrations get the order INT_MAX,
+// longer than anything a caller compares it with (from 5.8e16 on the root
+// exceeds an int, from 1e34 it is NaN).
 inline double fourier_root(double k) {
   static const double lim = -std::log(kFourierTail);
   double m = std::sqrt(2.0 * lim * k) + 12.0;
@@ -718,8 +724,10 @@ inline double fourier_root(double k) {
   }
   return m;
 }
+constexpr double kOrderKappaMin = 1e-100;
 inline int fourier_order(double k) {
-  if (!(k > 0.0)) return 1;
+  if (!(k > kOrderKappaMin)) return 1;
+  if (k > KDE_MAX_FOURIER_KAPPA) return INT_MAX;
   const int m = int(std::ceil(fourier_root(k)));
   return m < 1 ? 1 : m;
 }

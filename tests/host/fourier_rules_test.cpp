@@ -1,0 +1,36 @@
+// The host's rules of the Fourier-moment routes (csrc/dev_fourier.hpp).
+#include <climits>
+#include <cmath>
+#include <cstdio>
+#include <limits>
+
+#include "dev_fourier.hpp"
+
+using namespace kde;
+
+static int failures = 0;
+#define EXPECT(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); ++failures; } } while (0)
+
+// The order of every concentration an entry point accepts: 1 for the
+// smallest, growing with kappa, and beyond the longest series never short.
+static void orders() {
+  for (double k : {0.0, 5e-324, 1e-300, 1e-160, 1e-101, 1e-99, 1e-20}) EXPECT(fourier_order(k) == 1);
+  int last = 1;
+  for (double k = 1e-20; k <= KDE_MAX_FOURIER_KAPPA; k *= 1.01) {
+    const int m = fourier_order(k);
+    EXPECT(m >= last && m < 20000);
+    last = m;
+  }
+  EXPECT(last > 9000);
+  for (double k : {1.0001e6, 1e7, 1e12, 1e15, 5e16, 6e16, 1e17, 1e18, 1e33, 1e34, 1e100, 1e300,
+                   std::numeric_limits<double>::max()})
+    EXPECT(fourier_order(k) == INT_MAX);
+  // where the narrow form ends
+  EXPECT(fourier_order(144.5) == kNarrowMax && fourier_order(145.0) == kNarrowMax + 1);
+}
+
+int main() {
+  orders();
+  if (failures == 0) std::printf("fourier rules ok\n");
+  return failures ? 1 : 0;
+}
