@@ -429,6 +429,15 @@ struct ScanSmem {
   double ptot[kBlock / 64];
   double red[kBlock / 64][3];
 };
+// Where the backward recurrence of a series to order M starts, and the doubles
+// that hold its values (from index 1) over a bracket that ends at kappa: the
+// refinement evaluates the end at exp(log(kappa)), which can exceed kappa by
+// a rounding unit, and where M^2 + 40 kappa is a perfect square the series
+// is one longer then.
+__host__ __device__ inline int series_length(int M, double kappa) {
+  return int(ceil(sqrt(double(M) * double(M) + 40.0 * kappa))) + 16;
+}
+__host__ __device__ inline int series_slots(int M, double kappa) { return series_length(M, kappa) + 2; }
 __host__ __device__ inline size_t series_lds(int M) { return size_t(2) * size_t(M + 1) * sizeof(double); }
 
 // The ratios r_m = I_m/I_{m-1} (m = 1..M) of one concentration into LDS by
@@ -450,7 +459,7 @@ __device__ __forceinline__ void series_ratios(double kappa, int M, double* __res
                                               int& hm, double& p) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   constexpr int kWaves = kBlock / 64;
-  const int Ms = int(ceil(sqrt(double(M) * double(M) + 40.0 * kappa))) + 16;
+  const int Ms = series_length(M, kappa);
   const int len = (Ms + kBlock - 1) / kBlock;
   lo = 1 + t * len;
   const int hi = min(Ms, (t + 1) * len);  // empty when lo > hi

@@ -313,14 +313,10 @@ __device__ __forceinline__ void mat_mul_norm(const double* a, const double* b, d
 // sums over m (a combined prefix scan). The composition is a reassociation
 // of the recurrence; its rounding grows with the tree depth instead of the
 // length of the chain.
-// `ratio` (LDS, series_length doubles) keeps each thread's ratios for its
+// `ratio` (LDS, series_slots doubles) keeps each thread's ratios for its
 // later walks (DER only); a scan ends at the last thread that has a run. The
 // two forms round the ratio's denominator once (DER) or twice; they always
 // have, and the refinement's last bits are kept (refine_moments_kernel).
-__host__ __device__ inline int series_length(int M, double kappa) {
-  return int(ceil(sqrt(double(M) * double(M) + 40.0 * kappa))) + 16;
-}
-
 template <bool DER>
 __device__ __forceinline__ void bessel_series(double kappa, int M, double* __restrict__ rho, double* __restrict__ d1,
                                               double* __restrict__ d2, double* __restrict__ ratio, BesselSmem& sm) {
@@ -798,7 +794,7 @@ __device__ Bracket make_bracket(const double* __restrict__ cvgrid, int B, const 
 // A bracket whose series has at most 256 modes (kappa* up to a few hundred): waves
 // 0, 1 and 2 evaluate its ends and the first iterate side by side, then wave 0
 // goes on alone; a longer one is evaluated by the whole workgroup, one point
-// after the other. Dynamic LDS: the ratios of the series (series_length + 1)
+// after the other. Dynamic LDS: the ratios of the series (series_slots)
 // and, where they fit (LDS), three arrays of M + 1.
 // 65,536 particles, 32 concentrations up to 1e4 (911 modes, the bracket's series
 // about 90): 49 us, 62 with a workgroup for each start and another for the steps.
@@ -827,7 +823,7 @@ __global__ void __launch_bounds__(kBlock) newton_kernel(const double* __restrict
     cv_best = cvgrid[bs];
     g_best = 0.0;
   } else {
-    const int modes = series_length(br.Mk, br.khi);
+    const int modes = series_slots(br.Mk, br.khi) - 1;  // the longest series of the bracket
     const bool alone = modes <= kBlock;
     if (alone && int(threadIdx.x) < br.Mk) {
       const double sr = S[2 * threadIdx.x], si = S[2 * threadIdx.x + 1];
@@ -1143,7 +1139,7 @@ kde_status kde_cv_refine(const kde_domain* dom, int64_t N, const void* x, int32_
   hipLaunchKernelGGL(refine_series_kernel, dim3(unsigned(B)), dim3(kBlock), sizeof(double) * size_t(M + 1), s,
                      (const double*)b.S, M, double(N), dom->L, kl, grid);
   KDE_CHECK_LAUNCH();
-  const size_t ratios = sizeof(double) * size_t(series_length(M, kappas_h[B - 1]) + 1);
+  const size_t ratios = sizeof(double) * size_t(series_slots(M, kappas_h[B - 1]));
   const size_t all = ratios + sizeof(double) * 3 * size_t(M + 1);
   if (all <= kNewtonLds) {
     KDE_RETURN_IF(check_lds(all + sizeof(BesselSmem)));

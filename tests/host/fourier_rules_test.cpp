@@ -29,8 +29,26 @@ static void orders() {
   EXPECT(fourier_order(144.5) == kNarrowMax && fourier_order(145.0) == kNarrowMax + 1);
 }
 
+// The refinement's arrays hold every series of a bracket, whose ends it
+// evaluates at exp(log(kappa)): a few rounding units about kappa.
+static void bracket_lengths() {
+  int longer = 0;
+  auto check = [&](double k) {
+    double up = std::exp(std::log(k));
+    for (int u = 0; u < 4; ++u) up = std::nextafter(up, INFINITY);
+    for (int M : {fourier_order(k), fourier_order(k) - 1}) {  // (the refinement's may be one less)
+      longer += series_length(M, up) > series_length(M, k);
+      EXPECT(series_length(M, up) + 1 <= series_slots(M, k));  // its indices 0 .. length
+    }
+  };
+  for (int k = 1; k <= 1000000; ++k) check(double(k));
+  for (double k = 1e-3; k <= 1e6; k *= 1.00037) check(k);
+  EXPECT(longer > 0);  // the case is met
+}
+
 int main() {
   orders();
+  bracket_lengths();
   if (failures == 0) std::printf("fourier rules ok\n");
   return failures ? 1 : 0;
 }
