@@ -12,19 +12,23 @@
 // cell pairs through
 //   Q_m(e) = sum over the band's pairs of (v - u)^m,  m = 0..3,
 // which follow from the cells' centred moments sum (u - 1/2)^k and do not
-// depend on the width. A band takes the polynomial that holds at its left end
-// e - 1; a knot p inside it adds, per particle, the power (D - p)^3 (and (D -
-// p) for the triangle) of the partners beyond it: those of part of one cell
-// and of at most one whole cell, from the moments of the sorted cell's
-// prefixes. Pairs within a cell (D has a kink at 0) give sum |v - u|^m the
-// same way. So a width costs a binary search and two cubics per particle and
-// C / 2 cubics, against every pair within its support (29 % of n^2 / 2 on
-// average over a list up to half the period).
+// depend on the width. A band that ends before the knot p1 = h takes the inner
+// polynomial (and 1 - u), one that ends before p2 = 2h the outer one, (2 -
+// u)^3 / 8; none reaches past 2h. A band that holds a knot adds, per particle,
+// the powers (p1 - D)^3 and (p1 - D), or (p2 - D)^3, of the partners before it:
+// those ahead of it in one sorted cell and those of at most one whole cell,
+// from the moments of the cell's prefixes. So a partner outside the support
+// enters no sum, a sum without partners is exactly 0, and none is negative.
+// (The image's power (D - p2)^3 is taken likewise beyond its knot, C - 2h.)
+// Pairs within a cell (D has a kink at 0) give sum |v - u|^m the same way. So a
+// width costs a binary search and two cubics per particle and C / 2 cubics,
+// against every pair within its support (29 % of n^2 / 2 on average over a list up
+// to half the period).
 // Widths with a knot below one cell (narrower than a cell, or near L / 2) sum
 // the bands of their knots pair by pair: there the moments would lose the
 // figures that the separation has. Offsets are exact (C is a power of two,
 // the sorted values are positions in cell units) and s <= 1 elsewhere, so the
-// sums are as accurate as the direct ones (4.8e-16 against 8.4e-16 of the
+// sums are as accurate as the direct ones (5.1e-16 against 8.4e-16 of the
 // pair kernel at 30,001 particles and 32 widths, against direct sums).
 //
 // Kernels: cell counts (global integer atomics), scatter (each workgroup
@@ -32,7 +36,7 @@
 // gave is replaced by the order of the values, so that every sum below has a
 // fixed order), prefix moments, the knots' terms, band sums, and per width
 // the cubics, the partial sums and the objective. What bounds it is launches
-// and latency: at 30,001 particles and 32 widths the scan takes 58 us (1600 us
+// and latency: at 30,001 particles and 32 widths the scan takes 59 us (1600 us
 // over the pairs), 20 us of it the knots' terms (chains of dependent loads),
 // the rest eight kernels of 2 to 8 us.
 #include <cmath>
@@ -232,7 +236,7 @@ __global__ void __launch_bounds__(64) tri_prefix_kernel(const double* __restrict
 // Where a knot p of particle i falls: in cell J = I + rel (mod C), at t from
 // the cell's start; [a, b) narrows to the first particle at or beyond it.
 struct KnotPlace {
-  int f, rel, J, a, b, hi;
+  int f, rel, J, a, b, lo, hi;
   double base, t;
 };
 __device__ __forceinline__ KnotPlace knot_place(double ui, int I, double p, int C, const int* __restrict__ start) {
@@ -243,28 +247,38 @@ __device__ __forceinline__ KnotPlace knot_place(double ui, int I, double p, int 
   if (k.rel > k.f) k.t -= 1.0;
   k.J = (I + k.rel) & (C - 1);
   k.base = double(k.J);
-  k.a = start[k.J];
+  k.a = k.lo = start[k.J];
   k.b = k.hi = start[k.J + 1];
   return k;
 }
-// Sums of (D - p) and (D - p)^3 over the partners beyond the knot in the
-// bands that hold it (e <= last): the rest of its own cell, and the next
-// band's whole cell.
-__device__ __forceinline__ void beyond_knot(const KnotPlace& k, bool between, int last, const Mom4& own, const Mom4& next,
+// Sums of (p - D) and (p - D)^3 over the partners before the knot in the bands
+// that hold it (e <= last): those ahead of it in its own cell, and all of the
+// cell of the band before (`prev`, that of band f). Each is a sum of positive
+// terms, so what rounding leaves below 0 is 0.
+__device__ __forceinline__ void before_knot(const KnotPlace& k, int last, const Mom4& own, const Mom4& prev,
                                             const Mom4* __restrict__ pre, double& s1, double& s3) {
   s1 = s3 = 0.0;
-  if (k.rel <= last && k.a < k.hi) {
-    const Mom4 m = own - pre[k.a];
-    s1 = shift1(m, k.t - 0.5);
-    s3 = shift3(m, k.t - 0.5);
+  if (k.rel <= last && k.a > k.lo) {
+    const Mom4 m = k.a < k.hi ? pre[k.a] : own;
+    s1 = fmax(0.0, -shift1(m, k.t - 0.5));
+    s3 = fmax(0.0, -shift3(m, k.t - 0.5));
   }
-  if (k.rel == k.f && between && k.f + 1 <= last) {
-    s1 += shift1(next, k.t - 1.5);
-    s3 += shift3(next, k.t - 1.5);
+  if (k.rel > k.f && k.f <= last) {
+    s1 += fmax(0.0, -shift1(prev, k.t + 0.5));
+    s3 += fmax(0.0, -shift3(prev, k.t + 0.5));
   }
 }
+// The sum of (D - p)^3 over those beyond it: the rest of its own cell, and the
+// next band's whole cell.
+__device__ __forceinline__ double beyond_knot(const KnotPlace& k, bool between, int last, const Mom4& own,
+                                              const Mom4& next, const Mom4* __restrict__ pre) {
+  double s3 = 0.0;
+  if (k.rel <= last && k.a < k.hi) s3 = fmax(0.0, shift3(own - pre[k.a], k.t - 0.5));
+  if (k.rel == k.f && between && k.f + 1 <= last) s3 += fmax(0.0, shift3(next, k.t - 1.5));
+  return s3;
+}
 
-// Slot y of the grid: y < B, width y's terms beyond its knots (or its knots'
+// Slot y of the grid: y < B, width y's terms at its knots (or its knots'
 // bands pair by pair); y = B, sum |v - u|^m over the pairs within cells.
 // One particle per thread (two or four: 24 and 33 us against 20); a slot's partial sums go to part[(y gridDim.x + x) 4
 // ..]. A non-finite position makes every sum NaN.
@@ -281,11 +295,14 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
       const double zi = z[i];
       const int I = cell_index(zi);
       const double d = (zi - double(I)) - 0.5;
-      const Mom4 m = mu[I] - pre[i] - Mom4{1.0, d, d * d, d * d * d};  // the particles after this one
-      v[0] += m.m0 + 0.0 * zi;  // NaN for a non-finite position
-      v[1] += shift1(m, d);
-      v[2] += shift2(m, d);
-      v[3] += shift3(m, d);
+      v[0] += 0.0 * zi;  // NaN for a non-finite position
+      if (int(i) + 1 < start[I + 1]) {
+        const Mom4 m = mu[I] - pre[i] - Mom4{1.0, d, d * d, d * d * d};  // the particles after this one
+        v[0] += m.m0;
+        v[1] += shift1(m, d);
+        v[2] += shift2(m, d);
+        v[3] += shift3(m, d);
+      }
     }
   } else {
     const TriKnots k = tri_knots(W.h[slot], W.L, C);
@@ -298,8 +315,8 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
         const int I = cell_index(zi);
         const double ui = zi - double(I);
         KnotPlace g = knot_place(ui, I, k.p1, C, start), h = knot_place(ui, I, k.p2, C, start);
-        const Mom4 go = mu[g.J], gn = mu[(I + g.f + 1) & (C - 1)];
-        const Mom4 ho = mu[h.J], hn = mu[(I + h.f + 1) & (C - 1)];
+        const Mom4 go = mu[g.J], gp = mu[(I + g.f) & (C - 1)];
+        const Mom4 ho = mu[h.J], hp = mu[(I + h.f + (k.image ? 1 : 0)) & (C - 1)];
         while (g.a < g.b || h.a < h.b) {  // both searches at once: their loads overlap
           const int gm = (g.a + g.b) >> 1, hm = (h.a + h.b) >> 1;
           const double gz = g.a < g.b ? z[gm] : 0.0, hz = h.a < h.b ? z[hm] : 0.0;
@@ -313,8 +330,11 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
           }
         }
         double s1, s3, t1, t3;
-        beyond_knot(g, k.p1 > double(g.f), last, go, gn, pre, s1, s3);
-        beyond_knot(h, k.p2 > double(h.f), last, ho, hn, pre, t1, t3);
+        before_knot(g, last, go, gp, pre, s1, s3);
+        if (k.image)
+          t3 = beyond_knot(h, k.p2 > double(h.f), last, ho, hp, pre);
+        else
+          before_knot(h, last, ho, hp, pre, t1, t3);
         a1 += s1 + 0.0 * zi;
         a3 += s3;
         b3 += t3;
@@ -439,13 +459,13 @@ __global__ void __launch_bounds__(kBlock) tri_objective_kernel(const double* __r
     const double w = 2 * e == C ? 0.5 : 1.0, left = double(e - 1);
     const double q[4] = {w * Q[4 * e], w * Q[4 * e + 1], w * Q[4 * e + 2], w * Q[4 * e + 3]};
     const double u0 = double(e) * k.s;
-    if (left < k.p1) {
-      v[0] += band_inner(u0, k.s, q);
-      v[1] += fma(1.0 - u0, q[0], -k.s * q[1]);
-    } else if (left < 2.0 * k.p1) {
-      v[0] += band_outer(u0, k.s, q);
+    if (left + 2.0 <= k.p1) {
+      v[0] += fmax(0.0, band_inner(u0, k.s, q));
+      v[1] += fmax(0.0, fma(1.0 - u0, q[0], -k.s * q[1]));
+    } else if (k.image || left + 2.0 <= k.p2) {
+      v[0] += fmax(0.0, band_outer(u0, k.s, q));  // (less the power where it holds p1)
     }
-    if (k.image && left >= k.p2) v[0] += band_outer(double(C - e) * k.s, -k.s, q);
+    if (k.image && left >= k.p2) v[0] += fmax(0.0, band_outer(double(C - e) * k.s, -k.s, q));
   }
   for (int64_t r = threadIdx.x; r < blocks; r += kBlock) {
     const double* p = part + (int64_t(b) * blocks + r) * 4;
