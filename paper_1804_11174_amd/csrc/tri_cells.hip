@@ -36,9 +36,10 @@
 // gave is replaced by the order of the values, so that every sum below has a
 // fixed order), prefix moments, the knots' terms, band sums, and per width
 // the cubics, the partial sums and the objective. What bounds it is launches
-// and latency: at 30,001 particles and 32 widths the scan takes 59 us (1600 us
+// and latency: at 30,001 particles and 32 widths the scan takes 56 us (1600 us
 // over the pairs), 20 us of it the knots' terms (chains of dependent loads),
 // the rest eight kernels of 2 to 8 us.
+#include <algorithm>
 #include <cmath>
 
 #include "dev_layout.hpp"
@@ -49,15 +50,20 @@ namespace kde {
 
 namespace {
 
-constexpr int kTriMinCells = 256, kTriMaxCells = 2048;  // 4 moments of 2048 cells: 64 KB of LDS
+constexpr int kTriMinCells = 8, kTriMaxCells = 2048;  // 4 moments of 2048 cells: 64 KB of LDS
+constexpr int64_t kTriMany = int64_t(1) << 26;        // particles from which the knots' terms take kTriPer per thread
+constexpr int kTriPer = 4;
 constexpr int kBandBlock = 256;
 constexpr int kBands = kBandBlock / 64;                 // bands per workgroup, one per wave
 
-// About 16 particles per cell up to the limit: ranking within a cell costs
-// its count per particle, the band sums C^2 / 2 products.
+// About 16 particles per cell up to the limit, fewer for small samples: ranking
+// within a cell costs its count per particle, the band sums C^2 / 2
+// products. Up to 2048 particles 8 to 16 per cell, so that what the cells take
+// fits the pair layout's workspace (carve_tri).
 int tri_cells(int64_t n) {
-  int c = kTriMinCells;
+  int c = 256;
   while (c < kTriMaxCells && int64_t(c) * 16 < n) c *= 2;
+  while (c > kTriMinCells && int64_t(c) * 8 >= n) c /= 2;
   return c;
 }
 
@@ -133,9 +139,10 @@ __global__ void __launch_bounds__(kBlock) tri_scatter_kernel(const double* __res
   const int r = i < n ? rank[i] : 0;
   for (int c = t; c < C; c += kBlock) base[c] = count[c];
   __syncthreads();
-  const int per = C / kBlock;
+  const int per = C > kBlock ? C / kBlock : 1;
+  const int cells_of = t * per < C ? per : 0;
   int own = 0;
-  for (int k = 0; k < per; ++k) own += base[t * per + k];
+  for (int k = 0; k < cells_of; ++k) own += base[t * per + k];
   int incl = own;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -146,7 +153,7 @@ __global__ void __launch_bounds__(kBlock) tri_scatter_kernel(const double* __res
   __syncthreads();
   int run = incl - own;
   for (int k = 0; k < w; ++k) run += tot[k];
-  for (int k = 0; k < per; ++k) {
+  for (int k = 0; k < cells_of; ++k) {
     const int v = base[t * per + k];
     base[t * per + k] = run;
     run += v;
@@ -212,26 +219,64 @@ __device__ __forceinline__ double shift3(const Mom4& m, double t) {
   return fma(t, fma(t, fma(-t, m.m0, 3.0 * m.m1), -3.0 * m.m2), m.m3);
 }
 
-// Thread per cell: the moments of the particles before each one in its cell
-// (pre) and of the whole cell (mu).
-__global__ void __launch_bounds__(64) tri_prefix_kernel(const double* __restrict__ z, const int* __restrict__ start,
-                                                       int C, Mom4* __restrict__ pre, Mom4* __restrict__ mu) {
-  const int c = blockIdx.x * 64 + threadIdx.x;
+struct Mom3 {
+  double m1, m2, m3;
+};
+// Adds a particle at offset d.
+__device__ __forceinline__ void mom_add(Mom3& m, double d) {
+  const double d2 = d * d;
+  m.m1 += d;
+  m.m2 += d2;
+  m.m3 = fma(d2, d, m.m3);
+}
+
+// Wave per cell: the moments of the particles before each even place of the
+// sorted array in its cell (pre[place / 2], without the count, which the places
+// give), and of the whole cell (mu). A lane takes two places, and the lanes'
+// sums meet in a shuffle scan: one load and one scan per 128 particles, where a
+// thread per cell waits for each of its particles in turn (15,000 in one cell: ms).
+__global__ void __launch_bounds__(kBlock) tri_prefix_kernel(const double* __restrict__ z,
+                                                           const int* __restrict__ start, int C,
+                                                           Mom3* __restrict__ pre, Mom4* __restrict__ mu) {
+  const int lane = threadIdx.x & 63, c = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   if (c >= C) return;
   const double mid = double(c) + 0.5;
-  Mom4 m{0.0, 0.0, 0.0, 0.0};
-  const int hi = start[c + 1];
-#pragma unroll 4
-  for (int p = start[c]; p < hi; ++p) {
-    pre[p] = m;
-    const double d = z[p] - mid, d2 = d * d;
-    m.m0 += 1.0;
-    m.m1 += d;
-    m.m2 += d2;
-    m.m3 = fma(d2, d, m.m3);
+  const int lo = start[c], hi = start[c + 1];
+  Mom3 carry{0.0, 0.0, 0.0};
+  for (int base = lo & ~1; base < hi; base += 128) {
+    const int e = base + 2 * lane;
+    Mom3 m{0.0, 0.0, 0.0};
+    if (e >= lo && e < hi) mom_add(m, z[e] - mid);
+    if (e + 1 < hi) mom_add(m, z[e + 1] - mid);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const Mom3 o{__shfl_up(m.m1, d, 64), __shfl_up(m.m2, d, 64), __shfl_up(m.m3, d, 64)};
+      if (lane >= d) m = Mom3{o.m1 + m.m1, o.m2 + m.m2, o.m3 + m.m3};
+    }
+    Mom3 b{__shfl_up(m.m1, 1, 64), __shfl_up(m.m2, 1, 64), __shfl_up(m.m3, 1, 64)};
+    if (lane == 0) b = Mom3{0.0, 0.0, 0.0};
+    if (e >= lo && e < hi) pre[e >> 1] = Mom3{carry.m1 + b.m1, carry.m2 + b.m2, carry.m3 + b.m3};
+    carry.m1 += __shfl(m.m1, 63, 64);
+    carry.m2 += __shfl(m.m2, 63, 64);
+    carry.m3 += __shfl(m.m3, 63, 64);
   }
-  mu[c] = m;
+  if (lane == 0) mu[c] = Mom4{double(hi - lo), carry.m1, carry.m2, carry.m3};
 }
+// The moments of the particles [lo, a) of the cell that starts at lo, whose
+// middle is mid, for a place lo < a of the cell (elsewhere a value that means
+// nothing). Its loads are made at once and stay in the arrays.
+struct Prefixes {
+  const double* z;
+  const Mom3* pre;
+  int last;  // n - 1
+  __device__ __forceinline__ Mom4 of(int a, int lo, double mid) const {
+    a = min(a, last);
+    Mom3 m = pre[a >> 1];
+    const double before = z[max(a - 1, 0)];
+    mom_add(m, (a & 1) ? before - mid : 0.0);
+    return Mom4{double(a - lo), m.m1, m.m2, m.m3};
+  }
+};
 
 // Where a knot p of particle i falls: in cell J = I + rel (mod C), at t from
 // the cell's start; [a, b) narrows to the first particle at or beyond it.
@@ -256,10 +301,10 @@ __device__ __forceinline__ KnotPlace knot_place(double ui, int I, double p, int 
 // cell of the band before (`prev`, that of band f). Each is a sum of positive
 // terms, so what rounding leaves below 0 is 0.
 __device__ __forceinline__ void before_knot(const KnotPlace& k, int last, const Mom4& own, const Mom4& prev,
-                                            const Mom4* __restrict__ pre, double& s1, double& s3) {
+                                            const Prefixes& pre, double& s1, double& s3) {
   s1 = s3 = 0.0;
   if (k.rel <= last && k.a > k.lo) {
-    const Mom4 m = k.a < k.hi ? pre[k.a] : own;
+    const Mom4 m = k.a < k.hi ? pre.of(k.a, k.lo, k.base + 0.5) : own;
     s1 = fmax(0.0, -shift1(m, k.t - 0.5));
     s3 = fmax(0.0, -shift3(m, k.t - 0.5));
   }
@@ -271,33 +316,40 @@ __device__ __forceinline__ void before_knot(const KnotPlace& k, int last, const 
 // The sum of (D - p)^3 over those beyond it: the rest of its own cell, and the
 // next band's whole cell.
 __device__ __forceinline__ double beyond_knot(const KnotPlace& k, bool between, int last, const Mom4& own,
-                                              const Mom4& next, const Mom4* __restrict__ pre) {
+                                              const Mom4& next, const Prefixes& pre) {
   double s3 = 0.0;
-  if (k.rel <= last && k.a < k.hi) s3 = fmax(0.0, shift3(own - pre[k.a], k.t - 0.5));
+  if (k.rel <= last && k.a < k.hi) 
+    s3 = fmax(0.0, shift3(k.a > k.lo ? own - pre.of(k.a, k.lo, k.base + 0.5) : own, k.t - 0.5));
   if (k.rel == k.f && between && k.f + 1 <= last) s3 += fmax(0.0, shift3(next, k.t - 1.5));
   return s3;
 }
 
 // Slot y of the grid: y < B, width y's terms at its knots (or its knots'
 // bands pair by pair); y = B, sum |v - u|^m over the pairs within cells.
-// One particle per thread (two or four: 24 and 33 us against 20); a slot's partial sums go to part[(y gridDim.x + x) 4
-// ..]. A non-finite position makes every sum NaN.
+// P = 1 particle per thread (two or four: 24 and 33 us against 20), kTriPer where
+// there are so many that their partial sums would need more room; a slot's partial sums go to part[(y gridDim.x + x) 2 ..], four
+// of them for y = B. A non-finite position makes every sum NaN.
+template <int P>
 __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restrict__ z, int64_t n,
                                                           const int* __restrict__ start,
-                                                          const Mom4* __restrict__ pre, const Mom4* __restrict__ mu,
-                                                          TriWidths W, double* __restrict__ part) {
+                                                          const Mom3* __restrict__ pre_of,
+                                                          const Mom4* __restrict__ mu, TriWidths W, double* __restrict__ part) {
   __shared__ double red[kBlock / 64][4];
+  const Prefixes pre{z, pre_of, int(n - 1)};
   const int C = W.C, slot = W.B - int(blockIdx.y);  // the widest widths, which may be summed pair by pair, start first
   double v[4] = {0.0, 0.0, 0.0, 0.0};
-  const int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x;
+  const int64_t first = int64_t(blockIdx.x) * (P * kBlock) + threadIdx.x;
   if (slot == W.B) {
-    if (i < n) {
+    for (int64_t i = first, q = 0; q < P && i < n; ++q, i += kBlock) {
       const double zi = z[i];
       const int I = cell_index(zi);
       const double d = (zi - double(I)) - 0.5;
       v[0] += 0.0 * zi;  // NaN for a non-finite position
       if (int(i) + 1 < start[I + 1]) {
-        const Mom4 m = mu[I] - pre[i] - Mom4{1.0, d, d * d, d * d * d};  // the particles after this one
+        // the particles after this one
+        const int lo = start[I];
+        Mom4 m = mu[I] - Mom4{1.0, d, d * d, d * d * d};
+        if (int(i) > lo) m = m - pre.of(int(i), lo, double(I) + 0.5);
         v[0] += m.m0;
         v[1] += shift1(m, d);
         v[2] += shift2(m, d);
@@ -310,7 +362,7 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
     if (!k.direct) {
       const int last = k.half ? half - 1 : half;
       double a1 = 0.0, a3 = 0.0, b3 = 0.0;
-      if (i < n) {
+      for (int64_t i = first, q = 0; q < P && i < n; ++q, i += kBlock) {
         const double zi = z[i];
         const int I = cell_index(zi);
         const double ui = zi - double(I);
@@ -355,7 +407,7 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
         v[0] += kb;
         v[1] += c;
       };
-      if (i < n) {
+      for (int64_t i = first, q = 0; q < P && i < n; ++q, i += kBlock) {
         const double zi = z[i];
         const int I = cell_index(zi);
         const double ui = zi - double(I);
@@ -389,9 +441,14 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
   }
   sums_of_block<4, kBlock / 64>(v, red);
   if (threadIdx.x == 0) {
-    double* o = part + (int64_t(slot) * gridDim.x + blockIdx.x) * 4;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = v[k];
+    const bool within = slot == W.B;
+    double* o = part + int64_t(slot) * gridDim.x * 2 + int64_t(blockIdx.x) * (within ? 4 : 2);
+    o[0] = v[0];
+    o[1] = v[1];
+    if (within) {
+      o[2] = v[2];
+      o[3] = v[3];
+    }
   }
 }
 
@@ -468,14 +525,14 @@ __global__ void __launch_bounds__(kBlock) tri_objective_kernel(const double* __r
     if (k.image && left >= k.p2) v[0] += fmax(0.0, band_outer(double(C - e) * k.s, -k.s, q));
   }
   for (int64_t r = threadIdx.x; r < blocks; r += kBlock) {
-    const double* p = part + (int64_t(b) * blocks + r) * 4;
+    const double* p = part + (int64_t(b) * blocks + r) * 2;
     v[0] += p[0];
     v[1] += p[1];
   }
   if (!pair_band(k, 0, C)) {  // pairs within a cell: u = |v - u| s < 1, no image
     const double s = k.s, s2 = s * s;
     for (int64_t r = threadIdx.x; r < blocks; r += kBlock) {
-      const double* p = part + (int64_t(B) * blocks + r) * 4;
+      const double* p = part + int64_t(B) * blocks * 2 + r * 4;
       v[0] += 0.125 * fma(3.0 * s2 * s, p[3], fma(-6.0 * s2, p[2], 4.0 * p[0]));
       v[1] += fma(-s, p[1], p[0]);
     }
@@ -506,32 +563,43 @@ __global__ void __launch_bounds__(kBlock) tri_objective_kernel(const double* __r
   if (threadIdx.x == 0) *argmin = first_min(vals, B);
 }
 
+// The arrays of a scan in one block of doubles. They fit the pair layout of the
+// same (n, B), whose size the call asks for: the sorted values, and a place of 12
+// bytes per particle that holds the unsorted ones with their ranks first, the
+// prefix moments then and the band sums last; the counts lie where the cells'
+// moments follow.
 struct TriBufs {
-  int* count;       // C
-  int* start;       // C + 1
-  int* rank;        // n
-  double* cells;    // n
-  double* sorted;   // n
-  Mom4* pre;        // n
   Mom4* mu;         // C
-  double* Q;        // 4 (C / 2 + 1)
-  double* part;     // (B + 1) x blocks x 4
+  double* sorted;   // n
+  double* cells;    // n
+  int* rank;        // n
+  Mom3* pre;        // ceil(n / 2): over cells and rank
+  double* Q;        // 4 (C / 2 + 1): over pre
+  int* count;       // C: over mu
+  double* part;     // B x blocks x 2, then blocks x 4
+  int* start;       // C + 1
   unsigned int* done;
 };
 
+int64_t tri_blocks(int64_t n) { return ceil_div(n, (n >= kTriMany ? kTriPer : 1) * kBlock); }
+
 TriBufs carve_tri(Carver& c, int64_t n, int B) {
-  const int C = tri_cells(n);
-  TriBufs b;
-  b.count = c.take<int>(size_t(C));
-  b.start = c.take<int>(size_t(C) + 1);
-  b.rank = c.take<int>(size_t(n));
-  b.cells = c.take<double>(size_t(n));
-  b.sorted = c.take<double>(size_t(n));
-  b.pre = c.take<Mom4>(size_t(n));
-  b.mu = c.take<Mom4>(size_t(C));
-  b.Q = c.take<double>(size_t(4) * (C / 2 + 1));
-  b.part = c.take<double>(size_t(B + 1) * size_t(ceil_div(n, kBlock)) * 4);
-  b.done = c.take<unsigned int>(1);
+  const size_t C = size_t(tri_cells(n)), N = size_t(n);
+  const size_t part = size_t(tri_blocks(n)) * (2 * size_t(B) + 4), ints = (C + 2 + 1) / 2;
+  const size_t shared = std::max(3 * ((N + 1) / 2), 4 * (C / 2 + 1));
+  double* base = c.take<double>(4 * C + N + shared + part + ints);
+  TriBufs b{};
+  if (!base) return b;  // only the size is asked for
+  b.mu = reinterpret_cast<Mom4*>(base);
+  b.count = reinterpret_cast<int*>(base);
+  b.sorted = base + 4 * C;
+  b.cells = b.sorted + N;
+  b.rank = reinterpret_cast<int*>(b.cells + N);
+  b.pre = reinterpret_cast<Mom3*>(b.cells);
+  b.Q = b.cells;
+  b.part = b.cells + shared;
+  b.start = reinterpret_cast<int*>(b.part + part);
+  b.done = reinterpret_cast<unsigned int*>(b.start + C + 1);
   return b;
 }
 
@@ -556,7 +624,7 @@ kde_status tri_scan_f64(const kde_domain* dom, int64_t n, const double* x, int B
   for (int k = 0; k < B; ++k) W.h[k] = widths[k];
   const double reach = 2.0 * widths[B - 1] / dom->L * double(C) + 2.0;  // bands beyond it are zero for every width
   W.emax = reach < double(C / 2) ? int(reach) : C / 2;
-  const int64_t blocks = ceil_div(n, kBlock);
+  const int64_t blocks = tri_blocks(n);
   const dim3 per_particle{unsigned(ceil_div(n, kBlock))}, block{unsigned(kBlock)};
   TimedLaunch timed(KDE_KERNEL_CV_PAIRS, s);
   hipExtLaunchKernelGGL(tri_zero_kernel, dim3(unsigned(ceil_div(C, kBlock))), block, 0, s, timed.start(), nullptr, 0,
@@ -570,11 +638,12 @@ kde_status tri_scan_f64(const kde_domain* dom, int64_t n, const double* x, int B
   hipLaunchKernelGGL(tri_rank_kernel, per_particle, block, 0, s, (const double*)b.cells, n, (const int*)b.start,
                      b.sorted);
   KDE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(tri_prefix_kernel, dim3(unsigned(ceil_div(C, 64))), dim3(64), 0, s, (const double*)b.sorted,
+  hipLaunchKernelGGL(tri_prefix_kernel, dim3(unsigned(ceil_div(C, kBlock / 64))), block, 0, s, (const double*)b.sorted,
                      (const int*)b.start, C, b.pre, b.mu);
   KDE_CHECK_LAUNCH();
-  hipLaunchKernelGGL(tri_knots_kernel, dim3(unsigned(blocks), unsigned(B + 1)), block, 0, s, (const double*)b.sorted,
-                     n, (const int*)b.start, (const Mom4*)b.pre, (const Mom4*)b.mu, W, b.part);
+  const auto knots = n >= kTriMany ? tri_knots_kernel<kTriPer> : tri_knots_kernel<1>;
+  hipLaunchKernelGGL(knots, dim3(unsigned(blocks), unsigned(B + 1)), block, 0, s, (const double*)b.sorted, n,
+                     (const int*)b.start, (const Mom3*)b.pre, (const Mom4*)b.mu, W, b.part);
   KDE_CHECK_LAUNCH();
   hipLaunchKernelGGL(tri_bands_kernel, dim3(unsigned(ceil_div(W.emax, kBands))), dim3(kBandBlock),
                      size_t(C) * sizeof(Mom4), s, (const Mom4*)b.mu, C, W.emax, b.Q);
