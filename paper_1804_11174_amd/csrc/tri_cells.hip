@@ -24,9 +24,9 @@
 // width costs a binary search and two cubics per particle and C / 2 cubics,
 // against every pair within its support (29 % of n^2 / 2 on average over a list up
 // to half the period).
-// Widths with a knot below one cell (narrower than a cell, or near L / 2) sum
-// the bands of their knots pair by pair: there the moments would lose the
-// figures that the separation has. Offsets are exact (C is a power of two,
+// Widths narrower than a cell walk each particle's partners within the support
+// (they follow it in the sorted array) pair by pair: there the moments would
+// lose the figures that the separation has. Offsets are exact (C is a power of two,
 // the sorted values are positions in cell units) and s <= 1 elsewhere, so the
 // sums are as accurate as the direct ones (5.1e-16 against 8.4e-16 of the
 // pair kernel at 30,001 particles and 32 widths, against direct sums).
@@ -36,9 +36,12 @@
 // gave is replaced by the order of the values, so that every sum below has a
 // fixed order), prefix moments, the knots' terms, band sums, and per width
 // the cubics, the partial sums and the objective. What bounds it is launches
-// and latency: at 30,001 particles and 32 widths the scan takes 56 us (1600 us
+// and latency: at 30,001 particles and 32 widths the scan takes 54 us (1600 us
 // over the pairs), 20 us of it the knots' terms (chains of dependent loads),
-// the rest eight kernels of 2 to 8 us.
+// the rest seven kernels of 2 to 8 us. A sample within a few cells pays for its
+// ranks and, at widths narrower than a cell, for its pairs: 30,001 within 1e-4 L
+// 1.6 ms over 32 widths from L / 1024 (4.8 over the pairs), from L / 16384, six of
+// them narrower than a cell, 6.1 (4.8).
 #include <algorithm>
 #include <cmath>
 
@@ -78,7 +81,7 @@ struct TriWidths {
 struct TriKnots {
   double s, p1, p2;
   bool image;   // h > L / 4: the spline reaches its periodic image
-  bool direct;  // a knot below one cell: the knots' bands pair by pair
+  bool direct;  // narrower than a cell: pair by pair
   bool half;    // a knot in the last band (e = C / 2), which also holds its mirror image: that band pair by pair
 };
 
@@ -90,17 +93,10 @@ __device__ __forceinline__ TriKnots tri_knots(double h, double L, int C) {
   k.s = 1.0 / k.p1;
   k.image = g > 0.25;
   if (k.p2 > 0.5 * double(C)) k.p2 = fmax(double(C) - k.p2, 0.0);
-  k.direct = k.p1 < 1.0 || k.p2 < 1.0;
+  k.direct = k.p1 < 1.0;
   k.half = fmax(k.p1, k.p2) > double(C / 2 - 1);
   return k;
 }
-// Whether band e holds knot p strictly inside (e - 1, e + 1).
-__device__ __forceinline__ bool band_holds(double p, int e) { return double(e - 1) < p && p < double(e + 1); }
-// Whether width k sums band e pair by pair.
-__device__ __forceinline__ bool pair_band(const TriKnots& k, int e, int C) {
-  return k.direct ? (band_holds(k.p1, e) || band_holds(k.p2, e)) : (k.half && 2 * e == C);
-}
-
 // Position in cell units, in [0, C) (NaN for a non-finite one), and its cell.
 __device__ __forceinline__ double cell_position(double x, double L, int C) {
   double z = (wrap_d(x, L) / L) * double(C);
@@ -178,6 +174,7 @@ __global__ void __launch_bounds__(kBlock) tri_rank_kernel(const double* __restri
   const int lo = start[c], hi = start[c + 1];
   const uint64_t key = uint64_t(__double_as_longlong(z));
   int r = 0;
+#pragma unroll 8
   for (int j = lo; j < hi; ++j) {
     const uint64_t k = uint64_t(__double_as_longlong(cells[j]));
     r += (k < key || (k == key && j < int(i))) ? 1 : 0;
@@ -324,11 +321,12 @@ __device__ __forceinline__ double beyond_knot(const KnotPlace& k, bool between, 
   return s3;
 }
 
-// Slot y of the grid: y < B, width y's terms at its knots (or its knots'
-// bands pair by pair); y = B, sum |v - u|^m over the pairs within cells.
-// P = 1 particle per thread (two or four: 24 and 33 us against 20), kTriPer where
-// there are so many that their partial sums would need more room; a slot's partial sums go to part[(y gridDim.x + x) 2 ..], four
-// of them for y = B. A non-finite position makes every sum NaN.
+// Slot y of the grid: y < B, width y's terms at its knots (or all of its
+// pairs); y = B, sum |v - u|^m over the pairs within cells. P = 1 particle per
+// thread (two or four: 24 and 33 us against 20), kTriPer where there are so many
+// that their partial sums would need more room. A slot's partial sums go to
+// part[(y gridDim.x + x) 2 ..], four of them for y = B. A non-finite position makes
+// every sum NaN.
 template <int P>
 __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restrict__ z, int64_t n,
                                                           const int* __restrict__ start,
@@ -336,7 +334,7 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
                                                           const Mom4* __restrict__ mu, TriWidths W, double* __restrict__ part) {
   __shared__ double red[kBlock / 64][4];
   const Prefixes pre{z, pre_of, int(n - 1)};
-  const int C = W.C, slot = W.B - int(blockIdx.y);  // the widest widths, which may be summed pair by pair, start first
+  const int C = W.C, slot = W.B - int(blockIdx.y);  // the widest widths, the longest (but for the narrowest), start first
   double v[4] = {0.0, 0.0, 0.0, 0.0};
   const int64_t first = int64_t(blockIdx.x) * (P * kBlock) + threadIdx.x;
   if (slot == W.B) {
@@ -409,30 +407,35 @@ __global__ void __launch_bounds__(kBlock) tri_knots_kernel(const double* __restr
       };
       for (int64_t i = first, q = 0; q < P && i < n; ++q, i += kBlock) {
         const double zi = z[i];
-        const int I = cell_index(zi);
-        const double ui = zi - double(I);
-        auto band = [&](int e) {
-          if (e == 0) {
-            for (int j = int(i) + 1; j < start[I + 1]; ++j) term(z[j] - zi);
-          } else if (!(e == half && I >= half)) {  // at half the period each pair once
-            const int J = (I + e) & (C - 1);
-            const double off = double(e) - ui - double(J);
-            for (int j = start[J]; j < start[J + 1]; ++j) {
-              const double D = z[j] + off;
-              term(fmin(D, period - D));
-            }
-          }
-        };
         if (k.direct) {
-          const int f1 = int(k.p1), f2 = int(k.p2);
-          for (int r = 0; r < 4; ++r) {
-            const int e = (r < 2 ? f1 : f2) + (r & 1);
-            if (e > half || !pair_band(k, e, C)) continue;
-            if (r >= 2 && (e == f1 || (e == f1 + 1 && pair_band(k, f1 + 1, C)))) continue;  // done with p1
-            band(e);
+          // the ones behind it, then those of the next period's start: four at a
+          // time with the next four in flight (a term beyond the support is 0)
+          auto walk = [&](int from, int to, double off) {
+            double cur[4], nxt[4];
+            auto load = [&](int j, double (&v)[4]) {
+#pragma unroll
+              for (int u = 0; u < 4; ++u) v[u] = z[min(j + u, to - 1)];
+            };
+            if (from >= to) return;
+            load(from, cur);
+            for (int j = from;; j += 4) {
+              load(min(j + 4, to - 1), nxt);
+#pragma unroll
+              for (int u = 0; u < 4; ++u) term(j + u < to ? cur[u] + off : period);
+              if (j + 4 >= to || !(cur[3] + off < k.p2)) break;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+            }
+          };
+          walk(int(i) + 1, int(n), -zi);
+          if (zi + k.p2 > period) walk(0, int(i), period - zi);
+        } else if (cell_index(zi) < half) {  // at half the period each pair once
+          const int J = cell_index(zi) + half;
+          const double off = double(half) - (zi - double(J - half)) - double(J);
+          for (int j = start[J]; j < start[J + 1]; ++j) {
+            const double D = z[j] + off;
+            term(fmin(D, period - D));
           }
-        } else {
-          band(half);
         }
         v[0] += 0.0 * zi;
         v[1] += 0.0 * zi;
@@ -511,8 +514,8 @@ __global__ void __launch_bounds__(kBlock) tri_objective_kernel(const double* __r
   const int b = blockIdx.x, B = W.B, C = W.C;
   const TriKnots k = tri_knots(W.h[b], W.L, C);
   double v[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int e = 1 + threadIdx.x; e <= W.emax; e += kBlock) {
-    if (pair_band(k, e, C)) continue;
+  for (int e = 1 + threadIdx.x; e <= W.emax && !k.direct; e += kBlock) {
+    if (k.half && 2 * e == C) continue;
     const double w = 2 * e == C ? 0.5 : 1.0, left = double(e - 1);
     const double q[4] = {w * Q[4 * e], w * Q[4 * e + 1], w * Q[4 * e + 2], w * Q[4 * e + 3]};
     const double u0 = double(e) * k.s;
@@ -529,7 +532,7 @@ __global__ void __launch_bounds__(kBlock) tri_objective_kernel(const double* __r
     v[0] += p[0];
     v[1] += p[1];
   }
-  if (!pair_band(k, 0, C)) {  // pairs within a cell: u = |v - u| s < 1, no image
+  if (!k.direct) {  // pairs within a cell: u = |v - u| s <= 1 (their image is a knot's term)
     const double s = k.s, s2 = s * s;
     for (int64_t r = threadIdx.x; r < blocks; r += kBlock) {
       const double* p = part + int64_t(B) * blocks * 2 + r * 4;
