@@ -73,7 +73,7 @@ struct SetDev {
   double* ad_sums;    // 2
   void* kappa_i;      // N (prec)
   double* rho;        // M
-  double* cv;         // B
+  double* cv;         // B (NULL: not asked for, and none taken through the moments)
   double* kstar;      // 1
   int* kbest;         // 1: its index in the list
   int pil_mom;        // the pilot tries the moments first (deposit_tries_moments)
@@ -94,7 +94,6 @@ struct BatchArgs {
   const int64_t* prefix;  // PF_COUNT x (nsets + 1)
   unsigned long long* counters;
   uint32_t* statuses;     // nsets numeric status words, in the caller's set order
-  unsigned int* done;     // nsets counters of finished series units, then nsets pil_ok words
   int nsets;
   int B;
   double alpha;
@@ -135,13 +134,12 @@ __device__ __forceinline__ int64_t claim(unsigned long long* counter, int64_t* s
   return uni64(v);
 }
 
-__global__ void __launch_bounds__(kBlock) batch_zero_kernel(unsigned long long* counters, uint32_t* statuses,
-                                                            unsigned int* done, int nsets) {
-  if (threadIdx.x < kCounters) counters[threadIdx.x] = 0ull;
-  for (int k = threadIdx.x; k < nsets; k += kBlock) {
-    statuses[k] = 0u;
-    done[k] = 0u;
-    done[nsets + k] = 0u;
+__global__ void __launch_bounds__(kBlock) batch_zero_kernel(BatchArgs a) {
+  if (threadIdx.x < kCounters) a.counters[threadIdx.x] = 0ull;
+  for (int k = threadIdx.x; k < a.nsets; k += kBlock) {
+    a.statuses[k] = 0u;
+    *a.sets[k].done = 0u;
+    *a.sets[k].pil_ok = 0u;
   }
 }
 
@@ -161,6 +159,7 @@ __global__ void __launch_bounds__(kMomBlock) batch_moments_kernel(BatchArgs a) {
   MomentPlan p;
   p.M = uni32(s.mom.M);
   p.narrow = uni32(s.mom.narrow);
+  p.direct = uni32(s.mom.direct);
   p.mblocks = uni32(s.mom.mblocks);
   p.tiles = uni32(s.mom.tiles);
   p.ks = uni32(s.mom.ks);
@@ -346,7 +345,7 @@ __global__ void __launch_bounds__(kMomBlock) batch_pilot_moments_kernel(BatchArg
   if (order > kNarrowMax) return;
   unit_table_fill(sm.unit);
   __syncthreads();
-  moments_unit<T>(uni_ptr(static_cast<const T*>(s.x)), uni64(s.n), s.L, moment_plan(uni64(s.n), order),
+  moments_unit<T>(uni_ptr(static_cast<const T*>(s.x)), uni64(s.n), s.L, narrow_plan(uni64(s.n), order),
                   u - uni64(pf[si]), 0, uni_ptr(s.dep_part), sm, uni_ptr(s.status));
 }
 
@@ -359,7 +358,7 @@ __global__ void __launch_bounds__(kBlock) batch_pilot_sum_kernel(BatchArgs a, FK
   const SetDev& s = a.sets[si];
   const int order = uni32(kap.order[*s.kbest]);
   if (order > kNarrowMax) return;
-  moments_reduce(uni_ptr(s.dep_part), moment_plan(uni64(s.n), order).rows, 2 * order, u - uni64(pf[si]),
+  moments_reduce(uni_ptr(s.dep_part), narrow_plan(uni64(s.n), order).rows, 2 * order, u - uni64(pf[si]),
                  uni_ptr(s.pil_S), red);
 }
 
@@ -459,12 +458,11 @@ __global__ void __launch_bounds__(kBlock) batch_adapt_apply_kernel(BatchArgs a) 
 // images of the descriptors and prefix arrays.
 static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* descs, std::vector<int64_t>* prefix,
                            unsigned long long** counters, SetDev** dev_sets, int64_t** dev_prefix,
-                           uint32_t** statuses_out = nullptr, unsigned int** done_out = nullptr) {
+                           uint32_t** statuses_out = nullptr) {
   Carver c(ws, ~size_t(0));
   const int ns = int(b.sets.size());
-  unsigned long long* cnt = c.take<unsigned long long>(kCounters);
-  uint32_t* statuses = c.take<uint32_t>(size_t(ns));
-  unsigned int* done = c.take<unsigned int>(2 * size_t(ns));
+  unsigned long long* cnt = c.take<unsigned long long>(kCounters + (size_t(ns) + 1) / 2);
+  uint32_t* statuses = reinterpret_cast<uint32_t*>(cnt + kCounters);
   SetDev* ds = c.take<SetDev>(ns);
   int64_t* dp = c.take<int64_t>(size_t(PF_COUNT) * (ns + 1));
   if (descs) descs->assign(ns, SetDev{});
@@ -486,12 +484,6 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
     d.chunk = deposit_chunk(in.N);
     d.b0 = scan_fourier_count(b.prec, d.n_cv, b.kappas.data(), b.B);
     const bool pairs = d.b0 < b.B;
-    if (d.b0 > 0) {
-      d.mom = moment_plan(d.n_cv, fourier_order(b.kappas[size_t(d.b0) - 1]));
-      d.mom_part = c.take<double>(size_t(d.mom.rows) * 2 * size_t(d.mom.M));
-      d.S = c.take<double>(2 * size_t(d.mom.M));
-    }
-    d.done = done + r;
     d.slots = cv_slots(d.n_cv);
     if (pairs) {
       const PairTuning tp = tuned_pass(b.prec, d.n_cv);
@@ -503,35 +495,59 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
     d.g_dep = ceil_div(d.chunks, kSumRows);
     d.blocks = ceil_div(in.N, kBlock);
     d.g_ad = ceil_div(d.blocks, kSumRows);
-    if (pairs) {
-      d.hist = c.take<int32_t>(size_t(d.cells) * size_t(d.sblocks));
-      d.packed = b.prec == KDE_F64 ? static_cast<void*>(c.take<double>(Packed<double>::per_particle * size_t(d.n_cv)))
-                                   : static_cast<void*>(c.take<uint32_t>(size_t(d.n_cv)));
-      d.partials = c.take<double>(size_t(d.slots) * 2 * b.B);
-      d.cv_l1 = c.take<double>(size_t(d.g_cv) * 2 * b.B);
-    }
+    // the moments and the pair sums follow each other and share their place, as
+    // in the scan of one set, whose plan this is
+    auto moments = [&](Carver& m) {
+      if (d.b0 == 0) return;
+      const int M = fourier_order(b.kappas[size_t(d.b0) - 1]);
+      const ScanBufs buf = carve_scan(m, cv_moment_room(d.n_cv, b.B), d.n_cv, M);
+      d.mom = buf.plan;
+      d.mom_part = buf.partials;
+      d.S = buf.S;
+    };
+    auto pair_sums = [&](Carver& m) {
+      if (!pairs) return;
+      d.hist = m.take<int32_t>(size_t(d.cells) * size_t(d.sblocks));
+      d.packed = b.prec == KDE_F64 ? static_cast<void*>(m.take<double>(Packed<double>::per_particle * size_t(d.n_cv)))
+                                   : static_cast<void*>(m.take<uint32_t>(size_t(d.n_cv)));
+      d.partials = m.take<double>(size_t(d.slots) * 2 * b.B);
+      d.cv_l1 = m.take<double>(size_t(d.g_cv) * 2 * b.B);
+    };
+    Carver mom_size(nullptr, 0), pair_size(nullptr, 0);
+    moments(mom_size);
+    pair_sums(pair_size);
+    const size_t shared = std::max(mom_size.used, pair_size.used);
+    char* place = c.take<char>(shared);
+    Carver mom_at(place, shared), pairs_at(place, shared);
+    moments(mom_at);
+    pair_sums(pairs_at);
+    double* scalars = c.take<double>(5);
+    d.ad_sums = scalars;
+    d.kstar = scalars + 2;
+    d.kbest = reinterpret_cast<int*>(scalars + 3);
+    d.done = reinterpret_cast<unsigned int*>(scalars + 3) + 1;
+    d.pil_ok = reinterpret_cast<unsigned int*>(scalars + 4);
     d.dep_part = c.take<double>(size_t(d.chunks) * in.M);
     d.dep_l1 = c.take<double>(size_t(d.g_dep) * in.M);
     d.pilot = in.pilot ? in.pilot : c.take<double>(size_t(in.M));
     d.ad_part = c.take<double>(size_t(d.blocks) * 2);
     d.ad_l1 = c.take<double>(size_t(d.g_ad) * 2);
-    d.ad_sums = c.take<double>(2);
     d.kappa_i = in.kappa_i ? in.kappa_i : static_cast<void*>(c.take<char>(size_t(in.N) * es));
     d.rho = in.rho;
-    d.cv = in.cv ? in.cv : c.take<double>(size_t(b.B));
-    d.kstar = c.take<double>(1);
-    d.kbest = c.take<int>(1);
+    // the objective that the caller does not take: read before the deposits' and
+    // widths' arrays are written, of which these three alone are 768 bytes
+    static_assert(KDE_MAX_KAPPAS * sizeof(double) <= 3 * 256);
+    d.cv = in.cv || d.b0 == 0 ? in.cv : d.dep_part;
     d.pil_mom = deposit_tries_moments(b.prec, in.N, in.M) ? 1 : 0;
-    d.pil_S = d.pil_mom ? c.take<double>(2 * kNarrowMax) : nullptr;
-    d.pil_ok = done + ns + r;
-    const MomentPlan pil = moment_plan(in.N, kNarrowMax);  // (the narrow form's chunks do not depend on the order)
+    d.pil_S = d.dep_part + size_t(kMomChunks) * 2 * kNarrowMax;  // (behind its rows, as in deposit())
+    const MomentPlan pil = narrow_plan(in.N, kNarrowMax);  // (its chunks do not depend on the order)
     d.kstar_user = in.kappa_star;
     d.status = statuses + b.order[r];
     if (descs) (*descs)[r] = d;
     const int64_t per[PF_COUNT] = {pairs ? d.slots * d.groups : 0, pairs ? d.g_cv : 0, d.chunks, d.g_dep, d.blocks,
                                    d.g_ad, pairs ? int64_t(d.sblocks) : 0,
                                    d.b0 > 0 ? d.mom.chunks * d.mom.mblocks : 0,
-                                   d.b0 > 0 ? ceil_div(2 * d.mom.M, kRedCols) : 0, int64_t(d.b0), pairs ? 1 : 0,
+                                   d.b0 > 0 && d.mom.rows > 1 ? ceil_div(2 * d.mom.M, kRedCols) : 0, int64_t(d.b0), pairs ? 1 : 0,
                                    d.pil_mom ? pil.chunks : 0, d.pil_mom ? ceil_div(2 * kNarrowMax, kRedCols) : 0,
                                    int64_t(d.pil_mom)};
     for (int k = 0; k < PF_COUNT; ++k) {
@@ -543,7 +559,6 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
     if (prefix) (*prefix)[size_t(k) * (ns + 1) + ns] = acc[k];
   if (counters) *counters = cnt;
   if (statuses_out) *statuses_out = statuses;
-  if (done_out) *done_out = done;
   if (dev_sets) *dev_sets = ds;
   if (dev_prefix) *dev_prefix = dp;
   return c.used;
@@ -625,14 +640,16 @@ static kde_status enqueue_batch(const BatchPlan& b, const BatchArgs& a, const st
                                   dep_table_bytes<T>(kDepPairParticles, std::min(b.max_M, kBlock) & ~1));
   const size_t pack_lds = size_t(b.max_cells) * sizeof(int);
 
-  hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(kBlock), 0, s, a.counters, a.statuses, a.done, ns);
+  hipLaunchKernelGGL(batch_zero_kernel, dim3(1), dim3(kBlock), 0, s, a);
   KDE_CHECK_LAUNCH();
   if (total(PF_MOMENTS) > 0) {
     const FKappas fk = fourier_list(b.kappas.data(), b.max_b0);
     hipLaunchKernelGGL(batch_moments_kernel<T>, dim3(unsigned(total(PF_MOMENTS))), dim3(kMomBlock), 0, s, a);
     KDE_CHECK_LAUNCH();
-    hipLaunchKernelGGL(batch_moment_sum_kernel, dim3(unsigned(total(PF_MOM_SUM))), dim3(kBlock), 0, s, a);
-    KDE_CHECK_LAUNCH();
+    if (total(PF_MOM_SUM) > 0) {
+      hipLaunchKernelGGL(batch_moment_sum_kernel, dim3(unsigned(total(PF_MOM_SUM))), dim3(kBlock), 0, s, a);
+      KDE_CHECK_LAUNCH();
+    }
     hipLaunchKernelGGL(batch_series_kernel, dim3(unsigned(total(PF_SERIES))), dim3(kBlock),
                        series_lds(fk.order[b.max_b0 - 1]), s, a, fk);
     KDE_CHECK_LAUNCH();
@@ -713,9 +730,8 @@ static void batch_images(const BatchPlan& b, void* ws, std::vector<SetDev>& desc
   SetDev* dsets = nullptr;
   int64_t* dpref = nullptr;
   uint32_t* statuses = nullptr;
-  unsigned int* done = nullptr;
-  layout_batch(b, ws, &descs, &prefix, &counters, &dsets, &dpref, &statuses, &done);
-  a = BatchArgs{dsets, dpref, counters, statuses, done, int(b.sets.size()), b.B, b.alpha};
+  layout_batch(b, ws, &descs, &prefix, &counters, &dsets, &dpref, &statuses);
+  a = BatchArgs{dsets, dpref, counters, statuses, int(b.sets.size()), b.B, b.alpha};
 }
 
 kde_status batch_plan_make(const kde_batch_set* sets_h, int nsets, int prec, int B, const double* kappas_h,

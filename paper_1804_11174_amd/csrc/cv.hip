@@ -190,22 +190,22 @@ static CvBuffers carve_cv(Carver& cv, const CvPlan& p, int64_t n, int B, int pre
   return b;
 }
 
-// Series order the moments of a scan of n particles are sized for.
-static int scan_order(int64_t n) { return fourier_order(scan_kappa_limit(n)); }
-
 // The two parts of a scan follow each other on the stream and share the
-// workspace, and the triangle's scan takes the same size: the largest of
-// their needs.
+// workspace, and so does the triangle's scan in double: all of them fit the
+// pair layout (the moments take as many rows as it holds).
 size_t cv_workspace_bytes(int64_t n, int B, int prec) {
   CvPlan p = make_cv_plan(n);
-  Carver pairs(nullptr, 0), moments(nullptr, 0);
+  Carver pairs(nullptr, 0);
   carve_cv(pairs, p, n, B, prec);
-  size_t need = pairs.used;
-  if (prec == KDE_F64) {
-    carve_scan(moments, n, scan_order(n));
-    need = std::max(need, std::max(moments.used, tri_scan_workspace_bytes(n, B)));
-  }
-  return need;
+  return pairs.used;
+}
+// Of them for the moments: what the batched engine's pair sums take too (all
+// but the raw sums, which it keeps elsewhere), so that both plan alike.
+size_t cv_moment_room(int64_t n, int B) {
+  CvPlan p = make_cv_plan(n);
+  Carver pairs(nullptr, 0);
+  carve_cv(pairs, p, n, B, KDE_F64);
+  return pairs.used - 2 * size_t(B) * sizeof(double);
 }
 
 // The leading concentrations through the moments (double form,
@@ -215,15 +215,16 @@ template <typename T>
 static kde_status run_cv(const kde_domain* dom, int64_t n, const T* x, int B, const double* kappas,
                          double* cv, double* sums, int32_t* argmin, void* ws, size_t ws_bytes,
                          hipStream_t s, uint32_t* status) {
-  if (ws_bytes < cv_workspace_bytes(n, B, dom->prec))
-    return fail(KDE_E_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, cv_workspace_bytes(n, B, dom->prec));
+  const size_t need = cv_workspace_bytes(n, B, dom->prec);
+  if (ws_bytes < need) return fail(KDE_E_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
   const int b0 = scan_fourier_count(dom->prec, n, kappas, B);
   TimedLaunch timed(KDE_KERNEL_CV_PAIRS, s);  // the sums of every concentration
   if (b0 > 0) {
     Carver c(ws, ws_bytes);
-    const ScanBufs buf = carve_scan(c, n, scan_order(n));
     const int M = fourier_order(kappas[b0 - 1]);
-    KDE_RETURN_IF(launch_moments(x, n, dom->L, M, buf, s, timed.start(), nullptr, status));
+    const ScanBufs buf = carve_scan(c, cv_moment_room(n, B), n, M);
+    if (!c.fits()) return fail(KDE_E_INTERNAL, "%d moments do not fit %zu bytes", M, ws_bytes);
+    KDE_RETURN_IF(launch_moments(x, n, dom->L, buf, s, timed.start(), nullptr, status));
     KDE_RETURN_IF(launch_series(buf, M, n, dom->L, fourier_list(kappas, b0), b0, B, cv, sums,
                                 b0 == B ? argmin : nullptr, s, b0 == B ? timed.stop() : nullptr));
     if (b0 == B) return KDE_OK;

@@ -555,9 +555,9 @@ kde_status deposit(const kde_domain* dom, int64_t n, const void* x, const void* 
       static_assert(size_t(kMomChunks + 1) * 2 * kNarrowMax <= (size_t(1) << 25) / kDepMaxChunk);
       double* S = partials + size_t(kMomChunks) * 2 * kNarrowMax;
       unsigned int* ok = reinterpret_cast<unsigned int*>(scratch + sums);
-      const ScanBufs mom{partials, S, ok};
+      const ScanBufs mom{narrow_plan(n, order), partials, S, ok};
       KDE_RETURN_IF(check_lds(sizeof(double2) * size_t(dom->M) + sizeof(SynthSmem)));
-      KDE_RETURN_IF(launch_moments(static_cast<const double*>(x), n, dom->L, order, mom, s, start, nullptr, status));
+      KDE_RETURN_IF(launch_moments(static_cast<const double*>(x), n, dom->L, mom, s, start, nullptr, status));
       hipLaunchKernelGGL(deposit_synthesis_kernel, dim3(1), dim3(kBlock), sizeof(double2) * size_t(dom->M), s,
                          (const double*)S, order, kappa, double(n), dom->L, dom->M, rho, ok);
       KDE_CHECK_LAUNCH();

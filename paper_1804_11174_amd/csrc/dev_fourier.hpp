@@ -31,6 +31,9 @@
 //          no barrier between the waves. Up to four values of a (M <= 52) go
 //          to v_mfma_f64_4x4x4 (four blocks of 4 x 4): once for the cosines and
 //          once for the sines of a by the 16 columns, half the matrix time.
+//   direct (small samples): a workgroup per 4, 8 or 16 modes, each thread a phase,
+//          rotations and the sums of its particles, one exchange at the end: the
+//          moments themselves, with no rows and no launch to sum them.
 // The matrix instruction and the vector FMAs share a SIMD's FP64 units, so
 // what bounds it is their sum: the products (2 operations per particle and
 // mode) and the phases. Measured on MI355X against the kernel of rotations
@@ -59,46 +62,89 @@ constexpr int kMomPad = kMomGroup + 2;  // padded so that the 8 or 16 rows read 
 constexpr int kWideStep = 31, kWideB = 16, kWideA = 32;  // mode block: a < 32
 constexpr int kNarrowStep = 15, kNarrowB = 8, kNarrowA = 8;
 constexpr int kNarrowMax = kNarrowStep * (kNarrowA - 1) + kNarrowB - 1;  // 112
-constexpr int kWideModes = kWideStep * kWideA;                          // modes a further mode block adds
 constexpr int kMomBlock = 512;          // threads of a moment workgroup: two teams, or eight waves
 constexpr int kMomTeam = 256;
 constexpr int kMomWaves = kMomBlock / 64;
 constexpr int64_t kMomChunks = 256;     // particle chunks a launch aims for (one workgroup per CU: its LDS)
 
-// How the moments of n particles to order M are cut: a function of (n, M)
-// alone, so the one-set calls and the batched engine sum the same partials
-// in the same order.
+// How the moments of n particles to order M are cut. The scans of a sample
+// and the batched engine take the same plan (a function of n, M and the rows
+// that the scan's workspace holds), so they sum the same partials in the same order.
 struct MomentPlan {
   int M;
-  int narrow;
-  int mblocks;  // mode blocks
-  int tiles;    // wide: tiles of 8 a in a mode block (the last block may need fewer)
-  int ks;       // wide: waves sharing a tile (each a share of the particles, with rows of their own)
-  int na;       // values of a (narrow)
-  int64_t per;  // particles per chunk
-  int64_t chunks, rows;
+  int narrow, direct;    // direct: modes of a workgroup
+  int mblocks;           // mode blocks
+  int tiles, ks;         // wide: tiles of 8 a in a mode block, waves sharing a tile (each a share of the particles)
+  int na;                // values of a (narrow)
+  int64_t per;           // particles per chunk
+  int64_t chunks, rows;  // rows of 2 M partial sums, one per chunk; a single one is the result
 };
 
-__host__ __device__ inline MomentPlan moment_plan(int64_t n, int M) {
+__host__ __device__ inline MomentPlan narrow_plan(int64_t n, int M, int64_t max_rows = kMomChunks) {
   MomentPlan p{};
   p.M = M;
-  p.narrow = M <= kNarrowMax ? 1 : 0;
-  if (p.narrow) {
-    p.mblocks = p.tiles = p.ks = 1;
-    p.na = M <= kNarrowB - 1 ? 1 : (M - (kNarrowB - 1) + kNarrowStep - 1) / kNarrowStep + 1;
-    p.per = kMomBlock * ceil_div(ceil_div(n, kMomBlock), kMomChunks);
-    p.chunks = ceil_div(n, p.per);
-    p.rows = p.chunks;
-    return p;
-  }
-  const int na = (M - (kWideB - 1) + kWideStep - 1) / kWideStep + 1;
-  p.mblocks = (na + kWideA - 1) / kWideA;
-  p.tiles = p.mblocks > 1 ? 4 : (na + 7) / 8;
-  p.ks = p.tiles == 1 ? 4 : (p.tiles == 2 ? 2 : 1);
-  const int64_t aim = kMomChunks / p.mblocks > 1 ? kMomChunks / p.mblocks : 1;
-  p.per = 2 * kMomGroup * ceil_div(ceil_div(n, 2 * kMomGroup), aim);  // the teams take groups in turn
+  p.narrow = 1;
+  p.mblocks = p.tiles = p.ks = 1;
+  p.na = M <= kNarrowB - 1 ? 1 : (M - (kNarrowB - 1) + kNarrowStep - 1) / kNarrowStep + 1;
+  p.per = kMomBlock * ceil_div(ceil_div(n, kMomBlock), max_rows < kMomChunks ? max_rows : kMomChunks);
   p.chunks = ceil_div(n, p.per);
-  p.rows = p.chunks * p.ks;
+  p.rows = p.chunks;
+  return p;
+}
+
+// Tiles per mode block of the wide form: four, or fewer where the workspace holds
+// too few rows to fill the chip with chunks (a workgroup with one tile takes about
+// half the time per group of particles). Then the direct form, with the fewest
+// modes per workgroup that leave one workgroup per CU, where its time is below
+// the matrix forms' with their second launch, by the times of the parts in ns.
+// Whole scans of 8 concentrations to 1e4, direct against matrix forms: 1000 to
+// 8192 particles 18 us (21), 12,000 21.0 (21.0), 16,384 24.0 (20.5). With rows for
+// 46 to 60 chunks in the pair layout and two or one tiles: 20,011 particles 20.9 us,
+// 24.2 with four tiles and 20.9 with all 157 rows; a single concentration pays
+// more (23.4 against 20.4), and kappas near 1e6, whose rows are 146 KB, most:
+// 18,000 particles 95 us (52), 65,536 with one concentration 144 (99).
+inline double wide_group_ns(int tiles) { return tiles >= 3 ? 850.0 : (tiles == 2 ? 600.0 : 450.0); }
+inline double direct_particle_ns(int modes) { return modes == 4 ? 0.46 : (modes == 8 ? 0.65 : 1.1); }
+constexpr double kNarrowGroupNs = 600.0, kSecondLaunchNs = 3000.0;
+
+inline MomentPlan moment_plan(int64_t n, int M, int64_t max_rows) {
+  MomentPlan p{};
+  const int64_t most = max_rows > 1 ? max_rows : 1;
+  double ns = 0.0;
+  if (M <= kNarrowMax) {
+    p = narrow_plan(n, M, most);
+    ns = double(p.per / kMomBlock) * kNarrowGroupNs;
+  } else {
+    p.M = M;
+    const int na = (M - (kWideB - 1) + kWideStep - 1) / kWideStep + 1;
+    const int all = (na + 7) / 8;
+    for (int tiles = all < 4 ? all : 4;; tiles = tiles == 3 ? 2 : tiles / 2) {
+      p.tiles = tiles;
+      p.ks = tiles == 1 ? 4 : (tiles == 2 ? 2 : 1);
+      p.mblocks = (all + tiles - 1) / tiles;
+      int64_t aim = kMomChunks / p.mblocks;
+      if (aim > most) aim = most;
+      if (aim < 1) aim = 1;
+      p.per = 2 * kMomGroup * ceil_div(ceil_div(n, 2 * kMomGroup), aim);  // the teams take groups in turn
+      p.chunks = ceil_div(n, p.per);
+      const int finer = tiles == 3 ? 2 : tiles / 2;
+      if (tiles == 1 || p.chunks * ((all + finer - 1) / finer) > kMomChunks || p.per == 2 * kMomGroup) break;
+    }
+    p.rows = p.chunks;
+    ns = double(p.per / kMomGroup + 1) * wide_group_ns(p.tiles) * double(ceil_div(p.chunks * p.mblocks, kMomChunks));
+  }
+  int modes = 4;
+  while (modes < 16 && ceil_div(M, modes) > kMomChunks) modes *= 2;
+  const int64_t blocks = ceil_div(M, modes);
+  const double direct_ns = double(n) * direct_particle_ns(modes) * double(ceil_div(blocks, kMomChunks));
+  if (direct_ns >= ns + (p.rows > 1 ? kSecondLaunchNs : 0.0)) return p;
+  p = MomentPlan{};
+  p.M = M;
+  p.direct = modes;
+  p.mblocks = int(blocks);
+  p.tiles = p.ks = 1;
+  p.per = n;
+  p.chunks = p.rows = 1;
   return p;
 }
 
@@ -158,11 +204,10 @@ struct MomSmem {
   double2 unit[256];
 };
 
-// One (chunk, mode block) of the wide form; `rows` points at the chunk's ks
-// partial rows of 2 M doubles. Every thread of the workgroup must call this.
+// One (chunk, mode block) of the wide form, into the chunk's row of 2 M doubles. Every thread of the workgroup must call this.
 template <typename T>
 __device__ __forceinline__ void moments_wide(const T* __restrict__ x, int64_t lo, int64_t hi, double L,
-                                             const MomentPlan& p, int mb, double* __restrict__ rows, MomSmem& sm,
+                                             const MomentPlan& p, int mb, double* __restrict__ out, MomSmem& sm,
                                              uint32_t* status) {
   const int tid = threadIdx.x, lane = tid & 63, team = tid / kMomTeam, w = (tid % kMomTeam) >> 6;
   double2(*za)[kMomPad] = reinterpret_cast<double2(*)[kMomPad]>(sm.z) + team * (kWideA + kWideB);
@@ -172,11 +217,12 @@ __device__ __forceinline__ void moments_wide(const T* __restrict__ x, int64_t lo
   const int steps = (kMomGroup / 4) / p.ks;
   const int M = p.M;
   const double inv_L = 1.0 / L;
-  // values of a this mode block needs
-  const int na = (M - (kWideB - 1) + kWideStep - 1) / kWideStep + 1 - kWideA * mb;
-  const bool gen = 8 * w < na;  // wave w also generates the phases of a = 8 w ..
+  // values of a this mode block needs, from a0 on
+  const int a0 = 8 * p.tiles * mb;
+  const int na = min((M - (kWideB - 1) + kWideStep - 1) / kWideStep + 1 - a0, 8 * p.tiles);
+  const bool gen = 8 * w < na;  // wave w also generates the phases of a = a0 + 8 w ..
   const bool mul = slice < p.ks && 8 * tile < na;
-  const double m_a = double(kWideStep * (kWideA * mb + 8 * w));
+  const double m_a = double(kWideStep * (a0 + 8 * w));
   f64x4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
   const int groups = int((hi - lo + kMomGroup - 1) / kMomGroup);
   const double* arow = reinterpret_cast<const double*>(&za[8 * tile + (i16 & 7)][0]) + (i16 >> 3);
@@ -237,26 +283,27 @@ __device__ __forceinline__ void moments_wide(const T* __restrict__ x, int64_t lo
     }
     __syncthreads();
   }
-  // the second team's sums are added to the first's
+  // a tile's sums: the teams' and the slices' in order
   double* red = reinterpret_cast<double*>(sm.z);
-  if (team == 1) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      red[r * kMomTeam + tid - kMomTeam] = acc0[r];
-      red[(4 + r) * kMomTeam + tid - kMomTeam] = acc1[r];
-    }
+  for (int r = 0; r < 4; ++r) {
+    red[r * kMomBlock + tid] = acc0[r];
+    red[(4 + r) * kMomBlock + tid] = acc1[r];
   }
   __syncthreads();
-  if (team == 0 && mul) {
-    double* out = rows + int64_t(slice) * 2 * M;
+  if (team == 0 && slice == 0 && mul) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      acc0[r] += red[r * kMomTeam + tid];
-      acc1[r] += red[(4 + r) * kMomTeam + tid];
+      acc0[r] = acc1[r] = 0.0;
+      for (int q = 0; q < p.ks; ++q) {
+        const int at = tid + 64 * q * p.tiles;
+        acc0[r] += red[r * kMomBlock + at] + red[r * kMomBlock + at + kMomTeam];
+        acc1[r] += red[(4 + r) * kMomBlock + at] + red[(4 + r) * kMomBlock + at + kMomTeam];
+      }
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int a = kWideA * mb + 8 * tile + 4 * h + k4, b = i16;
+      const int a = a0 + 8 * tile + 4 * h + k4, b = i16;
       const double cc = acc0[h], sc = acc0[h + 2], cs = acc1[h], ss = acc1[h + 2];
       const int mp = kWideStep * a + b, mm = kWideStep * a - b;
       if (mp >= 1 && mp <= M) {
@@ -365,6 +412,59 @@ __device__ __forceinline__ void moments_narrow(const T* __restrict__ x, int64_t 
   __syncthreads();
 }
 
+// K modes of the direct form, over all particles, into the moments `out`.
+template <int K, typename T>
+__device__ __forceinline__ void moments_direct(const T* __restrict__ x, int64_t n, double L, int M, int mb,
+                                               double* __restrict__ out, MomSmem& sm, uint32_t* status) {
+  constexpr int kVals = 2 * K;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int m0 = 1 + K * mb;
+  const double inv_L = 1.0 / L;
+  double v[kVals];
+#pragma unroll
+  for (int k = 0; k < kVals; ++k) v[k] = 0.0;
+#pragma unroll 2
+  for (int64_t j = tid; j < n; j += kMomBlock) {
+    const double xv = double(x[j]);
+    if (mb == 0) note_numeric(status, !isfinite(xv), false);
+    const double f = period_fraction(xv, L, inv_L);
+    const double2 z1 = table_phase(1.0, f, sm.unit);
+    double2 z;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      z = k % 8 == 0 ? table_phase(double(m0 + k), f, sm.unit) : rotate(z, z1);
+      v[2 * k] += z.x;
+      v[2 * k + 1] += z.y;
+    }
+  }
+  // the lanes' sums in a tree over all values at once: after the exchange at
+  // distance d a lane keeps the half of the values that its bit d names
+  int half = K, d = 32;
+#pragma unroll
+  for (; half >= 1; half >>= 1, d >>= 1) {
+    const bool up = (lane & d) != 0;
+#pragma unroll
+    for (int k = 0; k < half; ++k) {
+      const double keep = up ? v[k + half] : v[k];
+      const double give = up ? v[k] : v[k + half];
+      v[k] = keep + shfl_xor_d(give, d);
+    }
+  }
+#pragma unroll
+  for (; d >= 1; d >>= 1) v[0] += shfl_xor_d(v[0], d);
+  constexpr int kSame = 64 / kVals;  // lanes that hold one value
+  double* red = reinterpret_cast<double*>(sm.z);
+  if (lane % kSame == 0) red[w * kVals + lane / kSame] = v[0];
+  __syncthreads();
+  if (tid < kVals) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMomWaves; ++q) t += red[q * kVals + tid];
+    if (m0 + (tid >> 1) <= M) out[2 * (m0 - 1) + tid] = t;
+  }
+  __syncthreads();
+}
+
 // Unit (chunk, mode block) of a set's moments into its partial rows, by a
 // workgroup of kMomBlock threads; sm.unit must be filled and visible.
 template <typename T>
@@ -372,10 +472,16 @@ __device__ __forceinline__ void moments_unit(const T* __restrict__ x, int64_t n,
                                              int64_t chunk, int mb, double* __restrict__ partials, MomSmem& sm,
                                              uint32_t* status) {
   const int64_t lo = chunk * p.per, hi = min(n, lo + p.per);
-  if (p.narrow)
+  if (p.direct == 4)
+    moments_direct<4>(x, n, L, p.M, mb, partials, sm, status);
+  else if (p.direct == 8)
+    moments_direct<8>(x, n, L, p.M, mb, partials, sm, status);
+  else if (p.direct == 16)
+    moments_direct<16>(x, n, L, p.M, mb, partials, sm, status);
+  else if (p.narrow)
     moments_narrow(x, lo, hi, L, p, partials + chunk * 2 * int64_t(p.M), sm, status);
   else
-    moments_wide(x, lo, hi, L, p, mb, partials + chunk * p.ks * 2 * int64_t(p.M), sm, status);
+    moments_wide(x, lo, hi, L, p, mb, partials + chunk * 2 * int64_t(p.M), sm, status);
 }
 
 // Sum of the partial rows, kRedCols columns per workgroup: thread (y, c)
@@ -771,7 +877,7 @@ inline FKappas fourier_list(const double* k, int B) {
 // pair sums within 1e-15. The route costs n x order multiply-adds against
 // n^2 / 2 pair terms of 33 operations, so where the accuracy allows it, it is
 // the faster one at every size measured (calls of 8 concentrations to 1e3 at
-// n = 4096: 22 us against 381; of 32 to 1e4 at 65,536: 24 us against 44,000).
+// n = 4096: 18 us against 381; of 32 to 1e4 at 65,536: 24 us against 44,000).
 // The float form keeps its float pair terms: its results are those of float
 // arithmetic, which the moments (in double) do not reproduce.
 inline double scan_kappa_limit(int64_t n) {
@@ -787,42 +893,29 @@ inline int scan_fourier_count(int prec, int64_t n, const double* kappas, int B) 
   return b;
 }
 
-// Largest (rows x 2 M) partial array, in doubles, of n particles over the
-// orders up to Mmax: rows x M grows with M inside each form, so its largest
-// value lies at the end of a form's range.
-inline size_t moment_partials_max(int64_t n, int Mmax) {
-  size_t most = 0;
-  auto take = [&](int M) {
-    if (M > Mmax) M = Mmax;
-    const MomentPlan p = moment_plan(n, M);
-    const size_t v = size_t(p.rows) * 2 * size_t(M);
-    if (v > most) most = v;
-  };
-  take(kNarrowMax);
-  for (int t = 1; t <= 4; ++t) take(kWideStep * (8 * t - 1) + kWideB - 1);
-  for (int mb = 2; kWideModes * (mb - 1) < Mmax; ++mb) take(kWideModes * mb - kWideStep + kWideB - 1);
-  take(Mmax);
-  return most;
-}
-
-// Workspace of the scan of n particles to order M: partial rows, moments.
+// The moments' part of a workspace: partial rows (where there is more than
+// one), the moments, and a counter of the series.
 struct ScanBufs {
+  MomentPlan plan;
   double* partials;
   double* S;
   unsigned int* done;  // workgroups of the series that have written their value
 };
-inline ScanBufs carve_scan(Carver& c, int64_t n, int Mmax) {
+// To order M, of n particles, in `room` bytes, which have to hold one row.
+inline ScanBufs carve_scan(Carver& c, size_t room, int64_t n, int M) {
   ScanBufs b{};
-  b.partials = c.take<double>(moment_partials_max(n, Mmax));
-  b.S = c.take<double>(size_t(2) * size_t(Mmax));
   b.done = c.take<unsigned int>(1);
+  b.S = c.take<double>(size_t(2) * size_t(M));
+  const size_t before = round_up(c.used, 256), row = size_t(2) * size_t(M) * sizeof(double);
+  b.plan = moment_plan(n, M, before < room ? int64_t((room - before) / row) : 0);
+  b.partials = b.plan.rows > 1 ? c.take<double>(size_t(b.plan.rows) * 2 * size_t(M)) : b.S;
   return b;
 }
 
 // Moments of x into b.S (fourier.hip). The launches record t0 as their
 // start, `done` is zeroed.
 template <typename T>
-kde_status launch_moments(const T* x, int64_t n, double L, int M, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
+kde_status launch_moments(const T* x, int64_t n, double L, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
                           hipEvent_t t1, uint32_t* status);
 // The series of concentrations [0, B) of a list of Ball: cv[b], sums[b],
 // sums[Ball + b] (sums may be NULL), and the first minimum into *argmin when

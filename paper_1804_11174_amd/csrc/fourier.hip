@@ -123,17 +123,40 @@ struct FourierBufs {
   double* sums2;     // [2]
 };
 
-FourierBufs carve_fourier(Carver& c, int op, int64_t n, int B) {
+// Doubles that the column sums of budget x 2 kMaxOrder partials need.
+size_t rot_colsum(int64_t budget) {
+  return (column_sum_scratch(budget * kMaxOrder, 2) + column_sum_scratch(1, 2 * kMaxOrder)) / sizeof(double) + 1;
+}
+
+// What the moments of a scan (or, with B = 1, of the exact pilot) may take, of any
+// order: a workspace that does not grow with the order asked for, and holds the
+// partials' budget, the sums and a series per concentration of the longest one.
+size_t moment_room(int64_t n, int B) {
+  Carver c(nullptr, 0);
+  const int64_t budget = rot_budget(n);
+  c.take<double>(size_t(budget) * 2 * kMaxOrder);
+  c.take<double>(rot_colsum(budget));
+  c.take<double>(size_t(2) * kMaxOrder);
+  c.take<double>(size_t(B) * (kMaxOrder + 1));
+  return c.used;
+}
+
+// order: that of the moments (their plan depends on it, the size does not).
+FourierBufs carve_fourier(Carver& c, int op, int64_t n, int B, int order) {
   FourierBufs b{};
   const int M = kMaxOrder;
-  if (op != KDE_OP_CV_REFINE) b.scan = carve_scan(c, n, M);
+  if (op != KDE_OP_CV_REFINE) {
+    const size_t room = moment_room(n, op == KDE_OP_ADAPT_EXACT ? 1 : B);
+    Carver part(c.take<char>(room), room);
+    b.scan = carve_scan(part, room, n, order);
+  }
   if (op == KDE_OP_CV_REFINE) {
     // any order's chunks x 2 M partials fit the budget; its column-sum
     // scratch, ceil(chunks / R) x 2 M for R rows per level-1 block, is at
     // most (chunks x 2 M) / R + 2 M
     const int64_t budget = rot_budget(n);
     b.rows = c.take<double>(size_t(budget) * 2 * M);
-    b.colsum = c.take<double>((column_sum_scratch(budget * M, 2) + column_sum_scratch(1, 2 * M)) / sizeof(double) + 1);
+    b.colsum = c.take<double>(rot_colsum(budget));
     b.S = c.take<double>(size_t(2) * M);
     b.rho = c.take<double>(size_t(3) * (M + 1));
     b.cvgrid = c.take<double>(size_t(B));
@@ -991,13 +1014,12 @@ __global__ void __launch_bounds__(kBlock) pilot_apply_kernel(const double* __res
   }
 }
 
-kde_status moments_any(const kde_domain* dom, int64_t n, const void* x, int M, const FourierBufs& b,
-                       hipStream_t s) {
+kde_status moments_any(const kde_domain* dom, int64_t n, const void* x, const FourierBufs& b, hipStream_t s) {
   TimedLaunch timed(KDE_KERNEL_MOMENTS, s);
   if (dom->prec == KDE_F64)
-    return launch_moments(static_cast<const double*>(x), n, dom->L, M, b.scan, s, timed.start(), timed.stop(),
+    return launch_moments(static_cast<const double*>(x), n, dom->L, b.scan, s, timed.start(), timed.stop(),
                           plain_numeric_word());
-  return launch_moments(static_cast<const float*>(x), n, dom->L, M, b.scan, s, timed.start(), timed.stop(),
+  return launch_moments(static_cast<const float*>(x), n, dom->L, b.scan, s, timed.start(), timed.stop(),
                         plain_numeric_word());
 }
 
@@ -1068,21 +1090,23 @@ kde_status check_fourier_kappas(int B, const double* kappas_h) {
 }  // namespace
 
 template <typename T>
-kde_status launch_moments(const T* x, int64_t n, double L, int M, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
+kde_status launch_moments(const T* x, int64_t n, double L, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
                           hipEvent_t t1, uint32_t* status) {
-  const MomentPlan p = moment_plan(n, M);
+  const MomentPlan& p = b.plan;
+  const bool one = p.rows == 1;
   hipExtLaunchKernelGGL((moments_kernel<T>), dim3(unsigned(p.chunks), unsigned(p.mblocks)), dim3(kMomBlock), 0, s, t0,
-                        nullptr, 0, x, n, L, p, b.partials, b.done, status);
+                        one ? t1 : nullptr, 0, x, n, L, p, one ? b.S : b.partials, b.done, status);
   KDE_CHECK_LAUNCH();
-  hipExtLaunchKernelGGL(moments_reduce_kernel, dim3(unsigned(ceil_div(2 * M, kRedCols))), dim3(kBlock), 0, s, nullptr,
-                        t1, 0, (const double*)b.partials, p.rows, 2 * M, b.S);
+  if (one) return KDE_OK;
+  hipExtLaunchKernelGGL(moments_reduce_kernel, dim3(unsigned(ceil_div(2 * p.M, kRedCols))), dim3(kBlock), 0, s, nullptr,
+                        t1, 0, (const double*)b.partials, p.rows, 2 * p.M, b.S);
   KDE_CHECK_LAUNCH();
   return KDE_OK;
 }
-template kde_status launch_moments<double>(const double*, int64_t, double, int, const ScanBufs&, hipStream_t,
-                                           hipEvent_t, hipEvent_t, uint32_t*);
-template kde_status launch_moments<float>(const float*, int64_t, double, int, const ScanBufs&, hipStream_t,
-                                          hipEvent_t, hipEvent_t, uint32_t*);
+template kde_status launch_moments<double>(const double*, int64_t, double, const ScanBufs&, hipStream_t, hipEvent_t,
+                                           hipEvent_t, uint32_t*);
+template kde_status launch_moments<float>(const float*, int64_t, double, const ScanBufs&, hipStream_t, hipEvent_t,
+                                          hipEvent_t, uint32_t*);
 
 kde_status launch_series(const ScanBufs& b, int M, int64_t n, double L, const FKappas& kap, int B, int Ball,
                          double* cv, double* sums, int32_t* argmin, hipStream_t s, hipEvent_t t1) {
@@ -1094,7 +1118,7 @@ kde_status launch_series(const ScanBufs& b, int M, int64_t n, double L, const FK
 
 size_t fourier_workspace_bytes(int op, int64_t n, int B) {
   Carver c(nullptr, 0);
-  carve_fourier(c, op, n, B);
+  carve_fourier(c, op, n, B, kMaxOrder);
   return c.used;
 }
 
@@ -1113,9 +1137,9 @@ kde_status kde_cv_scan_fourier(const kde_domain* dom, int64_t N, const void* x, 
   KDE_RETURN_IF(check_workspace(ws, ws_bytes, fourier_workspace_bytes(KDE_OP_CV_FOURIER, N, B)));
   hipStream_t s = static_cast<hipStream_t>(stream);
   Carver c(ws, ws_bytes);
-  const FourierBufs b = carve_fourier(c, KDE_OP_CV_FOURIER, N, B);
   const int M = fourier_order(kappas_h[B - 1]);
-  KDE_RETURN_IF(moments_any(dom, N, x, M, b, s));
+  const FourierBufs b = carve_fourier(c, KDE_OP_CV_FOURIER, N, B, M);
+  KDE_RETURN_IF(moments_any(dom, N, x, b, s));
   return launch_series(b.scan, M, N, dom->L, fourier_list(kappas_h, B), B, B, cv, sums, argmin, s, nullptr);
 }
 
@@ -1128,7 +1152,7 @@ kde_status kde_cv_refine(const kde_domain* dom, int64_t N, const void* x, int32_
   KDE_RETURN_IF(check_workspace(ws, ws_bytes, fourier_workspace_bytes(KDE_OP_CV_REFINE, N, B)));
   hipStream_t s = static_cast<hipStream_t>(stream);
   Carver c(ws, ws_bytes);
-  const FourierBufs b = carve_fourier(c, KDE_OP_CV_REFINE, N, B);
+  const FourierBufs b = carve_fourier(c, KDE_OP_CV_REFINE, N, B, 0);
   const FKappas kl = refine_list(kappas_h, B);
   const int M = kl.order[B - 1];
   if (dom->prec == KDE_F64)
@@ -1161,9 +1185,9 @@ kde_status kde_adapt_widths_exact(const kde_domain* dom, int64_t N, const void* 
   KDE_RETURN_IF(check_workspace(ws, ws_bytes, fourier_workspace_bytes(KDE_OP_ADAPT_EXACT, N, 0)));
   hipStream_t s = static_cast<hipStream_t>(stream);
   Carver c(ws, ws_bytes);
-  const FourierBufs b = carve_fourier(c, KDE_OP_ADAPT_EXACT, N, 0);
   const int M = fourier_order(kappa_star);
-  KDE_RETURN_IF(moments_any(dom, N, x, M, b, s));
+  const FourierBufs b = carve_fourier(c, KDE_OP_ADAPT_EXACT, N, 0, M);
+  KDE_RETURN_IF(moments_any(dom, N, x, b, s));
   hipLaunchKernelGGL(pilot_weights_kernel, dim3(1), dim3(kBlock), series_lds(M), s, (const double*)b.scan.S, M,
                      kappa_star, b.w);
   KDE_CHECK_LAUNCH();

@@ -217,6 +217,7 @@ inline kde_status launch_pack_sorted(const T* x, int64_t n, double L, const Sort
 // One-set launchers of the path (cv.hip, density.hip); `status` receives
 // KDE_NUMERIC_* bits (may be null).
 size_t cv_workspace_bytes(int64_t n, int B, int prec);
+size_t cv_moment_room(int64_t n, int B);
 kde_status cv_scan(const kde_domain* dom, int64_t n, const void* x, int B, const double* kappas, double* cv,
                    double* sums, int32_t* argmin, void* ws, size_t ws_bytes, hipStream_t s, uint32_t* status);
 // The triangle's scan in double (tri_cells.hip).

@@ -46,7 +46,34 @@ static void bracket_lengths() {
   EXPECT(longer > 0);  // the case is met
 }
 
+// A plan covers the particles and the modes, and its arrays fit the room that
+// they were planned for, down to the room for a single row.
+static void plans() {
+  for (int64_t n : {2, 63, 700, 4096, 12000, 20011, 65536, 1000003, 1 << 30}) {
+    for (int M : {1, 4, 5, 111, 112, 113, 263, 264, 500, 759, 911, 1007, 1008, 4000, 9105}) {
+      for (double rows : {1.0, 1.9, 2.0, 3.0, 7.5, 40.0, 300.0}) {
+        const size_t room = 512 + size_t((rows + 1.0) * 16.0 * M);
+        Carver c(nullptr, 0);
+        const ScanBufs b = carve_scan(c, room, n, M);
+        const MomentPlan& p = b.plan;
+        EXPECT(c.used <= room && p.rows == p.chunks && p.M == M);
+        EXPECT(p.chunks * p.per >= n && (p.chunks - 1) * p.per < n);
+        if (p.direct) {
+          EXPECT(p.mblocks * int64_t(p.direct) >= M && p.chunks == 1);
+        } else if (p.narrow) {
+          EXPECT(M <= kNarrowMax && kNarrowStep * (p.na - 1) + kNarrowB - 1 >= M && p.na <= kNarrowA);
+        } else {
+          const int values = 8 * p.tiles * p.mblocks;  // of a; modes kWideStep a +- b
+          EXPECT(kWideStep * (values - 1) + kWideB - 1 >= M && p.tiles * p.ks <= 4 && 8 * p.tiles <= kWideA);
+          EXPECT(p.per % (2 * kMomGroup) == 0);
+        }
+      }
+    }
+  }
+}
+
 int main() {
+  plans();
   orders();
   bracket_lengths();
   if (failures == 0) std::printf("fourier rules ok\n");
