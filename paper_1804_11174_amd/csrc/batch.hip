@@ -77,7 +77,7 @@ struct SetDev {
   double* kstar;      // 1
   int* kbest;         // 1: its index in the list
   int pil_mom;        // the pilot tries the moments first (deposit_tries_moments)
-  double* pil_S;      // 2 kNarrowMax
+  double* pil_S;      // kNarrowSums
   unsigned int* pil_ok;  // they gave the pilot (zeroed by the first kernel)
   double* kstar_user; // 1 or NULL
   uint32_t* status;   // the set's numeric status word (KDE_NUMERIC_* bits)
@@ -350,16 +350,15 @@ __global__ void __launch_bounds__(kMomBlock) batch_pilot_moments_kernel(BatchArg
 }
 
 __global__ void __launch_bounds__(kBlock) batch_pilot_sum_kernel(BatchArgs a, FKappas kap) {
-  __shared__ double red[kBlock];
+  __shared__ NarrowSmem sm;
   const int64_t* pf = a.prefix + PF_PIL_SUM * (a.nsets + 1);
   const int64_t u = int64_t(blockIdx.x);
   if (u >= pf[a.nsets]) return;
   const int si = uni32(find_set(pf, a.nsets, u));
   const SetDev& s = a.sets[si];
-  const int order = uni32(kap.order[*s.kbest]);
-  if (order > kNarrowMax) return;
-  moments_reduce(uni_ptr(s.dep_part), narrow_plan(uni64(s.n), order).rows, 2 * order, u - uni64(pf[si]),
-                 uni_ptr(s.pil_S), red);
+  const int order = uni32(kap.order[*s.kbest]), unit = int(u - uni64(pf[si]));
+  if (order > kNarrowMax || unit >= narrow_units(order)) return;
+  narrow_sums(uni_ptr(s.dep_part), narrow_plan(uni64(s.n), order).rows, order, unit, *s.kstar, uni_ptr(s.pil_S), sm);
 }
 
 __global__ void __launch_bounds__(kBlock) batch_pilot_synthesis_kernel(BatchArgs a, FKappas kap) {
@@ -371,7 +370,7 @@ __global__ void __launch_bounds__(kBlock) batch_pilot_synthesis_kernel(BatchArgs
   const SetDev& s = a.sets[uni32(find_set(pf, a.nsets, u))];
   const int order = uni32(kap.order[*s.kbest]);
   if (order > kNarrowMax) return;
-  const bool good = deposit_synthesis(*s.kstar, order, uni_ptr(s.pil_S), double(s.n), s.L, uni32(s.M),
+  const bool good = deposit_synthesis(order, uni_ptr(s.pil_S), double(s.n), s.L, uni32(s.M),
                                       uni_ptr(s.pilot), reinterpret_cast<double2*>(dyn), sm);
   if (good && threadIdx.x == 0) *s.pil_ok = 1u;
 }
@@ -548,7 +547,7 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
                                    d.g_ad, pairs ? int64_t(d.sblocks) : 0,
                                    d.b0 > 0 ? d.mom.chunks * d.mom.mblocks : 0,
                                    d.b0 > 0 && d.mom.rows > 1 ? ceil_div(2 * d.mom.M, kRedCols) : 0, int64_t(d.b0), pairs ? 1 : 0,
-                                   d.pil_mom ? pil.chunks : 0, d.pil_mom ? ceil_div(2 * kNarrowMax, kRedCols) : 0,
+                                   d.pil_mom ? pil.chunks : 0, d.pil_mom ? narrow_units(kNarrowMax) : 0,
                                    int64_t(d.pil_mom)};
     for (int k = 0; k < PF_COUNT; ++k) {
       if (prefix) (*prefix)[size_t(k) * (ns + 1) + r] = acc[k];

@@ -47,13 +47,20 @@ __global__ void __launch_bounds__(kBlock) deposit_kernel(const T* __restrict__ x
 
 // The grid from the particles' moments (dev_fourier.hpp); *ok stays 0 where
 // the sum over the particles has to follow. Dynamic LDS: Mg unit vectors.
-__global__ void __launch_bounds__(kBlock) deposit_synthesis_kernel(const double* __restrict__ S, int M, double kappa,
-                                                                  double n, double L, int Mg,
-                                                                  double* __restrict__ rho, unsigned int* ok) {
+__global__ void __launch_bounds__(kBlock) deposit_synthesis_kernel(const double* __restrict__ S, int M, double n,
+                                                                  double L, int Mg, double* __restrict__ rho,
+                                                                  unsigned int* ok) {
   __shared__ SynthSmem sm;
   extern __shared__ __align__(16) unsigned char dyn[];
-  const bool good = deposit_synthesis(kappa, M, S, n, L, Mg, rho, reinterpret_cast<double2*>(dyn), sm);
+  const bool good = deposit_synthesis(M, S, n, L, Mg, rho, reinterpret_cast<double2*>(dyn), sm);
   if (good && threadIdx.x == 0) *ok = 1u;
+}
+
+// The rows' sums and the series' coefficients for it.
+__global__ void __launch_bounds__(kBlock) deposit_sums_kernel(const double* __restrict__ partials, int64_t rows, int M,
+                                                             double kappa, double* __restrict__ S) {
+  __shared__ NarrowSmem sm;
+  narrow_sums(partials, rows, M, int(blockIdx.x), kappa, S, sm);
 }
 
 // The sum over the nodes for one particle (wrapped position xw, concentration
@@ -548,18 +555,21 @@ kde_status deposit(const kde_domain* dom, int64_t n, const void* x, const void* 
     hipEvent_t start = timed.start();
     const int order = kap ? 0 : fourier_order(kappa);
     if (!kap && deposit_tries_moments(dom->prec, n, dom->M) && order <= kNarrowMax) {
-      // their partial rows (at most 256 of 2 kNarrowMax) and sums fit the rows
+      // their partial rows (at most 256 of 2 kNarrowMax), sums and series fit the rows
       // of the sum over the particles (n M >= 2^25: at least 2^16 doubles),
       // which overwrites them if it has to run; the word behind the column
       // sums' scratch is nobody else's
-      static_assert(size_t(kMomChunks + 1) * 2 * kNarrowMax <= (size_t(1) << 25) / kDepMaxChunk);
+      static_assert(size_t(kMomChunks) * 2 * kNarrowMax + kNarrowSums <= (size_t(1) << 25) / kDepMaxChunk);
       double* S = partials + size_t(kMomChunks) * 2 * kNarrowMax;
       unsigned int* ok = reinterpret_cast<unsigned int*>(scratch + sums);
       const ScanBufs mom{narrow_plan(n, order), partials, S, ok};
       KDE_RETURN_IF(check_lds(sizeof(double2) * size_t(dom->M) + sizeof(SynthSmem)));
-      KDE_RETURN_IF(launch_moments(static_cast<const double*>(x), n, dom->L, mom, s, start, nullptr, status));
+      KDE_RETURN_IF(launch_moment_rows(static_cast<const double*>(x), n, dom->L, mom, s, start, nullptr, status));
+      hipLaunchKernelGGL(deposit_sums_kernel, dim3(unsigned(narrow_units(order))), dim3(kBlock), 0, s,
+                         (const double*)partials, mom.plan.rows, order, kappa, S);
+      KDE_CHECK_LAUNCH();
       hipLaunchKernelGGL(deposit_synthesis_kernel, dim3(1), dim3(kBlock), sizeof(double2) * size_t(dom->M), s,
-                         (const double*)S, order, kappa, double(n), dom->L, dom->M, rho, ok);
+                         (const double*)S, order, double(n), dom->L, dom->M, rho, ok);
       KDE_CHECK_LAUNCH();
       start = nullptr;
       skip = ok;

@@ -486,7 +486,7 @@ __device__ __forceinline__ void moments_unit(const T* __restrict__ x, int64_t n,
 
 // Sum of the partial rows, kRedCols columns per workgroup: thread (y, c)
 // adds rows y, y + 16, ... in order, then the 16 partial sums are added in
-// order. (Rows read by 16 threads side by side: the serial chain of a
+// a tree. (Rows read by 16 threads side by side: the serial chain of a
 // column is rows / 16 additions.)
 constexpr int kRedCols = 16;
 
@@ -503,10 +503,14 @@ __device__ __forceinline__ void moments_reduce(const double* __restrict__ partia
   red[threadIdx.x] = v;
   __syncthreads();
   if (y == 0 && col < cols) {
-    double t = 0.0;
+    double t[ny];
 #pragma unroll
-    for (int q = 0; q < ny; ++q) t += red[q * kRedCols + c];
-    S[col] = t;
+    for (int q = 0; q < ny; ++q) t[q] = red[q * kRedCols + c];
+#pragma unroll
+    for (int d = ny / 2; d >= 1; d /= 2)
+#pragma unroll
+      for (int q = 0; q < d; ++q) t[q] += t[q + d];
+    S[col] = t[0];
   }
   __syncthreads();
 }
@@ -640,6 +644,57 @@ __device__ __forceinline__ void series_rho(double kappa, int M, double* __restri
   __syncthreads();
 }
 
+// The same to a rounding unit, for series of at most kBlock modes (a thread's run
+// is one). The composed maps leave a few units in a ratio, and a grid's nodes hang on
+// single modes; they are taken out to first order: with r_m = (1 + d_m) times the exact
+// ratio, the recurrence's residual e_m = r_m (2m + kappa r_{m+1}) - kappa, evaluated with
+// its products' and sum's remainders, gives d_m = e_m / kappa - r_m r_{m+1} d_{m+1},
+// an affine recurrence solved by a suffix scan, and rho_m is divided by the
+// product of its ratios' 1 + d.
+__device__ __forceinline__ void series_rho_exact(double kappa, int M, double* __restrict__ rho, ScanSmem& sm) {
+  int m, hm;
+  double p;
+  series_ratios(kappa, M, rho, sm, m, hm, p);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const double r = m <= M ? rho[m] : 0.0;
+  double a = 0.0, b = 0.0;  // d_m = a + b d_{m+1}
+  if (m < M && kappa > 0.0) {
+#pragma clang fp contract(off)
+    const double r1 = rho[m + 1], m2 = 2.0 * double(m);
+    const double h = kappa * r1, s = m2 + h, bb = s - m2;
+    const double sl = ((m2 - (s - bb)) + (h - bb)) + fma(kappa, r1, -h);
+    const double q = r * s;
+    a = ((q - kappa) + fma(r, sl, fma(r, s, -q))) / kappa;
+    b = -r * r1;
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double oa = __shfl_down(a, d, 64), ob = __shfl_down(b, d, 64);
+    if (lane + d < 64) {
+      a = fma(b, oa, a);
+      b *= ob;
+    }
+  }
+  if (lane == 0) {
+    sm.red[w][0] = a;
+    sm.red[w][1] = b;
+  }
+  __syncthreads();  // also: every ratio has been read
+  double above = 0.0;
+  for (int k = kBlock / 64 - 1; k > w; --k) above = fma(sm.red[k][1], above, sm.red[k][0]);
+  double d = fma(b, above, a);
+#pragma unroll
+  for (int k = 1; k < 64; k <<= 1) {
+    const double o = __shfl_up(d, k, 64);
+    if (lane >= k) d += o;
+  }
+  if (lane == 63) sm.red[w][2] = d;
+  __syncthreads();
+  for (int k = 0; k < w; ++k) d += sm.red[k][2];
+  if (m <= M) rho[m] = fma(-d, p * r, p * r);
+  __syncthreads();
+}
+
 // A = sum_m rho_m^2 P_m, A0 = sum_m rho_m^2 (P_m - n), C = sum_m rho_m (P_m -
 // n), m = 1..M, P_m = |S_m|^2, for one concentration, by the whole workgroup.
 __device__ __forceinline__ void series_sums(double kappa, int M, const double* __restrict__ S, double n,
@@ -738,22 +793,52 @@ __device__ __forceinline__ int series_unit(double kappa, int M, const double* __
 // rho[g] = (1/L)(1 + (2/n) sum_m rho_m Re(conj(S_m) e^{i m theta_g})), the
 // deposit of n particles with one concentration, by one workgroup: `tab`
 // (LDS) holds exp(i 2 pi k / Mg), k < Mg. Returns whether the result is as
-// accurate as the sum over the particles: its rounding is a few units of the
-// series' magnitude A = 1 + (2/n) sum_m rho_m |S_m|, so every node has to be
-// at least A / 8 (a density with empty stretches fails this, and so does a
-// NaN). Against long double, 1,048,576 particles with 1 + a cos on 256 nodes:
-// largest error of a node 3.0e-16 at a = 0.5 and 1.9e-15 at a = 0.8 (the sum
-// over the particles: 7.0e-16 and 7.1e-16), of the grid's norm 1.4e-16 and
-// 1.6e-16 (4.1e-16 and 3.8e-16).
+// accurate as the sum over the particles: what is left of its rounding is about
+// half a unit of the series' magnitude A = 1 + (2/n) sum_m rho_m |S_m|, so every node
+// has to be at least A / 8 (a density with empty stretches fails this, and so
+// does a NaN). Against long double, 131,072 particles on 256 nodes, the largest
+// error of a node over 12 samples each (the sum over the particles: 5e-16 to
+// 7e-16): 1 + a cos at kappa = 26 4.2e-16 for a = 0.5 and 5.8e-16 for a = 0.75
+// (A / 6.7), at kappa = 144 3.4e-16 and 5.4e-16 (A / 7.3); a quarter in a clump of 0.02
+// L at kappa = 144 (A / 6.8) 5.2e-16 (1.3e-15). Summed upwards from the first mode,
+// without remainders and with coefficients of a few units it was 1.2e-15 to 4.3e-15.
+constexpr double kSynthLow = 0.125;
+constexpr int kSynthExact = 16;  // leading modes summed with their remainders
 struct SynthSmem {
-  ScanSmem scan;
-  double rho[kNarrowMax + 1];
   double2 w[kNarrowMax + 1];
+  double2 rest[kSynthExact + 1];  // what rounding takes from the first w
   double red[kBlock / 64][2];
 };
 
-__device__ __forceinline__ bool deposit_synthesis(double kappa, int M, const double* __restrict__ S, double n, double L,
-                                                  int Mg, double* __restrict__ out, double2* __restrict__ tab,
+// s += x, with what rounding takes added to `lost` (Knuth's two-sum).
+__device__ __forceinline__ void add_exact(double& s, double x, double& lost) {
+#pragma clang fp contract(off)
+  const double t = s + x, b = t - s;
+  lost += (s - (t - b)) + (x - b);
+  s = t;
+}
+
+// Where the moments of a deposit lie: S, rho behind it (narrow_sums).
+constexpr int kNarrowSums = 3 * kNarrowMax + 1;
+struct NarrowSmem {
+  ScanSmem scan;
+  double rho[kNarrowMax + 1];
+  double red[kBlock];
+};
+// Units of the launch that adds a deposit's partial rows: the column blocks, and one
+// that makes rho_m meanwhile.
+__host__ __device__ inline int narrow_units(int M) { return (2 * M + kRedCols - 1) / kRedCols + 1; }
+__device__ __forceinline__ void narrow_sums(const double* __restrict__ partials, int64_t rows, int M, int unit,
+                                            double kappa, double* __restrict__ S, NarrowSmem& sm) {
+  if (unit + 1 < narrow_units(M)) {
+    moments_reduce(partials, rows, 2 * M, unit, S, sm.red);
+  } else {
+    series_rho_exact(kappa, M, sm.rho, sm.scan);
+    for (int m = 1 + threadIdx.x; m <= M; m += kBlock) S[2 * kNarrowMax + m] = sm.rho[m];
+  }
+}
+
+__device__ __forceinline__ bool deposit_synthesis(int M, const double* __restrict__ S, double n, double L, int Mg, double* __restrict__ out, double2* __restrict__ tab,
                                                   SynthSmem& sm) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   for (int k = t; k < Mg; k += kBlock) {
@@ -761,26 +846,47 @@ __device__ __forceinline__ bool deposit_synthesis(double kappa, int M, const dou
     sincospi(2.0 * double(k) / double(Mg), &sn, &cs);
     tab[k] = double2{cs, sn};
   }
-  series_rho(kappa, M, sm.rho, sm.scan);
+  const double* rho = S + 2 * kNarrowMax;
   double mag = 0.0;
   for (int m = 1 + t; m <= M; m += kBlock) {
-    const double2 w = {sm.rho[m] * S[2 * (m - 1)], sm.rho[m] * S[2 * (m - 1) + 1]};
+    const double2 s = {S[2 * (m - 1)], S[2 * (m - 1) + 1]}, w = {rho[m] * s.x, rho[m] * s.y};
     sm.w[m] = w;
+    if (m <= kSynthExact)
+      sm.rest[m] = {fma(rho[m], s.x, -w.x), fma(rho[m], s.y, -w.y)};
     mag += sqrt(fma(w.x, w.x, w.y * w.y));
   }
   __syncthreads();
   double low = INFINITY;
   for (int g = t; g < Mg; g += kBlock) {
-    double v = 0.0;
-    int idx = 0;
-    for (int m = 1; m <= M; ++m) {
-      idx += g;
-      idx -= idx >= Mg ? Mg : 0;
-      const double2 e = tab[idx], w = sm.w[m];
+    // from the last mode, the smallest, down; the leading modes, whose sum is at
+    // its full size, with the remainders of their products and sums
+    double v = 0.0, vl = 0.0;
+    int idx = int((unsigned(M) * unsigned(g)) % unsigned(Mg));
+    auto next = [&]() {
+      const double2 e = tab[idx];
+      idx -= g;
+      idx += idx < 0 ? Mg : 0;
+      return e;
+    };
+    int m = M;
+#pragma unroll 4
+    for (; m > kSynthExact; --m) {
+      const double2 e = next(), w = sm.w[m];
       v = fma(w.x, e.x, v);
       v = fma(w.y, e.y, v);
     }
-    const double d = 1.0 + 2.0 * v / n;
+#pragma unroll 4
+    for (; m >= 1; --m) {
+      const double2 e = next(), w = sm.w[m], r = sm.rest[m];
+      const double px = w.x * e.x, py = w.y * e.y;
+      vl += fma(w.x, e.x, -px) + fma(w.y, e.y, -py) + fma(r.x, e.x, r.y * e.y);
+      add_exact(v, px, vl);
+      add_exact(v, py, vl);
+    }
+    const double q = 2.0 * v / n;
+    double d = 1.0, dl = (fma(-q, n, 2.0 * v) + 2.0 * vl) / n;
+    add_exact(d, q, dl);
+    d += dl;
     out[g] = d / L;
     low = fmin(low, d);
   }
@@ -801,7 +907,7 @@ __device__ __forceinline__ bool deposit_synthesis(double kappa, int M, const dou
     low = fmin(low, sm.red[k][1]);
   }
   __syncthreads();
-  return low >= 0.125 * (1.0 + 2.0 * mag / n);  // false where a moment is no number: mag is none then
+  return low >= kSynthLow * (1.0 + 2.0 * mag / n);  // false where a moment is no number: mag is none then
 }
 
 // -------------------------------------------------------------------- host
@@ -913,7 +1019,10 @@ inline ScanBufs carve_scan(Carver& c, size_t room, int64_t n, int M) {
 }
 
 // Moments of x into b.S (fourier.hip). The launches record t0 as their
-// start, `done` is zeroed.
+// start, `done` is zeroed. launch_moment_rows stops at the partial rows.
+template <typename T>
+kde_status launch_moment_rows(const T* x, int64_t n, double L, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
+                              hipEvent_t t1, uint32_t* status);
 template <typename T>
 kde_status launch_moments(const T* x, int64_t n, double L, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
                           hipEvent_t t1, uint32_t* status);

@@ -1090,13 +1090,23 @@ kde_status check_fourier_kappas(int B, const double* kappas_h) {
 }  // namespace
 
 template <typename T>
+kde_status launch_moment_rows(const T* x, int64_t n, double L, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
+                              hipEvent_t t1, uint32_t* status) {
+  const MomentPlan& p = b.plan;
+  hipExtLaunchKernelGGL((moments_kernel<T>), dim3(unsigned(p.chunks), unsigned(p.mblocks)), dim3(kMomBlock), 0, s, t0,
+                        t1, 0, x, n, L, p, b.partials, b.done, status);
+  KDE_CHECK_LAUNCH();
+  return KDE_OK;
+}
+template kde_status launch_moment_rows<double>(const double*, int64_t, double, const ScanBufs&, hipStream_t,
+                                               hipEvent_t, hipEvent_t, uint32_t*);
+
+template <typename T>
 kde_status launch_moments(const T* x, int64_t n, double L, const ScanBufs& b, hipStream_t s, hipEvent_t t0,
                           hipEvent_t t1, uint32_t* status) {
   const MomentPlan& p = b.plan;
-  const bool one = p.rows == 1;
-  hipExtLaunchKernelGGL((moments_kernel<T>), dim3(unsigned(p.chunks), unsigned(p.mblocks)), dim3(kMomBlock), 0, s, t0,
-                        one ? t1 : nullptr, 0, x, n, L, p, one ? b.S : b.partials, b.done, status);
-  KDE_CHECK_LAUNCH();
+  const bool one = p.rows == 1;  // (the moments themselves: partials is S)
+  KDE_RETURN_IF(launch_moment_rows(x, n, L, b, s, t0, one ? t1 : nullptr, status));
   if (one) return KDE_OK;
   hipExtLaunchKernelGGL(moments_reduce_kernel, dim3(unsigned(ceil_div(2 * p.M, kRedCols))), dim3(kBlock), 0, s, nullptr,
                         t1, 0, (const double*)b.partials, p.rows, 2 * p.M, b.S);
