@@ -166,22 +166,32 @@ __global__ void __launch_bounds__(kBlock) gather_kernel(const T* __restrict__ x,
 // of the grid's nodes or less at ordinary widths, and a mode costs 9
 // operations where a node costs 21: the backward recurrence t_{m-1} = t_{m+1}
 // + (2m/kappa) t_m of t_m ~ I_m(kappa) (2), X <- X exp(-i theta) + t_m F^_m (6)
-// and the sum of magnitudes (1); out = (t_0 F^_0 + 2 Re X) / t_0. A workgroup
+// and the largest part of X (1); out = (t_0 F^_0 + 2 Re X) / t_0. A workgroup
 // makes the modes it needs itself (order x M multiply-adds, a few per cent
 // of its work), so there is no scratch and no second launch.
 //
-// The rounding of the result is a few units of its magnitude |F^_0| + 2 sum
-// rho_m |F^_m|. Where the result is below 1/256 of that (a zero crossing of
-// the field, the empty stretch of a density), and where the concentration
-// needs too many modes or anything is not finite, the particle is listed and
-// summed over the nodes as gather_kernel does.
+// The rounding of the result is about half a unit of the series' size, |F^_0| and
+// twice the largest part of X; that of the sum over the nodes is one or two units of
+// G = sum |F_g| K_i. So a particle is taken whose value, or whose G (from the field's
+// running sum of magnitudes over one and two of the kernel's widths), is at least
+// 1/16 of the size; below (the empty stretch of a density), where the concentration
+// needs too many modes and where anything is not finite it is listed and summed
+// over the nodes as gather_kernel does. Against long double, 131,072 particles of
+// kappa 14 to 68 on 256 nodes (over the nodes): four random modes and noise, error
+// of the norm 2.6e-16 (3.1e-16), largest error 3.5e-15 G (2.3e-15); 1 + 0.95 cos 1.4e-16
+// (2.8e-16) and 1.8e-15 (1.3e-15); a bump on a floor of 0.01 1.9e-16 (3.6e-16) and 3.2e-15
+// (1.7e-15). Where the modes came from rotations and values of 1/256 were taken: 3.7e-16
+// and 4.8e-15, 1.7e-16 and 4.8e-15, 2.4e-16 and 1.6e-14.
+//
+// The modes are scaled by a power of two (the field's largest node), so that neither
+// a tiny field loses them nor a huge one overflows the recurrence.
 // Bound by the FP64 vector pipe: 1,048,576 particles with concentrations of
-// 14 to 68 on 256 nodes in 38.6 us (172 over the nodes): 18 the 75 modes, 5
-// the first reads (one round of workgroups, so nothing overlaps them), 4 the
-// listed particles, the rest the tables, the modes' sums and the divisions.
-// 256 or 1024 threads 40.8 and 45.8 us, 8 particles per thread 38.3.
+// 14 to 68 on 256 nodes in 34 us (172 over the nodes), about half of it the 75
+// modes, the rest the first reads (one round of workgroups, so nothing overlaps
+// them), the tables, the modes' sums, the divisions and the listed particles.
 constexpr int kGatherBlock = 512;    // threads
 constexpr int kGatherModes = 1023;   // highest mode taken (kappa up to about 12,500)
+constexpr double kGatherLow = 1.0 / 16.0;  // of the series' size
 // Order from which rho_m(kappa) < 1e-18: m asinh(m/kappa) - sqrt(m^2 +
 // kappa^2) + kappa, which bounds -log rho_m from below, is at least 41.45 at m
 // = sqrt(83 (kappa + 7)) for every kappa (and the root of that bound is within
@@ -189,8 +199,8 @@ constexpr int kGatherModes = 1023;   // highest mode taken (kappa up to about 12
 __device__ __forceinline__ int gather_order(float kappa) { return int(ceilf(sqrtf(83.0f * (kappa + 7.0f)))) + 1; }
 static double gather_kappa(int order) { return double(order - 2) * double(order - 2) / 83.0 - 7.0; }
 
-// Dynamic LDS: the node table, the modes up to M/2 (double2), the field and
-// the modes' magnitudes. P particles per thread.
+// Dynamic LDS: the node table, the modes up to M/2 (double2), the field and the
+// running sum of its magnitudes. P particles per thread.
 template <int P>
 __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double* __restrict__ x,
                                                              const double* __restrict__ kap, double kappa_g, bool per,
@@ -199,16 +209,17 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
                                                              double* __restrict__ out, uint32_t* status) {
   extern __shared__ __align__(16) unsigned char dyn[];
   __shared__ double2 unit[256];
-  __shared__ double2 part[kGatherBlock];  // the modes' partial sums; then the list and its exponential table
-  static_assert(sizeof(part) >= 256 * sizeof(double) + 4 * kGatherBlock * sizeof(uint16_t));
-  double* etab = reinterpret_cast<double*>(part);
-  uint16_t* list = reinterpret_cast<uint16_t*>(etab + 256);
-  __shared__ float kwave[kGatherBlock / 64];
+  __shared__ double2 part[kGatherBlock];  // the modes' partial sums; then the list
+  __shared__ double etab[256];
+  static_assert(sizeof(part) >= 4 * kGatherBlock * sizeof(uint16_t));
+  uint16_t* list = reinterpret_cast<uint16_t*>(part);
+  __shared__ float kwave[kGatherBlock / 64], rwave[kGatherBlock / 64];
+  __shared__ int ewave[kGatherBlock / 64];
   __shared__ int listed;
   SinCos<double>* tab = reinterpret_cast<SinCos<double>*>(dyn);
   double2* modes = reinterpret_cast<double2*>(tab + M);
   double* tf = reinterpret_cast<double*>(modes + M / 2 + 1);
-  double* mags = tf + M;
+  float* run = reinterpret_cast<float*>(tf + M);  // sum of |F_g|, g < k, scaled
   const int tid = threadIdx.x;
   const int64_t base = int64_t(blockIdx.x) * (P * kGatherBlock);
   const int cnt = int(min(int64_t(P * kGatherBlock), n - base));
@@ -222,15 +233,20 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
   }
   if (tid == 0) listed = 0;
   unit_table_fill(unit);
+  if (tid < kBlock) exp_table_fill<double>(etab);
+  int fexp = -2000;
   for (int k = tid; k < M; k += kGatherBlock) {
     double sv, cv;
     sincospi(double(k) / double(M), &sv, &cv);
     tab[k] = SinCos<double>{sv, cv};
-    tf[k] = field[k];
+    const double v = field[k];
+    tf[k] = v;
+    if (v != 0.0) fexp = max(fexp, __builtin_amdgcn_frexp_exp(v));
   }
   // those the series does not serve keep kappa = -1
   float kmax = 0.0f;
   const double inv_L = 1.0 / L;
+  const float node_width = float(M) * 0.15915494f;  // M / 2 pi: the kernel's width in nodes times sqrt(kappa)
 #pragma unroll
   for (int p = 0; p < P; ++p) {
     const bool finite = isfinite(f1[p]), serves = finite && kk[p] >= 0.0 && kk[p] <= kcap;
@@ -240,61 +256,91 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
     kk[p] = serves ? kk[p] : -1.0;
   }
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) kmax = fmaxf(kmax, __shfl_xor(kmax, d, 64));
-  if ((tid & 63) == 0) kwave[tid >> 6] = kmax;
+  for (int d = 32; d >= 1; d >>= 1) {
+    kmax = fmaxf(kmax, __shfl_xor(kmax, d, 64));
+    fexp = max(fexp, __shfl_xor(fexp, d, 64));
+  }
+  if ((tid & 63) == 0) {
+    kwave[tid >> 6] = kmax;
+    ewave[tid >> 6] = fexp;
+  }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kGatherBlock / 64; ++w) kmax = fmaxf(kmax, kwave[w]);
+  for (int w = 0; w < kGatherBlock / 64; ++w) {
+    kmax = fmaxf(kmax, kwave[w]);
+    fexp = max(fexp, ewave[w]);
+  }
+  if (fexp == -2000) fexp = 0;  // (a field of zeros)
+  {  // the running sum of |F|: a run of nodes per thread, the runs' sums by shuffles
+    const int len = (M + kGatherBlock - 1) / kGatherBlock, lo = min(tid * len, M), hi = min(lo + len, M);
+    float own = 0.0f;
+    for (int k = lo; k < hi; ++k) own += fabsf(float(ldexp(tf[k], -fexp)));
+    float sum = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const float o = __shfl_up(sum, d, 64);
+      if ((tid & 63) >= d) sum += o;
+    }
+    if ((tid & 63) == 63) rwave[tid >> 6] = sum;
+    __syncthreads();
+    sum -= own;
+    for (int w = 0; w < (tid >> 6); ++w) sum += rwave[w];
+    for (int k = lo; k < hi; ++k) {
+      run[k] = sum;
+      sum += fabsf(float(ldexp(tf[k], -fexp)));
+    }
+    if (hi == M && lo < M) run[M] = sum;
+    __syncthreads();
+  }
 
   if (kmax > 0.0f) {  // (uniform)
     const int ord = __builtin_amdgcn_readfirstlane(min(cap, gather_order(kmax)));
     // F^_m, m = 0..min(ord, M/2) (the others are their conjugates): modes
     // side by side, the node pairs (g, M - g) in runs over the threads that
-    // are left; a phase from the table (which holds half the circle) every 8
-    // nodes and rotations between
+    // are left, every phase from the table (which holds half the circle), in four
+    // sums each
     const int K = min(ord, M / 2) + 1, H = (M - 1) / 2;
     for (int m0 = 0; m0 < K; m0 += kGatherBlock) {
       const int kb = min(K - m0, kGatherBlock), S = kGatherBlock / kb;
       const int m = m0 + tid % kb, sub = tid / kb;
-      auto node_phase = [&](int g) {
-        const int idx = int((2u * unsigned(m) * unsigned(g)) % unsigned(2 * M));
-        const SinCos<double> e = tab[idx >= M ? idx - M : idx];
-        return idx >= M ? double2{-e.c, -e.s} : double2{e.c, e.s};
-      };
       double fr = 0.0, fi = 0.0;
       if (sub < S) {
         const int len = (H + S - 1) / S;
         const int lo = 1 + sub * len, hi = min(H, lo + len - 1);
-        const double2 z1 = node_phase(1);
-        for (int g0 = lo; g0 <= hi; g0 += 8) {
-          double2 z = node_phase(g0);
-          auto pair = [&](int g) {
-            const double a = tf[g], b = tf[M - g];
-            fr = fma(a + b, z.x, fr);
-            fi = fma(a - b, z.y, fi);
-            z = rotate(z, z1);
-          };
-          if (g0 + 7 <= hi) {
+        int idx = int((2u * unsigned(m) * unsigned(lo)) % unsigned(2 * M));
+        double sr[4] = {0.0, 0.0, 0.0, 0.0}, si[4] = {0.0, 0.0, 0.0, 0.0};
+        auto pair = [&](int g, int k) {
+          const bool far = idx >= M;
+          const SinCos<double> e = tab[far ? idx - M : idx];
+          const double a = tf[g], b = tf[M - g];
+          sr[k] = fma(far ? -e.c : e.c, a + b, sr[k]);
+          si[k] = fma(far ? -e.s : e.s, a - b, si[k]);
+          idx += 2 * m;
+          idx -= idx >= 2 * M ? 2 * M : 0;
+        };
+        int g = lo;
+        for (; g + 3 <= hi; g += 4) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) pair(g0 + u);
-          } else {
-            for (int g = g0; g <= hi; ++g) pair(g);
-          }
+          for (int k = 0; k < 4; ++k) pair(g + k, k);
         }
+        for (; g <= hi; ++g) pair(g, 0);
+        fr = (sr[0] + sr[1]) + (sr[2] + sr[3]);
+        fi = (si[0] + si[1]) + (si[2] + si[3]);
       }
       part[tid] = double2{fr, fi};
       __syncthreads();
       if (tid < kb) {
-        for (int q = 1; q < S; ++q) {
-          fr += part[q * kb + tid].x;
-          fi += part[q * kb + tid].y;
+        fr = tf[0];
+        fi = 0.0;
+        double lr = 0.0, li = 0.0;
+        if ((M & 1) == 0) add_exact(fr, (m & 1) ? -tf[M / 2] : tf[M / 2], lr);
+        for (int q = 0; q < S; ++q) {
+          add_exact(fr, part[q * kb + tid].x, lr);
+          add_exact(fi, part[q * kb + tid].y, li);
         }
-        fr += tf[0];
-        if ((M & 1) == 0) fr += (m & 1) ? -tf[M / 2] : tf[M / 2];
-        fr /= double(M);
-        fi /= double(M);
+        fr = ldexp((fr + lr) / double(M), -fexp);
+        fi = ldexp((fi + li) / double(M), -fexp);
         modes[m] = double2{fr, fi};
-        mags[m] = sqrt(fma(fr, fr, fi * fi));
       }
       __syncthreads();
     }
@@ -309,15 +355,18 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
       t[p] = 1.0;
       tp[p] = xr[p] = xi[p] = mag[p] = 0.0;
     }
-    auto mode = [&](int m, int j, double sign) {
+    // `parts` of X for its size: in turn, as it turns from mode to mode, and both
+    // of the last eight
+    auto mode = [&](int m, int j, double sign, int parts) {
       const double2 f = modes[j];
-      const double fy = sign * f.y, a = mags[j], m2 = double(2 * m);
+      const double fy = sign * f.y, m2 = double(2 * m);
 #pragma unroll
       for (int p = 0; p < P; ++p) {
         const double r = fma(xr[p], c1[p], fma(xi[p], s1[p], t[p] * f.x));
         xi[p] = fma(xi[p], c1[p], fma(-xr[p], s1[p], t[p] * fy));
         xr[p] = r;
-        mag[p] = fma(t[p], a, mag[p]);
+        if (parts & 1) mag[p] = fmax(mag[p], fabs(xr[p]));
+        if (parts & 2) mag[p] = fmax(mag[p], fabs(xi[p]));
         const double tn = fma(m2 * ik[p], t[p], tp[p]);
         tp[p] = t[p];
         t[p] = tn;
@@ -342,29 +391,48 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
       }
     };
     // runs of modes m whose remainder mod M rises to M/2 or falls to 0
-    for (int m = ord; m > 0;) {
+    for (int m = ord; m > 8;) {  // (ord >= 26)
       const int r = m % M;
       const bool mirror = 2 * r > M;
-      const int end = m - min(m, mirror ? r - M / 2 : r + 1);
+      const int end = m - min(m - 8, mirror ? r - M / 2 : r + 1);
       int j = mirror ? M - r : r;
       const int step = mirror ? 1 : -1;
       const double sign = mirror ? -1.0 : 1.0;
       rescale();
-      for (; (m - end) & 7; --m, j += step) mode(m, j, sign);
+      for (; (m - end) & 7; --m, j += step) mode(m, j, sign, 3);
       for (; m > end; m -= 8, j += 8 * step) {
         rescale();
 #pragma unroll
-        for (int u = 0; u < 8; ++u) mode(m - u, j + u * step, sign);
+        for (int u = 0; u < 8; ++u) mode(m - u, j + u * step, sign, 1 + (u & 1));
       }
     }
+    rescale();
+#pragma unroll 2
+    for (int m = 8; m >= 1; --m) mode(m, m, 1.0, 3);
     const double f0 = modes[0].x;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int k = p * kGatherBlock + tid;
       const double v = fma(t[p], f0, 2.0 * fma(xr[p], c1[p], xi[p] * s1[p]));
       if (k < cnt) {
-        if (kk[p] >= 0.0 && fabs(v) >= 0.00390625 * fma(t[p], fabs(f0), 2.0 * mag[p]))
-          out[base + k] = v / t[p];
+        const double whole = fma(t[p], fabs(f0), 2.0 * mag[p]);
+        bool good = fabs(v) >= kGatherLow * whole;
+        if (!good && whole > 0.0) {
+          // of a width's peak, the nodes within one width have at least e^-1/2
+          // and those within two at least e^-2
+          const float u = float(f1[p]) * float(M), h = node_width * rsqrtf(fmaxf(float(kk[p]), 1.0f));
+          auto within = [&](float reach) {
+            const int a = int(ceilf(u - reach)), b = int(floorf(u + reach));
+            float sum = run[min(max(b + 1, 0), M)] - run[min(max(a, 0), M)];
+            if (a < 0) sum += run[M] - run[max(M + a, 0)];
+            if (b >= M) sum += run[min(b + 1 - M, M)];
+            return sum;
+          };
+          const float sum = 0.205f * within(h) + 0.136f * within(2.0f * h);
+          good = double(sum) * t[p] >= kGatherLow * whole * double(h);
+        }
+        if (kk[p] >= 0.0 && good && whole < INFINITY && fabs(v) < INFINITY)
+          out[base + k] = ldexp(v / t[p], fexp);
         else
           list[atomicAdd(&listed, 1)] = uint16_t(k);
       }
@@ -379,8 +447,6 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
   // their values do not depend on it
   const int nl = listed;
   if (nl == 0) return;
-  if (tid < kBlock) exp_table_fill<double>(etab);
-  __syncthreads();
   int S = 1;
   while (S < 64 && 2 * S * nl <= kGatherBlock) S *= 2;
   for (int q = tid / S; q < nl; q += kGatherBlock / S) {
@@ -624,8 +690,11 @@ static kde_status launch_gather_t(const kde_domain* dom, int64_t n, const T* x, 
     const double kcap = gather_kappa(cap);
     if (dom->M >= (per ? kGatherPerFrom : kGatherFrom) && n >= 8 * int64_t(dom->M) &&
         n * dom->M >= kGatherPairs && (per || kappa <= kcap)) {
-      const size_t modes = size_t(dom->M) * 3 * sizeof(double) + size_t(dom->M / 2 + 1) * 3 * sizeof(double);
-      KDE_RETURN_IF(check_lds(modes + 256 * sizeof(double2) + kGatherBlock * sizeof(double2) + 64));
+      const size_t tables = size_t(dom->M) * 3 * sizeof(double) + size_t(dom->M / 2 + 1) * sizeof(double2);
+      const size_t fixed = 256 * (sizeof(double2) + sizeof(double)) + kGatherBlock * sizeof(double2) + 128;
+      const size_t runs = (size_t(dom->M) + 1) * sizeof(float);
+      const size_t modes = tables + runs;
+      KDE_RETURN_IF(check_lds(modes + fixed));
       TimedLaunch timed(KDE_KERNEL_GATHER, s);
       if (2 * n > 3 * kGatherSpread)
         hipExtLaunchKernelGGL(gather_modes_kernel<4>, dim3(unsigned(ceil_div(n, 4 * kGatherBlock))), dim3(kGatherBlock), modes, s, timed.start(), timed.stop(), 0, x, kap, kappa, per, n, dom->M, cap, kcap, dom->L, field, out, status);
