@@ -131,6 +131,44 @@ __device__ __forceinline__ T gather_nodes(double xw, double kk, int j, int S, in
   return T(w * tot);
 }
 
+// The same for two particles of one thread (double): a node's reads serve both and
+// their chains overlap. Every term and sum is gather_nodes'.
+__device__ __forceinline__ void gather_nodes2(const double (&xw)[2], const double (&kk)[2], int M, double L,
+                                              const SinCos<double>* tab, const double* tf, const double* etab,
+                                              double (&out)[2]) {
+  PGeo<double> gp[2];
+  double A[2];
+  Acc<double> acc[2];
+  bool sharp[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    make_geo(xw[u], L, M, gp[u]);
+    A[u] = -2.0 * kk[u] * Flt<double>::unit;
+    sharp[u] = A[u] < -2.0 * kNearKappa;
+    acc[u].zero();
+  }
+  const double dx = L / double(M);
+  auto sum = [&](auto near, auto clamp) {
+    for (int g = 0; g < M; ++g) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        double s = node_s(gp[u], g, M, tab);
+        if (decltype(near)::value && sharp[u]) s = near_node_s(s, g, dx, gp[u].w, L);
+        const double a = A[u] * (s * s);
+        acc[u].add(tf[g] * (decltype(clamp)::value ? Flt<double>::ex(a, etab) : Flt<double>::ex_in(a, etab)));
+      }
+    }
+  };
+  if (__all(!sharp[0] && !sharp[1]))
+    sum(std::false_type{}, std::false_type{});
+  else if (__all(A[0] >= kExpTableMin && A[1] >= kExpTableMin))
+    sum(std::true_type{}, std::false_type{});
+  else
+    sum(std::true_type{}, std::true_type{});
+#pragma unroll
+  for (int u = 0; u < 2; ++u) out[u] = (L / M) / (L * i0e_f64(kk[u])) * acc[u].value();
+}
+
 // S lanes per particle (1, 2, 4 or 8, from gather_split). Dynamic LDS: the
 // node table (M SinCos<T>) and the field (M values of T).
 template <typename T, int S>
@@ -214,7 +252,7 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
   static_assert(sizeof(part) >= 4 * kGatherBlock * sizeof(uint16_t));
   uint16_t* list = reinterpret_cast<uint16_t*>(part);
   __shared__ float kwave[kGatherBlock / 64], rwave[kGatherBlock / 64];
-  __shared__ int ewave[kGatherBlock / 64];
+  __shared__ int ewave[kGatherBlock / 64], swave[kGatherBlock / 64];
   __shared__ int listed;
   SinCos<double>* tab = reinterpret_cast<SinCos<double>*>(dyn);
   double2* modes = reinterpret_cast<double2*>(tab + M);
@@ -245,6 +283,7 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
   }
   // those the series does not serve keep kappa = -1
   float kmax = 0.0f;
+  int served = 0;
   const double inv_L = 1.0 / L;
   const float node_width = float(M) * 0.15915494f;  // M / 2 pi: the kernel's width in nodes times sqrt(kappa)
 #pragma unroll
@@ -253,6 +292,7 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
     note_numeric(status, !finite, per && !(isfinite(kk[p]) && kk[p] >= 0.0));
     f1[p] = period_fraction(f1[p], L, inv_L);
     if (serves) kmax = fmaxf(kmax, fmaxf(float(kk[p]), 1e-10f));
+    served += __popcll(__ballot(serves));
     kk[p] = serves ? kk[p] : -1.0;
   }
 #pragma unroll
@@ -263,12 +303,15 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
   if ((tid & 63) == 0) {
     kwave[tid >> 6] = kmax;
     ewave[tid >> 6] = fexp;
+    swave[tid >> 6] = served;
   }
   __syncthreads();
+  int all = 0;
 #pragma unroll
   for (int w = 0; w < kGatherBlock / 64; ++w) {
     kmax = fmaxf(kmax, kwave[w]);
     fexp = max(fexp, ewave[w]);
+    all += swave[w];
   }
   if (fexp == -2000) fexp = 0;  // (a field of zeros)
   {  // the running sum of |F|: a run of nodes per thread, the runs' sums by shuffles
@@ -293,8 +336,10 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
     __syncthreads();
   }
 
-  if (kmax > 0.0f) {  // (uniform)
-    const int ord = __builtin_amdgcn_readfirstlane(min(cap, gather_order(kmax)));
+  // the series runs for every particle, and the others are summed over the nodes
+  // besides: taken where the nodes of those it serves (28 operations each) cost more
+  const int ord = __builtin_amdgcn_readfirstlane(min(cap, gather_order(kmax)));
+  if (kmax > 0.0f && 28.0f * float(M) * float(all) > 10.0f * float(ord) * float(P * kGatherBlock)) {  // (uniform)
     // F^_m, m = 0..min(ord, M/2) (the others are their conjugates): modes
     // side by side, the node pairs (g, M - g) in runs over the threads that
     // are left, every phase from the table (which holds half the circle), in four
@@ -448,14 +493,30 @@ __global__ void __launch_bounds__(kGatherBlock) gather_modes_kernel(const double
   const int nl = listed;
   if (nl == 0) return;
   int S = 1;
-  while (S < 64 && 2 * S * nl <= kGatherBlock) S *= 2;
-  for (int q = tid / S; q < nl; q += kGatherBlock / S) {
+  while (S < 64 && 2 * S * (nl % (2 * kGatherBlock)) <= kGatherBlock) S *= 2;
+  auto over_nodes = [&](int q, int lanes) {
     const int64_t i = base + list[q];
     const double xv = x[i];
-    const double v = gather_nodes<double>(xv - L * floor(xv / L), per ? kap[i] : kappa_g, tid & (S - 1), S, M, L, tab,
-                                          tf, etab);
-    if ((tid & (S - 1)) == 0) out[i] = v;
+    const int j = tid & (lanes - 1);
+    const double v = gather_nodes<double>(xv - L * floor(xv / L), per ? kap[i] : kappa_g, j, lanes, M, L, tab, tf, etab);
+    if (j == 0) out[i] = v;
+  };
+  int first = 0;  // of those not done two to a thread
+  for (; first + 2 * kGatherBlock <= nl; first += 2 * kGatherBlock) {
+    double xw[2], k2[2], v[2];
+    int64_t i[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      i[u] = base + list[first + u * kGatherBlock + tid];
+      const double xv = x[i[u]];
+      xw[u] = xv - L * floor(xv / L);
+      k2[u] = per ? kap[i[u]] : kappa_g;
+    }
+    gather_nodes2(xw, k2, M, L, tab, tf, etab, v);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) out[i[u]] = v[u];
   }
+  for (int q = first + tid / S; q < nl; q += kGatherBlock / S) over_nodes(q, S);
 }
 
 template <typename T>
@@ -668,14 +729,13 @@ static int gather_split(int64_t n, int M) {
 // on, on grids with at least 8 particles per node (each workgroup makes its
 // modes), of at least 64 nodes with one concentration and 256 with per-
 // particle ones, which only the device sees. 131,072 particles on 256 nodes:
-// 13.5 us at kappa = 26 (32.3 over the nodes), 23.7 at 300 (36.9), 36.1 at
-// 1200 (36.3); 16,000 on 256: 11.3 (8.0); 40,000 on 4096: 34 (261); 300,000
-// on 128 with concentrations of 300: 43 (40). The series is taken up to 7/4 M
-// modes, where it costs what the nodes do; a call whose per-particle
-// concentrations are all sharper (kappa > 2300 on 256 nodes: a kernel narrower than
-// the spacing) is up to a quarter slower than with one workgroup
-// per 256 particles. 4, 2 or 1 particles per thread by what fills the chip
-// with two workgroups per CU.
+// 11.2 us at kappa = 26 (29 over the nodes), 22.6 at 300 (34), 29.6 at 700 (34),
+// 34.8 at 1200 (34); 16,000 on 256: 11.3 (8.0); 40,000 on 4096: 109 at 300 (350). The
+// series is taken up to 7/4 M modes, where it costs what the nodes do; a workgroup
+// whose particles are mostly sharper sums all of them over the nodes, two to a
+// thread: 1,048,576 on 256 nodes all above 1500 (a kernel about as narrow as the
+// spacing) 218 us (190), 131,072 all above 10,000 43 us (34). 4, 2 or 1
+// particles per thread by what fills the chip with two workgroups per CU.
 constexpr int kGatherFrom = 64, kGatherPerFrom = 256;
 constexpr int64_t kGatherPairs = int64_t(1) << 25;
 constexpr int64_t kGatherSpread = 512 * kGatherBlock;
