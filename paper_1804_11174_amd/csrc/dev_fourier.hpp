@@ -283,19 +283,24 @@ __device__ __forceinline__ void moments_wide(const T* __restrict__ x, int64_t lo
     }
     __syncthreads();
   }
-  // a tile's sums: the teams' and the slices' in order
+  // a tile's sums: to the first wave's those of the others, the teams' and the
+  // slices' in order
   double* red = reinterpret_cast<double*>(sm.z);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    red[r * kMomBlock + tid] = acc0[r];
-    red[(4 + r) * kMomBlock + tid] = acc1[r];
-  }
-  __syncthreads();
-  if (team == 0 && slice == 0 && mul) {
+  const bool first = team == 0 && slice == 0;
+  if (!first) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      acc0[r] = acc1[r] = 0.0;
-      for (int q = 0; q < p.ks; ++q) {
+      red[r * kMomBlock + tid] = acc0[r];
+      red[(4 + r) * kMomBlock + tid] = acc1[r];
+    }
+  }
+  __syncthreads();
+  if (first && mul) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      acc0[r] += red[r * kMomBlock + tid + kMomTeam];
+      acc1[r] += red[(4 + r) * kMomBlock + tid + kMomTeam];
+      for (int q = 1; q < p.ks; ++q) {
         const int at = tid + 64 * q * p.tiles;
         acc0[r] += red[r * kMomBlock + at] + red[r * kMomBlock + at + kMomTeam];
         acc1[r] += red[(4 + r) * kMomBlock + at] + red[(4 + r) * kMomBlock + at + kMomTeam];
