@@ -166,6 +166,9 @@ __device__ __forceinline__ void make_geo(double xw, double L, int M, PGeo<float>
   double g0 = floor(v + 0.5);
   const double d = v - g0;
   if (g0 >= double(M)) g0 -= double(M);
+  // (a position beyond 2^53 periods leaves the wrap anywhere: the tables are
+  // read inside, whatever its value is worth)
+  g0 = fmin(fmax(g0, 0.0), double(M - 1));
   double sb, cb;
   sincospi(d / double(M), &sb, &cb);
   p.g0 = int(g0);

@@ -275,6 +275,7 @@ __device__ __forceinline__ TriGeo<T> tri_geo(double xi, double h, double L, int 
   double g0 = floor(v + 0.5);
   const double d = v - g0;
   if (g0 >= double(M)) g0 -= double(M);
+  g0 = fmin(fmax(g0, 0.0), double(M - 1));  // (the wrap of a position beyond 2^53 periods)
   p.g0 = int(g0);
   p.delta = T(d);
   const bool ok = (h > 0.0) && (h <= 0.5 * L);
