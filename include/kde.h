@@ -204,7 +204,9 @@ kde_status kde_workspace_size(int32_t op, const kde_domain* dom, int64_t N, int3
  * evaluated through the sample's Fourier moments (below), the same sums in
  * O(N M) work; there the diagonal that separates the double sums from S1 and
  * S2 is at most a few times S2 wherever the particles lie, so they keep their
- * accuracy. Larger ones, and the float form, are summed over the pairs.
+ * accuracy. Larger ones, and the float form, are summed over the pairs, and
+ * so is the whole list of a sample of at most 256 particles that needs the
+ * pairs anyway and would be spared too little of them.
  * Of the pair sums, terms whose exponent lies below -70 (each smaller than
  * e^-70 times the largest term of its sum) may be left out: the kernel skips
  * them where that saves work and keeps them where it does not (the sums
@@ -550,7 +552,8 @@ kde_status kde_damping_rate(const double* energy_h, int64_t n, double dt, double
  * thread admits them into `nslots` slots (each a HIP stream of default
  * priority) whenever a slot is free and their workspaces fit in the free
  * part of the caller's arena (the HBM budget). A request's estimated work is
- * B n_cv (n_cv - 1) / 2 CV pair terms plus 2 N M deposit terms plus 5e7; it
+ * B n_cv (n_cv - 1) / 2 CV pair terms plus 2 N M deposit terms plus 5e7 (in
+ * double, whose scans seldom go over the pairs, an upper estimate); it
  * is large from large_terms on. Large requests run alone, at most
  * large_slots at a time, in arrival order. Otherwise the oldest small
  * request heads a group, joined by up to max_batch - 1 later small ones

@@ -995,12 +995,20 @@ inline double scan_kappa_limit(int64_t n) {
   const double k = double(n) / (3.0 * 3.141592653589793);
   return std::fmin(k * k, KDE_MAX_FOURIER_KAPPA);
 }
-// How many leading concentrations of an ascending list that is.
+// How many leading concentrations of an ascending list are taken through the
+// moments: those, but none of a sample within one tile whose list needs the pair
+// kernel as well and would be spared too little of it: passes of four, each
+// about as long as the sample, against two launches of about 9 us. 64
+// particles, 8 concentrations to 1e4, three of them below the limit (no pass):
+// 103 us over pairs alone, 109 by both; 30, 16 to 1e4, four below (one): 66 and
+// 74; 200, 16 to 1e4, ten below (two): 305 and 199.
 inline int scan_fourier_count(int prec, int64_t n, const double* kappas, int B) {
   if (prec != KDE_F64) return 0;
   const double lim = scan_kappa_limit(n);
   int b = 0;
   while (b < B && kappas[b] <= lim) ++b;
+  const int spared = (B + 3) / 4 - (B - b + 3) / 4;
+  if (b < B && n <= kCvTile && n * spared < 64) return 0;
   return b;
 }
 

@@ -72,7 +72,19 @@ static void plans() {
   }
 }
 
+// Which leading concentrations of a list go through the moments.
+static void lists() {
+  const double one[] = {0.3, 1.0, 3.7, 13.9, 51.8, 193.0, 720.0, 2683.0, 1e4};
+  EXPECT(scan_fourier_count(KDE_F32, 65536, one, 9) == 0);
+  EXPECT(scan_fourier_count(KDE_F64, 65536, one, 9) == 9);
+  EXPECT(scan_fourier_count(KDE_F64, 64, one, 4) == 4);   // all below (64 / 3 pi)^2 = 46.1
+  EXPECT(scan_fourier_count(KDE_F64, 64, one + 1, 8) == 0);  // three of eight: two passes of the rest as of all
+  EXPECT(scan_fourier_count(KDE_F64, 64, one, 9) == 4);      // nine are three passes, the other five two
+  EXPECT(scan_fourier_count(KDE_F64, 257, one + 1, 8) == 6 && scan_fourier_count(KDE_F64, 10, one, 9) == 0);
+}
+
 int main() {
+  lists();
   plans();
   orders();
   bracket_lengths();

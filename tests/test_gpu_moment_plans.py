@@ -92,3 +92,20 @@ def test_batch_without_a_place_for_the_objective(gpu):
                 assert host(ks)[k] == kap[am]
         finally:
             gpu.kde_batch_destroy(h)
+
+
+@pytest.mark.parametrize("n,B", [(2, 8), (10, 8), (10, 9), (64, 8), (64, 9), (256, 8), (257, 8)])
+def test_small_samples_whose_lists_need_the_pairs_too(gpu, n, B):
+    x = W.cosine_positions(np.random.default_rng([96, n]), n, L, 0.4, 0.5)
+    kap = W.log_kappas(1.0, 1e4, B)
+    announce("moment plans, small lists", n, B)
+    cv, sums, am = gpu.cv_scan(to_gpu(x), L, kap)
+    ref, S1, S2 = ocv.cv_curve(x, L, kap)
+    first = conv2_at_zero(kap, L) / n + 2 * S1 / n ** 2
+    assert np.all(np.abs(host(cv) - ref) <= 1e-12 * np.maximum(np.abs(ref), 0.01 * first))
+    bt = gpu.Batch([to_gpu(x)], [L], [16], kap)
+    try:
+        bt.run()
+        assert np.array_equal(host(bt.cv[0]), host(cv))
+    finally:
+        bt.close()
