@@ -358,7 +358,8 @@ __global__ void __launch_bounds__(kBlock) batch_pilot_sum_kernel(BatchArgs a, FK
   const SetDev& s = a.sets[si];
   const int order = uni32(kap.order[*s.kbest]), unit = int(u - uni64(pf[si]));
   if (order > kNarrowMax || unit >= narrow_units(order)) return;
-  narrow_sums(uni_ptr(s.dep_part), narrow_plan(uni64(s.n), order).rows, order, unit, *s.kstar, uni_ptr(s.pil_S), sm);
+  narrow_sums(uni_ptr(s.dep_part), narrow_plan(uni64(s.n), order).rows, order, unit, *s.kstar, uni_ptr(s.pil_S),
+              s.pil_ok, sm);
 }
 
 __global__ void __launch_bounds__(kBlock) batch_pilot_synthesis_kernel(BatchArgs a, FKappas kap) {
@@ -367,12 +368,13 @@ __global__ void __launch_bounds__(kBlock) batch_pilot_synthesis_kernel(BatchArgs
   const int64_t* pf = a.prefix + PF_PIL_SYNTH * (a.nsets + 1);
   const int64_t u = int64_t(blockIdx.x);
   if (u >= pf[a.nsets]) return;
-  const SetDev& s = a.sets[uni32(find_set(pf, a.nsets, u))];
+  const int si = uni32(find_set(pf, a.nsets, u));
+  const SetDev& s = a.sets[si];
   const int order = uni32(kap.order[*s.kbest]);
   if (order > kNarrowMax) return;
-  const bool good = deposit_synthesis(order, uni_ptr(s.pil_S), double(s.n), s.L, uni32(s.M),
+  const bool good = deposit_synthesis(order, uni_ptr(s.pil_S), double(s.n), s.L, uni32(s.M), int(u - uni64(pf[si])),
                                       uni_ptr(s.pilot), reinterpret_cast<double2*>(dyn), sm);
-  if (good && threadIdx.x == 0) *s.pil_ok = 1u;
+  if (!good && threadIdx.x == 0) *s.pil_ok = 0u;
 }
 
 // Deposit chunks of every set: the pilot at kappa* (PER = false) or the
@@ -548,7 +550,7 @@ static size_t layout_batch(const BatchPlan& b, void* ws, std::vector<SetDev>* de
                                    d.b0 > 0 ? d.mom.chunks * d.mom.mblocks : 0,
                                    d.b0 > 0 && d.mom.rows > 1 ? ceil_div(2 * d.mom.M, kRedCols) : 0, int64_t(d.b0), pairs ? 1 : 0,
                                    d.pil_mom ? pil.chunks : 0, d.pil_mom ? narrow_units(kNarrowMax) : 0,
-                                   int64_t(d.pil_mom)};
+                                   d.pil_mom ? synthesis_parts(in.M) : 0};
     for (int k = 0; k < PF_COUNT; ++k) {
       if (prefix) (*prefix)[size_t(k) * (ns + 1) + r] = acc[k];
       acc[k] += per[k];

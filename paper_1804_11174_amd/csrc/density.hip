@@ -45,22 +45,23 @@ __global__ void __launch_bounds__(kBlock) deposit_kernel(const T* __restrict__ x
   deposit_block<T, PER, G>(x, kap, kappa_g, n, M, L, lo, cnt, partials + int64_t(blockIdx.x) * M, tab, sm, status);
 }
 
-// The grid from the particles' moments (dev_fourier.hpp); *ok stays 0 where
+// The grid from the particles' moments (dev_fourier.hpp); *ok becomes 0 where
 // the sum over the particles has to follow. Dynamic LDS: Mg unit vectors.
 __global__ void __launch_bounds__(kBlock) deposit_synthesis_kernel(const double* __restrict__ S, int M, double n,
                                                                   double L, int Mg, double* __restrict__ rho,
                                                                   unsigned int* ok) {
   __shared__ SynthSmem sm;
   extern __shared__ __align__(16) unsigned char dyn[];
-  const bool good = deposit_synthesis(M, S, n, L, Mg, rho, reinterpret_cast<double2*>(dyn), sm);
-  if (good && threadIdx.x == 0) *ok = 1u;
+  const bool good = deposit_synthesis(M, S, n, L, Mg, blockIdx.x, rho, reinterpret_cast<double2*>(dyn), sm);
+  if (!good && threadIdx.x == 0) *ok = 0u;
 }
 
 // The rows' sums and the series' coefficients for it.
 __global__ void __launch_bounds__(kBlock) deposit_sums_kernel(const double* __restrict__ partials, int64_t rows, int M,
-                                                             double kappa, double* __restrict__ S) {
+                                                             double kappa, double* __restrict__ S,
+                                                             unsigned int* ok) {
   __shared__ NarrowSmem sm;
-  narrow_sums(partials, rows, M, int(blockIdx.x), kappa, S, sm);
+  narrow_sums(partials, rows, M, int(blockIdx.x), kappa, S, ok, sm);
 }
 
 // The sum over the nodes for one particle (wrapped position xw, concentration
@@ -693,10 +694,10 @@ kde_status deposit(const kde_domain* dom, int64_t n, const void* x, const void* 
       KDE_RETURN_IF(check_lds(sizeof(double2) * size_t(dom->M) + sizeof(SynthSmem)));
       KDE_RETURN_IF(launch_moment_rows(static_cast<const double*>(x), n, dom->L, mom, s, start, nullptr, status));
       hipLaunchKernelGGL(deposit_sums_kernel, dim3(unsigned(narrow_units(order))), dim3(kBlock), 0, s,
-                         (const double*)partials, mom.plan.rows, order, kappa, S);
+                         (const double*)partials, mom.plan.rows, order, kappa, S, ok);
       KDE_CHECK_LAUNCH();
-      hipLaunchKernelGGL(deposit_synthesis_kernel, dim3(1), dim3(kBlock), sizeof(double2) * size_t(dom->M), s,
-                         (const double*)S, order, double(n), dom->L, dom->M, rho, ok);
+      hipLaunchKernelGGL(deposit_synthesis_kernel, dim3(unsigned(synthesis_parts(dom->M))), dim3(kBlock),
+                         sizeof(double2) * size_t(dom->M), s, (const double*)S, order, double(n), dom->L, dom->M, rho, ok);
       KDE_CHECK_LAUNCH();
       start = nullptr;
       skip = ok;

@@ -796,7 +796,7 @@ __device__ __forceinline__ int series_unit(double kappa, int M, const double* __
 // ---------------------------------------------- a grid density from moments
 
 // rho[g] = (1/L)(1 + (2/n) sum_m rho_m Re(conj(S_m) e^{i m theta_g})), the
-// deposit of n particles with one concentration, by one workgroup: `tab`
+// deposit of n particles with one concentration, 256 nodes by one workgroup: `tab`
 // (LDS) holds exp(i 2 pi k / Mg), k < Mg. Returns whether the result is as
 // accurate as the sum over the particles: what is left of its rounding is about
 // half a unit of the series' magnitude A = 1 + (2/n) sum_m rho_m |S_m|, so every node
@@ -834,7 +834,9 @@ struct NarrowSmem {
 // that makes rho_m meanwhile.
 __host__ __device__ inline int narrow_units(int M) { return (2 * M + kRedCols - 1) / kRedCols + 1; }
 __device__ __forceinline__ void narrow_sums(const double* __restrict__ partials, int64_t rows, int M, int unit,
-                                            double kappa, double* __restrict__ S, NarrowSmem& sm) {
+                                            double kappa, double* __restrict__ S, unsigned int* ok,
+                                            NarrowSmem& sm) {
+  if (unit == 0 && threadIdx.x == 0) *ok = 1u;  // until a part of the synthesis refuses
   if (unit + 1 < narrow_units(M)) {
     moments_reduce(partials, rows, 2 * M, unit, S, sm.red);
   } else {
@@ -843,7 +845,11 @@ __device__ __forceinline__ void narrow_sums(const double* __restrict__ partials,
   }
 }
 
-__device__ __forceinline__ bool deposit_synthesis(int M, const double* __restrict__ S, double n, double L, int Mg, double* __restrict__ out, double2* __restrict__ tab,
+// Workgroups of it: a node per thread.
+__host__ __device__ inline int synthesis_parts(int Mg) { return (Mg + kBlock - 1) / kBlock; }
+
+__device__ __forceinline__ bool deposit_synthesis(int M, const double* __restrict__ S, double n, double L, int Mg,
+                                                  int part, double* __restrict__ out, double2* __restrict__ tab,
                                                   SynthSmem& sm) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   for (int k = t; k < Mg; k += kBlock) {
@@ -862,7 +868,8 @@ __device__ __forceinline__ bool deposit_synthesis(int M, const double* __restric
   }
   __syncthreads();
   double low = INFINITY;
-  for (int g = t; g < Mg; g += kBlock) {
+  const int g = part * kBlock + t;
+  if (g < Mg) {
     // from the last mode, the smallest, down; the leading modes, whose sum is at
     // its full size, with the remainders of their products and sums
     double v = 0.0, vl = 0.0;
@@ -893,7 +900,7 @@ __device__ __forceinline__ bool deposit_synthesis(int M, const double* __restric
     add_exact(d, q, dl);
     d += dl;
     out[g] = d / L;
-    low = fmin(low, d);
+    low = d < INFINITY ? d : -1.0;  // (no number: refused)
   }
   mag = wave_sum(mag);
 #pragma unroll
@@ -919,11 +926,12 @@ __device__ __forceinline__ bool deposit_synthesis(int M, const double* __restric
 
 // Whether the deposit of n particles on Mg nodes with one concentration tries
 // the moments first (double form; a concentration whose series fits the
-// narrow form, kappa up to about 144.8): they cost about 20 us with the 3 launches that find
-// nothing to do, plus 12 ps per particle, against 0.65 ps per particle and
-// node (1,048,576 on 256 nodes: 28 us against 174; where the grid is refused
-// they come on top), so the line is drawn where the sum over the particles
-// takes about as long, 2^25 pairs.
+// narrow form, kappa up to about 144.8): they cost about 15 us with the launches
+// that find nothing to do, plus 12 ps per particle, against 0.65 ps per particle
+// and node (1,048,576 on 256 nodes: 28 us against 168; 131,072: 21 and 35; 8192 on
+// 4096: 22 and 105), so the line is drawn at 2^25 pairs, where 40,000 on 100 nodes
+// just below take 12.5. Where the grid is refused, which the host cannot see, they
+// come on top of the sum over the particles (190 us, and 45).
 __host__ __device__ inline bool deposit_tries_moments(int prec, int64_t n, int Mg) {
   return prec == KDE_F64 && n * int64_t(Mg) >= (int64_t(1) << 25);
 }
