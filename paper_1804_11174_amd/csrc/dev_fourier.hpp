@@ -926,12 +926,12 @@ __device__ __forceinline__ bool deposit_synthesis(int M, const double* __restric
 
 // Whether the deposit of n particles on Mg nodes with one concentration tries
 // the moments first (double form; a concentration whose series fits the
-// narrow form, kappa up to about 144.8): they cost about 15 us with the launches
-// that find nothing to do, plus 12 ps per particle, against 0.65 ps per particle
-// and node (1,048,576 on 256 nodes: 28 us against 168; 131,072: 21 and 35; 8192 on
-// 4096: 22 and 105), so the line is drawn at 2^25 pairs, where 40,000 on 100 nodes
-// just below take 12.5. Where the grid is refused, which the host cannot see, they
-// come on top of the sum over the particles (190 us, and 45).
+// narrow form, kappa up to about 144.8): they cost about 20 us with the launches
+// that find nothing to do, and 8 ps per particle beyond that, against 0.65 ps
+// per particle and node (1,048,576 on 256 nodes: 28 us against 178; 131,072: 21
+// and 36; 8192 on 4096: 22 and 104). Where the grid is refused, which the host
+// cannot see, they come on top of the sum over the particles (200 us, and 46), so
+// the line is drawn at 2^25 pairs, the second of these sizes.
 __host__ __device__ inline bool deposit_tries_moments(int prec, int64_t n, int Mg) {
   return prec == KDE_F64 && n * int64_t(Mg) >= (int64_t(1) << 25);
 }
